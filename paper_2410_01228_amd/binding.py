@@ -158,6 +158,10 @@ EXPORTS = [
 
 def _stream(stream) -> int:
     if stream is None:
+        # The handle alone: building the torch.cuda.Stream object around it took 2.7 us a call, a
+        # fifth of the host time of a small append + attention step (13.9 us).
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
