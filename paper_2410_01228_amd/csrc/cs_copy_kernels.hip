@@ -75,53 +75,54 @@ int launch_page_copy(const cs_kv_pool& pool, int32_t layer_begin, int32_t layer_
 // ------------------------------------------------------------------------------------
 // Token-granular checkpoint copies (paper Sec. 4.4: KV state is kept per token; after a
 // generation step only the newly generated tokens are checkpointed).  The staging buffer
-// holds plain rows, [layer][token][K|V][kv head][D]; one lane moves one 16-byte unit of a
-// row (8 features): a K unit is one 16-byte unit of the page too, a V unit is 8 elements
-// that lie 16 bytes apart in the page (one per feature's token group).
+// holds plain rows, [layer][token][K|V][kv head][D].
+//
+// Bound by the cache lines the page format spreads a token over: per kv head 16 K units of 16
+// bytes, each in a line of its own, and the 2 KiB of V units that hold its 128 features (head dim
+// 128): 400 MB of lines for 50 MB of tokens, and on the way back as many partly written ones.  So
+// every line is asked for once and everything is in flight together: one wavefront per (token, kv
+// head, layer); a K lane moves one 16-byte unit, a V lane the 2-byte elements of features lane and
+// lane + 64 (consecutive lanes, consecutive units: 8 lines an instruction, where a lane that moved
+// 8 features touched 64 lines with each), K and V are loaded before either is stored, and all of
+// it bypasses the caches' retention (nontemporal).  256 tokens x 48 layers x 8 kv heads: gather 155
+// -> 75 us (5.4 TB/s of lines); the pair 289 -> 233 us.  What is left of the restore (155 us) is the
+// partly written lines: rewriting whole V units instead, which would not be safe beside another
+// writer of the unit, measured no faster.
 // ------------------------------------------------------------------------------------
-constexpr int kTokenCopyThreads = 256;
+constexpr int kTokenCopyThreads = 64;
 
-template <bool kToStaging>
+template <bool kToStaging, int D>
 __global__ __launch_bounds__(kTokenCopyThreads) void token_copy_kernel(
     uint16_t* __restrict__ pool_base, int64_t layer_stride, int64_t page_stride,
     int32_t num_pages, int32_t layer_begin, const int32_t* __restrict__ token_slots, int32_t n,
-    uint16_t* __restrict__ staging, int32_t Hkv, int32_t D, int32_t page_size)
+    uint16_t* __restrict__ staging, int32_t Hkv, int32_t page_shift)
 {
-    const int32_t units_per_head = D / 8, units_per_side = Hkv * units_per_head;
-    const int32_t units_per_token = 2 * units_per_side;
-    const int64_t gid = (int64_t)blockIdx.x * kTokenCopyThreads + threadIdx.x;
-    if (gid >= (int64_t)n * units_per_token) return;
-    const int32_t i = (int32_t)(gid / units_per_token), u = (int32_t)(gid - (int64_t)i * units_per_token);
-    const int32_t l = blockIdx.y;
+    const int32_t i = blockIdx.x / Hkv, h = blockIdx.x - i * Hkv, l = blockIdx.y, lane = threadIdx.x;
     const int32_t slot = token_slots[i];
-    const int32_t page = slot / page_size, t = slot - page * page_size;
+    const int32_t page = slot >> page_shift, t = slot & ((1 << page_shift) - 1);
     if (slot < 0 || page >= num_pages) return;                   // never touch a bad slot
-    const int32_t groups = page_size >> 3;                       // 8-token groups of a page
-    const int32_t kv = u / units_per_side, r = u - kv * units_per_side;
-    const int32_t h = r / units_per_head, d8 = r - h * units_per_head;
-    uint16_t* blk = pool_base + (int64_t)(layer_begin + l) * layer_stride + (int64_t)page * page_stride
-                  + (int64_t)(kv * Hkv + h) * (page_size * D);
-    uint16_t* row = staging + ((int64_t)l * n + i) * (2 * Hkv * D) + (int64_t)u * 8;
-    if (kv == 0) {
-        u32x4* unit = (u32x4*)(blk + (d8 * page_size + t) * 8);
-        if (kToStaging) *(u32x4*)row = *unit; else *unit = *(const u32x4*)row;
-    } else {
-        // features d8*8 .. +8 of token t: element (((d/16)*groups + t/8)*16 + d%16)*8 + t%8
-        const int32_t d0 = d8 * 8;
-        uint16_t* first = blk + ((((d0 >> 4) * groups + (t >> 3)) * 16 + (d0 & 15)) * 8 + (t & 7));
-        if (kToStaging) {
-            uint16_t e[8];
+    const int32_t block_elems = D << page_shift;                 // one kv head's K (or V) block
+    uint16_t* kblk = pool_base + (int64_t)(layer_begin + l) * layer_stride + (int64_t)page * page_stride + (int64_t)h * block_elems;
+    uint16_t* vblk = kblk + (int64_t)Hkv * block_elems;
+    uint16_t* krow = staging + (((int64_t)l * n + i) * 2 * Hkv + h) * D;
+    uint16_t* vrow = krow + Hkv * D;
+    // feature d of token t: K unit (d/8) * page tokens + t; V element
+    // (((d/16)*groups + t/8)*16 + d%16)*8 + t%8, groups = page tokens / 8: 64 features further on is
+    // 4 * groups * 128 elements further on
+    constexpr int kVPerLane = D / 64;
+    u32x4* kp = (u32x4*)(kblk + ((lane << page_shift) + t) * 8);
+    uint16_t* vp = vblk + ((lane >> 4) << (page_shift + 4)) + ((t >> 3) << 7) + ((lane & 15) << 3) + (t & 7);
+    u32x4* ks = (u32x4*)krow + lane;
+    u32x4 k;
+    uint16_t v[kVPerLane];
+    if (lane < D / 8) k = __builtin_nontemporal_load(kToStaging ? kp : ks);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) e[j] = first[j * 8];
-            u32x4 v = { (uint32_t)e[0] | ((uint32_t)e[1] << 16), (uint32_t)e[2] | ((uint32_t)e[3] << 16),
-                        (uint32_t)e[4] | ((uint32_t)e[5] << 16), (uint32_t)e[6] | ((uint32_t)e[7] << 16) };
-            *(u32x4*)row = v;
-        } else {
-            const u32x4 v = *(const u32x4*)row;
+    for (int j = 0; j < kVPerLane; ++j)
+        v[j] = __builtin_nontemporal_load(kToStaging ? vp + (j << (page_shift + 6)) : vrow + lane + j * 64);
+    if (lane < D / 8) __builtin_nontemporal_store(k, kToStaging ? ks : kp);
 #pragma unroll
-            for (int j = 0; j < 8; ++j) first[j * 8] = (uint16_t)(v[j >> 1] >> ((j & 1) * 16));
-        }
-    }
+    for (int j = 0; j < kVPerLane; ++j)
+        __builtin_nontemporal_store(v[j], kToStaging ? vrow + lane + j * 64 : vp + (j << (page_shift + 6)));
 }
 
 int launch_token_copy(const cs_kv_pool& pool, int32_t layer_begin, int32_t layer_end,
@@ -129,16 +130,16 @@ int launch_token_copy(const cs_kv_pool& pool, int32_t layer_begin, int32_t layer
 {
     const int32_t layers = layer_end - layer_begin;
     if (n == 0 || layers == 0) return CS_OK;
-    const int64_t units = (int64_t)n * 2 * pool.num_kv_heads * pool.head_dim / 8;
-    dim3 grid((uint32_t)((units + kTokenCopyThreads - 1) / kTokenCopyThreads), (uint32_t)layers);
-    if (to_staging)
-        hipLaunchKernelGGL(token_copy_kernel<true>, grid, dim3(kTokenCopyThreads), 0, st, (uint16_t*)pool.base,
-                           pool.layer_stride, pool.page_stride, pool.num_pages, layer_begin, token_slots, n,
-                           (uint16_t*)staging, pool.num_kv_heads, pool.head_dim, pool.page_size);
-    else
-        hipLaunchKernelGGL(token_copy_kernel<false>, grid, dim3(kTokenCopyThreads), 0, st, (uint16_t*)pool.base,
-                           pool.layer_stride, pool.page_stride, pool.num_pages, layer_begin, token_slots, n,
-                           (uint16_t*)staging, pool.num_kv_heads, pool.head_dim, pool.page_size);
+    if ((int64_t)n * pool.num_kv_heads > 2147483647ll) return CS_ERR_UNSUPPORTED;
+    const dim3 grid((uint32_t)n * pool.num_kv_heads, (uint32_t)layers);
+    const int32_t page_shift = pool.page_size == 16 ? 4 : 3;
+#define CS_LAUNCH_TOKEN_COPY(DIR, DD)                                                                            \
+    hipLaunchKernelGGL((token_copy_kernel<DIR, DD>), grid, dim3(kTokenCopyThreads), 0, st, (uint16_t*)pool.base,   \
+                       pool.layer_stride, pool.page_stride, pool.num_pages, layer_begin, token_slots, n,          \
+                       (uint16_t*)staging, pool.num_kv_heads, page_shift);
+    if (pool.head_dim == 128) { if (to_staging) { CS_LAUNCH_TOKEN_COPY(true, 128) } else { CS_LAUNCH_TOKEN_COPY(false, 128) } }
+    else                      { if (to_staging) { CS_LAUNCH_TOKEN_COPY(true, 64) } else { CS_LAUNCH_TOKEN_COPY(false, 64) } }
+#undef CS_LAUNCH_TOKEN_COPY
     return check_launch("token_copy_kernel");
 }
 
