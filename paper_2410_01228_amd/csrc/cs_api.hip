@@ -6,6 +6,7 @@
 #include "cs_common.h"
 #include <atomic>
 #include <functional>
+#include <random>
 #include <vector>
 #include <string.h>
 #include <stdio.h>
@@ -177,9 +178,8 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim) {
             recs[n_rec++] = Rec{k > 1 ? decode_chunk_keys(n, k) : n, s, k};
         }
         std::stable_sort(recs, recs + n_rec, [](const Rec& a, const Rec& c) { return a.keys > c.keys; });
-        int32_t item = 0, m = 0;
+        int32_t item = 0;
         for (int32_t r = 0; r < n_rec; ++r) {
-            if (recs[r].k > 1) p.arg_multi.e[m++] = (uint32_t)recs[r].seq | ((uint32_t)item << 16);
             for (int32_t i = 0; i < recs[r].k; ++i)
                 p.arg_items.e[item++] = (uint32_t)recs[r].seq | ((uint32_t)i << 16) | ((uint32_t)recs[r].k << 24);
         }
@@ -258,7 +258,7 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D) 
         };
         int best = 1;
         double best_cost = cost(1);
-        for (int r = 2; r <= 16; ++r) {
+        for (int r = 2; r <= kMaxMergeRanges; ++r) {
             if (max_steps / r < 32) break;
             const double c = cost(r);
             if (c < best_cost) { best = r; best_cost = c; }
@@ -585,19 +585,35 @@ static FusePlan plan_fusion(const cs_batch* b, const DecodePlan& d, PrefillPlan&
     return f;
 }
 
+// Where the partials of cut decode sequences are merged.  In place costs every workgroup three round
+// trips to memory at its end (stores acknowledged, announcement acknowledged, the others' read; about
+// 4 us), a kernel of its own 5 us behind the last: so in place where the workgroups end about
+// together -- all resident at once, or a workgroup per CU that walks its pairs first -- and in a
+// kernel where they run in rounds and each round would pay.
+static bool decode_merges_in_place(const DecodePlan& d, const PrefillPlan& p, const FusePlan& f, int32_t Hkv, int32_t D) {
+    if (!d.in_args || d.num_multi == 0) return false;
+    const int64_t cus = device_cus(), wgs = (int64_t)d.total_items * Hkv;
+    if (f.arrangement == 2) return wgs <= (int64_t)kMaxPairsInPlace * std::min<int64_t>(f.persistent_wgs, wgs);
+    if (f.arrangement == 1) return wgs + (int64_t)p.num_slots * p.max_ranges * Hkv <= 2 * cus;
+    return wgs <= cus * (D == 128 ? (d.pages_ahead == 2 ? 2 : 3) : 4);
+}
+
+uint64_t next_launch_number() {
+    static std::atomic<uint64_t> next{((uint64_t)std::random_device{}() << 24) + 1};    // 56 bits
+    const uint64_t n = next.fetch_add(1, std::memory_order_relaxed) & 0xffffffffffffffull;
+    return n ? n : next_launch_number();
+}
+
 static size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
-DecodeWorkspace decode_workspace(const DecodePlan& p, int32_t S, int32_t Hq, int32_t D) {
+DecodeWorkspace decode_workspace(const DecodePlan& p, int32_t Hq, int32_t Hkv, int32_t D) {
     DecodeWorkspace w = {};
     if (p.num_decode == 0 || p.num_multi == 0) return w;   // nothing is cut: no item list, no partials
     size_t off = 0;
-    w.items = off;    off += align16((size_t)p.total_items * 8 * sizeof(int32_t));
-    w.cu_items = off; off += align16((size_t)(S + 1) * sizeof(int32_t));
-    w.multi = off;    off += align16((size_t)(p.num_multi + 1) * sizeof(int32_t));
+    w.items = off;    off += align16((size_t)p.total_items * (p.in_args ? Hkv * sizeof(uint64_t) : 8 * sizeof(int32_t)));
     // partials are indexed by item; only items of multi-item sequences are ever written
-    const size_t part_items = p.num_multi ? (size_t)p.total_items : 0;
-    w.part_ml = off;  off += align16(part_items * Hq * 2 * sizeof(float));
-    w.part_o = off;   off += align16(part_items * Hq * D * sizeof(float));
+    w.part_ml = off;  off += align16((size_t)p.total_items * Hq * 2 * sizeof(float));
+    w.part_o = off;   off += align16((size_t)p.total_items * Hq * D * sizeof(float));
     w.total = off;
     return w;
 }
@@ -673,7 +689,8 @@ static const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_
     m.plans.d = plan_decode(b, Hkv, D);
     m.plans.p = m.plans.d.num_prefill ? plan_prefill(b, Hq, Hkv, D) : PrefillPlan{};
     m.plans.f = plan_fusion(b, m.plans.d, m.plans.p, Hq, Hkv, D, fuse);
-    m.plans.decode_bytes = decode_workspace(m.plans.d, S, Hq, D).total;
+    m.plans.d.merges_in_place = decode_merges_in_place(m.plans.d, m.plans.p, m.plans.f, Hkv, D);
+    m.plans.decode_bytes = decode_workspace(m.plans.d, Hq, Hkv, D).total;
     m.plans.need = m.plans.decode_bytes + m.plans.p.bytes;
     m.valid = true;
     return m.plans;
@@ -726,13 +743,11 @@ static int attention_mixed(const cs_kv_pool* pool, int32_t layer, const cs_batch
     if (workspace_bytes < need) return CS_ERR_WORKSPACE_TOO_SMALL;
     hipStream_t st = (hipStream_t)stream;
     if (plans.f.arrangement != 0) {
-        // both kinds of work in one grid, then the merges of whatever was cut
-        void* prefill_ws = (char*)workspace + decode_bytes;
-        rc = launch_mixed(*pool, layer, *batch, plan, pplan, q, out, Hq, softmax_scale, workspace, prefill_ws, st, f16,
-                          plans.f.prio, plans.f.arrangement == 2 ? plans.f.persistent_wgs : 0);
-        if (rc) return rc;
-        rc = launch_prefill_merge(*pool, *batch, pplan, out, Hq, prefill_ws, st, f16);
-        if (rc) return rc;
+        // both kinds of work in one grid, then the merge of cut sequences where the grid does not do it
+        rc = launch_mixed(*pool, layer, *batch, plan, pplan, q, out, Hq, softmax_scale, workspace,
+                          (char*)workspace + decode_bytes, st, f16, plans.f.prio,
+                          plans.f.arrangement == 2 ? plans.f.persistent_wgs : 0);
+        if (rc || plan.num_multi == 0 || plan.merges_in_place) return rc;
         return launch_decode(*pool, layer, *batch, plan, q, out, Hq, softmax_scale, workspace, st, f16, true);
     }
     if (plan.num_prefill > 0) {
@@ -1010,7 +1025,7 @@ double cs_debug_play_tiles(const float* work_us, int32_t n, int32_t cus, double 
 
 void cs_debug_set_tail_cut(int32_t whole_tiles, int32_t ranges) {
     g_forced_tail_whole.store(whole_tiles >= 0 && ranges >= 1 ? whole_tiles : whole_tiles == -2 ? -2 : -1);   // (-2: no cut by the model either)
-    g_forced_tail_ranges.store(whole_tiles >= 0 && ranges >= 1 ? ranges : 0);
+    g_forced_tail_ranges.store(whole_tiles >= 0 && ranges >= 1 ? std::min(ranges, kMaxMergeRanges) : 0);
 }
 
 void cs_set_mixed_fusion(int32_t mode) {

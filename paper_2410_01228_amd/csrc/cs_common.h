@@ -48,6 +48,7 @@ constexpr int kPrefillThreads = kPrefillWaves * 64;
 constexpr int kNCT = 2;                       // column tiles (16 query rows) per wavefront
 constexpr int kKeysPerStep = 32;              // keys a workgroup walks per step: two pages of 16
 constexpr int kTileCols = kPrefillWaves * kNCT;   // column tiles per workgroup
+constexpr int kMaxMergeRanges = 16;           // key ranges a tile is cut into at most
 
 // Workgroup slots.  A sequence with q new tokens has ceil(q/16) * G column tiles, numbered
 // token-block major (ct = token_block * G + head), and needs ceil(that / kTileCols)
@@ -61,10 +62,10 @@ __host__ __device__ inline int64_t prefill_slot_start(int32_t cu_q, int32_t s, i
 // Small batches carry their work-item list inside the kernel arguments: the host already has
 // the lengths, so it lists the items itself, longest first, and no planning kernel and no
 // host-to-device copy is needed.  One word per item: sequence (bits 0-15), piece (16-23),
-// pieces of that sequence (24-31).  One word per cut sequence for the merge: sequence (bits
-// 0-15), its first item (16-31).  The list must fit the 4 KiB argument block of a launch.
+// pieces of that sequence (24-31).  The list must fit the 4 KiB argument block of a launch.
 constexpr int kMaxArgItems = 880;
 struct ItemsInArgs { uint32_t e[kMaxArgItems]; };
+constexpr int kMaxPairsInPlace = 64;         // (item, kv head) pairs a workgroup can walk and still merge in place
 
 // Plan of the decode path, a pure function of the host lengths (used by both the
 // workspace query and the launch).
@@ -77,16 +78,19 @@ struct DecodePlan {
     int64_t decode_keys;       // total keys read by decode sequences
     int32_t pages_ahead;       // pages a wavefront of the decode kernel prefetches (1 or 2)
     bool    in_args;           // the item list below is valid and replaces the planning kernel
+    bool    merges_in_place;   // the workgroups merge the cut sequences themselves, no kernel follows
     ItemsInArgs arg_items;     // total_items words
-    ItemsInArgs arg_multi;     // num_multi words
 };
 DecodePlan plan_decode(const cs_batch* batch, int32_t num_kv_heads, int32_t head_dim);
-// Workspace layout (all 16-byte aligned): work items | per-sequence item offsets |
-// multi-item sequence list | partial (max, sum) | partial outputs.
+// Workspace layout (all 16-byte aligned): announcements of the partials (item list in the kernel
+// arguments: 8 bytes per item and kv head, cs_arrive.h) or the item list | partial (max, sum) |
+// partial outputs.  All zero when nothing is cut.
 struct DecodeWorkspace {
-    size_t items, cu_items, multi, part_ml, part_o, total;
+    size_t items, part_ml, part_o, total;
 };
-DecodeWorkspace decode_workspace(const DecodePlan& p, int32_t num_seqs, int32_t num_q_heads, int32_t head_dim);
+DecodeWorkspace decode_workspace(const DecodePlan& p, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim);
+// A number no other launch of this process gets (cs_arrive.h).
+uint64_t next_launch_number();
 
 // Kernel launchers (defined next to their kernels).
 int launch_append(const cs_kv_pool& pool, int32_t layer, const cs_batch& b,
@@ -121,18 +125,15 @@ struct PrefillPlan {
 PrefillPlan plan_prefill(const cs_batch* batch, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim);
 int launch_prefill(const cs_kv_pool& pool, int32_t layer, const cs_batch& b, const PrefillPlan& plan,
                    const void* q, void* out, int32_t Hq, float scale, void* workspace, hipStream_t st, bool f16);
-// The merge of the key-range partials alone (what launch_prefill ends with when tiles are cut).
-int launch_prefill_merge(const cs_kv_pool& pool, const cs_batch& b, const PrefillPlan& plan, void* out, int32_t Hq,
-                         void* workspace, hipStream_t st, bool f16);
 // One launch for a batch that holds both chunks and decode tokens.  persistent_wgs == 0: the
 // prefill workgroups first, one workgroup per decode (item, kv head) pair behind them, so that
 // decode work fills the slots the uneven prefill tiles leave empty instead of waiting for the
 // last of them.  persistent_wgs > 0: that many decode workgroups first (the host passes the CU
 // count: one per CU), each walking several pairs, the tiles beside them.  Needs the item list
 // in the kernel arguments (dplan.in_args).  Tiles cut into key ranges bring one workgroup per
-// range; the caller merges their partials (launch_prefill_merge) and the cut decode sequences
-// (launch_decode with merge_only) afterwards.  tile_priority: 0, or the higher of the two issue
-// priorities the tile wavefronts alternate between (1 or 2; decode wavefronts stay at 0).
+// range; tiles and cut decode sequences are merged by whichever of their workgroups finishes last.
+// tile_priority: 0, or the higher of the two issue priorities the tile wavefronts alternate between
+// (1 or 2; decode wavefronts stay at 0).
 int launch_mixed(const cs_kv_pool& pool, int32_t layer, const cs_batch& b, const DecodePlan& dplan,
                  const PrefillPlan& pplan, const void* q, void* out, int32_t Hq, float scale,
                  void* decode_workspace_base, void* prefill_workspace, hipStream_t st, bool f16,

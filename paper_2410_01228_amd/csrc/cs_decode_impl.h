@@ -4,7 +4,8 @@
 // four wavefronts stream the split's pages straight from HBM into MFMA operand registers
 // (the page format IS the operand layout, so there is no LDS staging and no shuffle),
 // keep an online softmax per query head in fp32, and leave one partial (max, sum,
-// unnormalised output) per split; a second kernel merges the splits.
+// unnormalised output) per split; the splits are merged by whichever of their workgroups
+// finishes last, or by a second kernel (see DecodePartials).
 //
 // Tile algebra per 16-token page and kv head (G = query heads sharing it, padded to 16):
 //   S^T[token][head] = K[token][:] . Q[head][:]      v_mfma_f32_16x16x32_{bf16,f16}, D/32 steps
@@ -12,8 +13,10 @@
 // The C layout of S^T (lane = head + 16*(token/4), register = token%4) is exactly the B
 // layout the second product wants, so P never leaves its registers.
 #pragma once
+#include "cs_arrive.h"
 #include "cs_common.h"
 #include "cs_elem.h"
+
 
 namespace cs {
 
@@ -180,7 +183,7 @@ __device__ __forceinline__ void process_page(WaveState<D>& st, const PageRegs<D>
 // and kv head: no workgroup starts only to find it has nothing to do, and a long sequence
 // and a short one both break into pieces of about the same size.
 struct DecodeItem {
-    int32_t seq, token, n_keys, key_begin, key_end, n_splits, pad0, pad1;   // 32 bytes
+    int32_t seq, token, n_keys, key_begin, key_end, n_splits, first_item, pad;   // 32 bytes
 };
 
 // Where a workgroup's item comes from.
@@ -199,6 +202,7 @@ __device__ inline bool fetch_item(const ItemsIdentity&, int32_t item, const int3
     it.key_begin = 0;
     it.key_end = it.n_keys;
     it.n_splits = 1;
+    it.first_item = item;
     return true;
 }
 __device__ inline bool fetch_item(const ItemsInArgs& src, int32_t item, const int32_t* ctx_lens, const int32_t* cu_q_lens, DecodeItem& it) {
@@ -211,6 +215,7 @@ __device__ inline bool fetch_item(const ItemsInArgs& src, int32_t item, const in
     it.key_begin = k > 1 ? min(it.n_keys, piece * chunk) : 0;
     it.key_end = k > 1 ? min(it.n_keys, (piece + 1) * chunk) : it.n_keys;
     it.n_splits = k;
+    it.first_item = item - piece;
     return true;
 }
 
@@ -220,7 +225,64 @@ struct DecodeLds {
     float o[kDecodeWaves][kMaxGroup][D];
     float m[kDecodeWaves][kMaxGroup];
     float l[kDecodeWaves][kMaxGroup];
+    int32_t last[kMaxPairsInPlace];                   // which of its pairs' sequences this workgroup merges
 };
+
+// Where the items of cut sequences leave their partials: floats [item][Hq][D] and [item][Hq][2]
+// (max, sum).  words: the announcements of the workgroups, [item][Hkv] (cs_arrive.h), where the host
+// has the workgroups merge them (DecodePlan::merges_in_place); else null, and decode_merge_kernel
+// follows.
+struct DecodePartials {
+    float* o;
+    float* ml;
+    uint64_t* words;
+    uint64_t launch;
+};
+
+// Merge of the n_splits partials of one (cut sequence, kv head), by one workgroup: a lane per (head,
+// 4 features), up to 8 pieces' loads in flight at once.  o0, ml0: the partials of the first item's
+// first head of the group; piece i lies i * Hq rows further on.
+template <int D, class E>
+__device__ __forceinline__ void merge_pieces(const DecodePartials& part, int32_t first_item, int32_t n_splits, int32_t Hq,
+                                             int32_t g, int32_t G, uint16_t* __restrict__ out_row)
+{
+    constexpr int kQuads = D / 4;
+    const int64_t row0 = (int64_t)first_item * Hq + g * G;
+    const Shared po(part.o + row0 * D, (uint32_t)n_splits * Hq * D * 4);
+    const Shared pm(part.ml + row0 * 2, (uint32_t)n_splits * Hq * 8);
+    for (int idx = threadIdx.x; idx < G * kQuads; idx += kDecodeThreads) {
+        const int head = idx / kQuads, quad = idx - head * kQuads;
+        float M = -INFINITY, L = 0.f;
+        f32x4 O = {0.f, 0.f, 0.f, 0.f};
+        for (int32_t i0 = 0; i0 < n_splits; i0 += 8) {
+            a_u32x2 ml[8];
+            a_u32x4 o[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {                                  // (past the last piece: the last again)
+                const uint32_t row = (uint32_t)min(i0 + j, n_splits - 1) * Hq + head;
+                ml[j] = pm.load2(row * 8);
+                o[j] = po.load4(row * (D * 4) + quad * 16);
+            }
+            float M_new = M;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) M_new = fmaxf(M_new, as_float(ml[j][0]));
+            const float keep = M == -INFINITY ? 0.f : exp2f(M - M_new);
+            L *= keep;
+            O *= keep;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float m = as_float(ml[j][0]);
+                const float f = m == -INFINITY || i0 + j >= n_splits ? 0.f : exp2f(m - M_new);    // a piece without keys
+                L += as_float(ml[j][1]) * f;
+                O += __builtin_bit_cast(f32x4, o[j]) * f;
+            }
+            M = M_new;
+        }
+        u32x2 w = {0u, 0u};
+        if (L > 0.f) w = u32x2{ E::pack(O[0] / L, O[1] / L), E::pack(O[2] / L, O[3] / L) };
+        *(u32x2*)(out_row + (g * G + head) * D + quad * 4) = w;
+    }
+}
 
 // The work of one decode workgroup: item `item` (a sequence's key range), kv head g; 4
 // wavefronts.  Src says where the item list is: in memory, in the kernel arguments, or
@@ -246,7 +308,7 @@ __device__ __forceinline__ void decode_item(
     const Src& src,
     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens,
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out,
-    float scale_log2e, float* __restrict__ part_o, float* __restrict__ part_ml,
+    float scale_log2e, const DecodePartials& part,
     int32_t item, int32_t g)
 {
     DecodeItem it;
@@ -376,9 +438,54 @@ __device__ __forceinline__ void decode_item(
             out[((int64_t)t * Hq + hq) * D + d] = (uint16_t)(E::pack(r, 0.f) & 0xffffu);
         } else {
             const int64_t slot = (int64_t)item * Hq + hq;
-            part_o[slot * D + d] = O;
-            if (d == 0) { part_ml[slot * 2] = M; part_ml[slot * 2 + 1] = L; }
+            __hip_atomic_store(part.o + slot * D + d, O, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (d == 0) {
+                __hip_atomic_store(part.ml + slot * 2, M, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(part.ml + slot * 2 + 1, L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
+    }
+}
+
+// The end of a workgroup that has worked off pairs pair_at(0) .. pair_at(n_pairs - 1) (item * Hkv + kv
+// head; -1: none): announces the partials it left, and merges the sequences it finds complete.  All
+// announcements go out together and behind the last pair, so a workgroup that walks several pairs
+// does not stop between them.
+template <int D, class E, class Src, class PairAt>
+__device__ __forceinline__ void merge_in_place(
+    DecodeLds<D>& lds, const DecodePartials& part, const Src& src, PairAt pair_at, int32_t n_pairs,
+    const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens, int32_t Hkv, int32_t G, uint16_t* __restrict__ out)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t Hq = Hkv * G;
+    auto piece_of = [&](int32_t k, DecodeItem& it, int32_t& item, int32_t& g) {      // is pair k a piece of a cut sequence?
+        const int32_t pair = pair_at(k);
+        if (pair < 0) return false;
+        item = pair / Hkv;
+        g = pair - item * Hkv;
+        return fetch_item(src, item, ctx_lens, cu_q_lens, it) && it.n_splits > 1;
+    };
+    auto words_of = [&](const DecodeItem& it, int32_t g) {
+        return Announcements(Shared(part.words + (int64_t)it.first_item * Hkv + g, (uint32_t)it.n_splits * Hkv * 8), 0,
+                             Hkv * 8, it.n_splits, part.launch);
+    };
+    DecodeItem it;
+    int32_t item, g;
+    wait_stores();
+    __syncthreads();
+    for (int32_t k = wave; k < n_pairs; k += kDecodeWaves)
+        if (piece_of(k, it, item, g)) words_of(it, g).announce(item - it.first_item);
+    wait_stores();
+    for (int32_t k = wave; k < n_pairs; k += kDecodeWaves) {
+        const bool last = piece_of(k, it, item, g) && words_of(it, g).all();
+        if ((threadIdx.x & 63) == 0) lds.last[k] = last;
+    }
+    __syncthreads();
+    for (int32_t k = 0; k < n_pairs; ++k) {
+        if (!lds.last[k]) continue;
+        piece_of(k, it, item, g);
+        merge_pieces<D, E>(part, it.first_item, it.n_splits, Hq, g, G, out + (int64_t)it.token * Hq * D);
+        if (wave == 0) words_of(it, g).clear();
     }
 }
 

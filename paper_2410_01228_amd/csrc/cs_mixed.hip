@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kPrefillThreads, 2) void mixed_kernel(
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float scale_log2e,
     int32_t range_steps, int32_t base_slot, int32_t num_slots, int32_t cut_first_pos, int32_t max_ranges,
     float* __restrict__ prefill_part, uint32_t dec_first, uint32_t dec_wgs, uint32_t n_decode, int32_t backwards,
-    const ItemsInArgs items, float* __restrict__ part_o, float* __restrict__ part_ml)
+    const ItemsInArgs items, const DecodePartials part)
 {
     __shared__ MixedLds<D> lds;
     if (blockIdx.x < dec_first || blockIdx.x >= dec_first + dec_wgs) {
@@ -64,21 +64,27 @@ __global__ __launch_bounds__(kPrefillThreads, 2) void mixed_kernel(
             part_tile = partials_of<D>(prefill_part, pos - cut_first_pos, Hkv, g, max_ranges);
         }
         const int32_t b = base_slot + (backwards ? num_slots - 1 - pos : pos);   // backwards: longest tiles first
-        prefill_tile<D, E, kPriority, PS, true>(lds.prefill, layer_base, page_stride, num_pages, Hkv, G, S, block_tables, max_blocks,
-                           ctx_lens, cu_q_lens, q, out, scale_log2e, steps_per_range, part_tile, g, b, range);
+        prefill_tile<D, E, kPriority, PS, true, true>(lds.prefill, layer_base, page_stride, num_pages, Hkv, G, S, block_tables, max_blocks,
+                           ctx_lens, cu_q_lens, q, out, scale_log2e, steps_per_range, part_tile, part.launch, g, b, range);
     } else {
         const uint32_t j = blockIdx.x - dec_first;
-        for (uint32_t base = 0, round = 0; base < n_decode; base += dec_wgs, ++round) {
-            const uint32_t w = base + ((round & 1) ? dec_wgs - 1 - j : j);
-            if (w >= n_decode) continue;
+        auto pair_at = [&](int32_t round) -> int32_t {
+            const uint32_t w = (uint32_t)round * dec_wgs + ((round & 1) ? dec_wgs - 1 - j : j);
+            return w < n_decode ? (int32_t)w : -1;
+        };
+        int32_t round = 0;
+        for (; (uint32_t)round * dec_wgs < n_decode; ++round) {
+            const int32_t w = pair_at(round);
+            if (w < 0) continue;
             const int32_t item = w / Hkv, g = w - item * Hkv;
             // one page ahead, with loads the compiler can count (a workgroup that shares its CU
             // with a tile must stream by itself); a deeper queue only delays the tile's own
             // copies, which share the CU's memory pipeline
             decode_item<D, ItemsInArgs, E, 1, PS, true>(lds.decode, layer_base, page_stride, num_pages, Hkv, G, block_tables, max_blocks,
-                                           items, ctx_lens, cu_q_lens, q, out, scale_log2e, part_o, part_ml, item, g);
+                                           items, ctx_lens, cu_q_lens, q, out, scale_log2e, part, item, g);
             __syncthreads();     // the next pair reuses the merge buffers
         }
+        if (part.words) merge_in_place<D, E>(lds.decode, part, items, pair_at, round, ctx_lens, cu_q_lens, Hkv, G, out);
     }
 }
 
@@ -96,9 +102,9 @@ static int launch_mixed_as(const cs_kv_pool& pool, int32_t layer, const cs_batch
     const int64_t dec_wgs = persistent_wgs > 0 ? std::min<int64_t>(persistent_wgs, n_decode) : n_decode;
     const int64_t dec_first = persistent_wgs > 0 ? 0 : n_prefill;
     if (n_prefill + dec_wgs > 2147483647ll) return CS_ERR_UNSUPPORTED;
-    const DecodeWorkspace w = decode_workspace(dplan, b.num_seqs, Hq, D);
-    float* part_ml = (float*)((char*)decode_ws + w.part_ml);
-    float* part_o = (float*)((char*)decode_ws + w.part_o);
+    const DecodeWorkspace w = decode_workspace(dplan, Hq, Hkv, D);
+    const DecodePartials part = {(float*)((char*)decode_ws + w.part_o), (float*)((char*)decode_ws + w.part_ml),
+                                 dplan.merges_in_place ? (uint64_t*)decode_ws : nullptr, next_launch_number()};
     dim3 grid((uint32_t)(n_prefill + dec_wgs));
 #define CS_LAUNCH_MIXED_P(DD, PRIO, PS)                                                                      \
     hipLaunchKernelGGL((mixed_kernel<DD, E, PRIO, PS>), grid, dim3(kPrefillThreads), 0, st, layer_base, pool.page_stride, \
@@ -106,7 +112,7 @@ static int launch_mixed_as(const cs_kv_pool& pool, int32_t layer, const cs_batch
                        b.cu_q_lens, (const uint16_t*)q, (uint16_t*)out, scale_log2e, pplan.range_steps,         \
                        pplan.base_slot, pplan.num_slots, pplan.cut_first_pos, pplan.max_ranges,                 \
                        (float*)prefill_ws, (uint32_t)dec_first, (uint32_t)dec_wgs, (uint32_t)n_decode, (int32_t)pplan.backwards,    \
-                       dplan.arg_items, part_o, part_ml);
+                       dplan.arg_items, part);
 #define CS_LAUNCH_MIXED(DD, PRIO)                                                                            \
     if (pool.page_size == 16) { CS_LAUNCH_MIXED_P(DD, PRIO, 16) } else { CS_LAUNCH_MIXED_P(DD, PRIO, 8) }
     if (D == 128) { if (prio == 2) { CS_LAUNCH_MIXED(128, 2) } else if (prio == 1) { CS_LAUNCH_MIXED(128, 1) } else { CS_LAUNCH_MIXED(128, 0) } }

@@ -23,6 +23,7 @@
 // maximum is only raised (and the accumulators rescaled) when a new score exceeds it by
 // more than 2^kLazyLog2, which keeps the rescale out of the steady-state loop.
 #pragma once
+#include "cs_arrive.h"
 #include "cs_common.h"
 #include "cs_elem.h"
 #include <algorithm>
@@ -120,6 +121,7 @@ template <int D>
 struct PrefillLds {
     u32x4 k[kRing][4 * D];                            // 2 pages x 2*D 16-byte units per step
     u32x4 v[kRing][4 * D];
+    int32_t last;                                     // all other ranges of this workgroup's cut tile are done
 };
 
 // The work of one prefill workgroup: the tile in slot b, kv head g, key range `range` (a tile
@@ -131,7 +133,9 @@ struct PrefillLds {
 // grids whose other wavefronts are mostly tiles too, or become so once a decode workgroup per CU
 // is done; 2: the same and always above decode wavefronts, which stay at 0; with decode work of
 // equal weight queued behind the tiles either costs more than it gains).
-template <int D, class E, int kPriority, int PS, bool kLaneAddr16>
+// kMayCut: false where the host cuts no tile of the launch (the code behind the loop would change
+// the loop's register allocation for the worse).
+template <int D, class E, int kPriority, int PS, bool kLaneAddr16, bool kMayCut>
 __device__ __forceinline__ void prefill_tile(
     PrefillLds<D>& lds,
     const uint16_t* __restrict__ layer_base, int64_t page_stride, int32_t num_pages,
@@ -139,7 +143,7 @@ __device__ __forceinline__ void prefill_tile(
     const int32_t* __restrict__ block_tables, int32_t max_blocks,
     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens,
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float scale_log2e,
-    int32_t range_steps, float* __restrict__ part_tile,
+    int32_t range_steps, float* __restrict__ part_tile, uint64_t launch,
     int32_t g, int32_t b, int32_t range)
 {
     constexpr int kUnits = D * 2;                     // 16-byte units per K (or V) block of a page
@@ -557,34 +561,102 @@ __device__ __forceinline__ void prefill_tile(
     if (kPriority) __builtin_amdgcn_s_setprio(0);
     wait_vmcnt<0>();                                   // no copy may outlive the workgroup's LDS
 
-    // ---- store: lane holds 4 consecutive features of one query row per tile ----
-    if (n_ranges == 1) {
+    // ---- a cut tile: the last of its ranges to get here adds the others' partials (unnormalised
+    // output, running max and sum per query row) to its registers; one that finds another range
+    // missing leaves its own.  The announcements lie in the padding of each range's first row. ----
+    if constexpr (kMayCut) {
+        if (n_ranges > 1) {
+            if (part_tile == nullptr) return;             // (a cut tile always has a block: a planning error must not write)
+            constexpr uint32_t kRangeBytes = kTileCols * 16 * kPartRow * 4;
+            const Shared part(part_tile, (uint32_t)n_ranges * kRangeBytes);
+            const Announcements words(part, (D + 2) * 4, kRangeBytes, n_ranges, launch);
+            if (wave == 0) {
+                const bool last = words.all_but(range);
+                if (lane == 0) lds.last = last;
+            }
+            __syncthreads();
+            if (!lds.last) {
+                float* wg = part_tile + (int64_t)range * (kTileCols * 16 * kPartRow);
 #pragma unroll
-        for (int c = 0; c < kNCT; ++c) {
-            const int32_t ct = ct0 + wave * kNCT + c;
-            const int32_t tb = ct / G, hh = ct - tb * G;
-            const int32_t tl = tb * 16 + (lane & 15);
-            if (ct < n_ct && tl < q_len) {
-                const float inv = 1.f / lacc[c][0];
-                uint16_t* dst = out + ((int64_t)(t_seq + tl) * Hq + g * G + hh) * D + (lane >> 4) * 4;
+                for (int c = 0; c < kNCT; ++c) {
+                    float* row = wg + ((wave * kNCT + c) * 16 + (lane & 15)) * kPartRow;
 #pragma unroll
-                for (int dt = 0; dt < D / 16; ++dt) {
-                    u32x2 w = { E::pack(o[c][dt][0] * inv, o[c][dt][1] * inv),
-                                E::pack(o[c][dt][2] * inv, o[c][dt][3] * inv) };
-                    *(u32x2*)(dst + dt * 16) = w;
+                    for (int dt = 0; dt < D / 16; ++dt) store_shared4(row + dt * 16 + (lane >> 4) * 4, o[c][dt]);
+                    if (lane < 16) store_shared2(row + D, a_f32x2{m_run[c], lacc[c][0]});
+                }
+                wait_stores();
+                __syncthreads();
+                if (wave == 0) {
+                    words.announce(range);
+                    wait_stores();
+                    const bool last = words.all();
+                    if (lane == 0) lds.last = last;
+                }
+                __syncthreads();
+                if (!lds.last) return;
+            }
+            // in the order of the ranges, whichever of them this is
+            f32x4 sum[kNCT][D / 16];
+            float M[kNCT], L[kNCT];
+#pragma unroll
+            for (int c = 0; c < kNCT; ++c) {
+                M[c] = kNoMax;
+                L[c] = 0.f;
+#pragma unroll
+                for (int dt = 0; dt < D / 16; ++dt) sum[c][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            auto add = [&](int c, float m, float l, const f32x4 (&v)[D / 16]) {
+                const float M_new = fmaxf(M[c], m);
+                const float keep = __builtin_amdgcn_exp2f(M[c] - M_new), f = __builtin_amdgcn_exp2f(m - M_new);
+                M[c] = M_new;
+                L[c] = L[c] * keep + l * f;
+#pragma unroll
+                for (int dt = 0; dt < D / 16; ++dt) sum[c][dt] = sum[c][dt] * keep + v[dt] * f;
+            };
+            for (int r = 0; r < n_ranges; ++r) {
+                if (r == range) {
+#pragma unroll
+                    for (int c = 0; c < kNCT; ++c) add(c, m_run[c], lacc[c][0], o[c]);
+                } else {
+                    a_u32x2 ml[kNCT];
+                    f32x4 v[kNCT][D / 16];
+#pragma unroll
+                    for (int c = 0; c < kNCT; ++c) {
+                        const uint32_t row = (uint32_t)r * kRangeBytes + ((wave * kNCT + c) * 16 + (lane & 15)) * (kPartRow * 4);
+                        ml[c] = part.load2(row + D * 4);
+#pragma unroll
+                        for (int dt = 0; dt < D / 16; ++dt)
+                            v[c][dt] = __builtin_bit_cast(f32x4, part.load4(row + (dt * 16 + (lane >> 4) * 4) * 4));
+                    }
+#pragma unroll
+                    for (int c = 0; c < kNCT; ++c) add(c, as_float(ml[c][0]), as_float(ml[c][1]), v[c]);
                 }
             }
+#pragma unroll
+            for (int c = 0; c < kNCT; ++c) {
+                lacc[c][0] = L[c];
+#pragma unroll
+                for (int dt = 0; dt < D / 16; ++dt) o[c][dt] = sum[c][dt];
+            }
+            if (wave == 0) words.clear();
         }
-    } else {
-        // partial of this key range: unnormalised output, running max and sum per query row
-        if (part_tile == nullptr) return;                 // (a cut tile always has a block: a planning error must not write)
-        float* wg = part_tile + (int64_t)range * (kTileCols * 16 * kPartRow);
+    }
+
+    // ---- store: lane holds 4 consecutive features of one query row per tile ----
 #pragma unroll
-        for (int c = 0; c < kNCT; ++c) {
-            float* row = wg + ((wave * kNCT + c) * 16 + (lane & 15)) * kPartRow;
+    for (int c = 0; c < kNCT; ++c) {
+        const int32_t ct = ct0 + wave * kNCT + c;
+        const int32_t tb = ct / G, hh = ct - tb * G;
+        const int32_t tl = tb * 16 + (lane & 15);
+        if (ct < n_ct && tl < q_len) {
+            const float inv = 1.f / lacc[c][0];
+            uint16_t* dst = out + ((int64_t)(t_seq + tl) * Hq + g * G + hh) * D + (lane >> 4) * 4;
 #pragma unroll
-            for (int dt = 0; dt < D / 16; ++dt) *(f32x4*)(row + dt * 16 + (lane >> 4) * 4) = o[c][dt];
-            if (lane < 16) { row[D] = m_run[c]; row[D + 1] = lacc[c][0]; }
+            for (int dt = 0; dt < D / 16; ++dt) {
+                u32x2 w = { E::pack(o[c][dt][0] * inv, o[c][dt][1] * inv),
+                            E::pack(o[c][dt][2] * inv, o[c][dt][3] * inv) };
+                *(u32x2*)(dst + dt * 16) = w;
+            }
         }
     }
 }
