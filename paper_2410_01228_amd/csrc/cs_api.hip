@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 #include "cs_common.h"
+#include "cs_plan.h"
 #include <atomic>
 #include <functional>
 #include <random>
@@ -86,7 +87,7 @@ int validate_batch(const cs_kv_pool* pool, const cs_batch* b) {
     return CS_OK;
 }
 
-DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim) {
+DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim, int32_t layers) {
     DecodePlan p = {};
     int32_t max_keys = 0, min_keys = 2147483647;
     for (int32_t s = 0; s < b->num_seqs; ++s) {
@@ -121,14 +122,14 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim) {
         // (the workgroup counts and byte volumes below were measured on 256 CUs and scale with the chip)
         const int32_t cap = head_dim >= 128 ? 4096 : 8192;
         const bool uniform = (int64_t)max_keys * 4 <= (int64_t)min_keys * 5;
-        const int64_t kv_bytes = p.decode_keys * 2 * Hkv * head_dim * 2;
+        const int64_t kv_bytes = p.decode_keys * 2 * Hkv * head_dim * 2 * layers;
         const int64_t need = uniform ? cus : kv_bytes >= 400000000ll * cus / 256 ? 3 * cus : cus * 3 / 2;
         auto workgroups_at = [&](int32_t sp) {
             int64_t items = 0;
             for (int32_t s = 0; s < b->num_seqs; ++s)
                 if (b->h_cu_q_lens[s + 1] - b->h_cu_q_lens[s] == 1)
                     items += decode_num_splits(b->h_ctx_lens[s] + 1, sp);
-            return items * Hkv;
+            return items * Hkv * layers;
         };
         // no sequence is cut into more than about 16 pieces: beyond that the partials, their merge
         // and the start-up of ever shorter items cost more than the fuller grid gains -- unless
@@ -153,12 +154,12 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim) {
     // steady state to dominate (from about 0.65 GB of K/V on, ~100 us), and loses 2-7% on
     // smaller launches, where start-up and tail decide and every workgroup slot counts.
     {
-        const int64_t kv_bytes = p.decode_keys * 2 * Hkv * head_dim * 2;
+        const int64_t kv_bytes = p.decode_keys * 2 * Hkv * head_dim * 2 * layers;
         p.pages_ahead = kv_bytes >= 650000000ll * cus / 256 ? 2 : 1;
         // equal items run in rounds over the workgroup slots: between 513 and 768 of them are one
         // round of three per CU, but a round and a quarter of two per CU
         const bool uniform = (int64_t)max_keys * 4 <= (int64_t)min_keys * 5;
-        const int64_t wgs = (int64_t)p.total_items * Hkv;
+        const int64_t wgs = (int64_t)p.total_items * Hkv * layers;
         if (uniform && wgs > 2 * cus && wgs <= 3 * cus) p.pages_ahead = 1;
         const int32_t forced = g_forced_ahead.load();
         if (forced == 1 || forced == 2) p.pages_ahead = forced;
@@ -188,7 +189,7 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim) {
 }
 
 // Host plan of the key-range split (a pure function of the host lengths).
-PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D) {
+PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers) {
     PrefillPlan p = {};
     const int32_t G = Hq / Hkv;
     int64_t total_steps = 0, tiles = 0;
@@ -220,14 +221,14 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D) 
     p.base_slot = (int32_t)prefill_slot_start(b->h_cu_q_lens[first], first, G);
     // (the slots of the sequences before the first chunk and behind the last one are empty)
     p.num_slots = (int32_t)(prefill_slot_start(b->h_cu_q_lens[last + 1], last + 1, G) - p.base_slot);
-    const int64_t wgs = tiles * Hkv;
+    const int64_t wgs = tiles * Hkv * layers;
 
     // The chip: `cus` compute units, two workgroup slots each.  (The counts in the comments below
     // are those of the 256-CU part the rules were measured on.)
     const int64_t cus = device_cus(), slots = 2 * cus;
     if (wgs <= cus * 3 / 4 && max_steps < 128) {
         // few and short tiles: about four workgroups per CU, ranges of at least 32 steps
-        const int64_t rs = std::max<int64_t>(32, (total_steps * Hkv + 4 * cus - 1) / (4 * cus));
+        const int64_t rs = std::max<int64_t>(32, (total_steps * Hkv * layers + 4 * cus - 1) / (4 * cus));
         if (rs < max_steps) {
             p.range_steps = (int32_t)rs;
             p.max_ranges = (max_steps + p.range_steps - 1) / p.range_steps;
@@ -281,7 +282,7 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D) 
     for (int32_t k = 0; k < n_listed; ++k) slots_fit = slots_fit && tile_list[k].slot < 65536;
     if (p.max_ranges == 1 && wgs > cus) {
         const bool listed = tiles == n_listed && slots_fit;
-        if (listed && wgs <= slots && cus % Hkv == 0) {
+        if (listed && wgs <= slots && cus % Hkv == 0 && layers == 1) {
             std::stable_sort(tile_list, tile_list + n_listed, [](const Tile& a, const Tile& c) { return a.steps > c.steps; });
             const int32_t n_pair = (int32_t)tiles - first_round, n_solo = first_round - n_pair;
             for (int32_t k = 0; k < n_solo; ++k) p.order.slot[n_pair + k] = (uint16_t)tile_list[k].slot;
@@ -300,20 +301,10 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D) 
         }
     }
     if (p.max_ranges > 1) {
-        p.bytes = (size_t)p.num_slots * Hkv * p.max_ranges * kTileCols * 16 * (D + 4) * sizeof(float);
+        p.bytes = (size_t)layers * p.num_slots * Hkv * p.max_ranges * kTileCols * 16 * (D + 4) * sizeof(float);
     }
     return p;
 }
-
-// How a batch with both kinds of work is launched (see cs_mixed.hip): as two kernels in a row, as
-// one grid with the decode pairs behind the tiles, or as one grid with a decode workgroup per CU
-// beside the tiles.  mode: cs_set_mixed_fusion's (0 never fuse, 1 choose, 2 always behind, 3
-// always beside).
-struct FusePlan {
-    int32_t arrangement;       // 0 two kernels, 1 decode behind the tiles, 2 decode beside the tiles
-    int32_t prio;              // 0, or the higher of the two issue priorities the tiles alternate between (1, 2)
-    int32_t persistent_wgs;    // arrangement 2: decode workgroups (one per CU)
-};
 
 // The tile workgroups of a fused grid played through the chip's workgroup slots (two per CU), in
 // microseconds.  work[i]: what workgroup i takes while another tile shares its CU; it runs
@@ -417,7 +408,7 @@ static double play_tiles(const std::vector<float>& work, int32_t cus, double dec
 // promises 6% of the whole call after the cost of the partials (it overrates what cutting gains
 // beside a decode load, so the bar is not lower).
 static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, PrefillPlan& p, int32_t Hq, int32_t Hkv,
-                                     int32_t D, int32_t mode) {
+                                     int32_t D, int32_t mode, int32_t layers) {
     FusePlan f = {0, 0, 0};
     if (d.num_prefill == 0 || d.num_decode == 0 || !d.in_args || mode == 0) return f;
     const int32_t G = Hq / Hkv;
@@ -443,9 +434,9 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
     if (mode == 2 || (mode == 1 && D != 128)) return f;
     bool beside = mode == 3;
     double t_beside = 0;                                               // the model's time of that arrangement as planned (0: not played)
-    const int64_t tile_units = (int64_t)p.num_slots * p.max_ranges;       // tiles x ranges: what the model plays
+    const int64_t tile_units = (int64_t)p.num_slots * p.max_ranges * layers;       // tiles x ranges: what the model plays
     const int32_t groups = std::max(1, cus / Hkv);                         // CU groups of one CU per kv head
-    const double us_per_step = 0.88, t_dec = decode_bytes / 6.5e6;      // microseconds
+    const double us_per_step = 0.88, t_dec = layers * decode_bytes / 6.5e6;      // microseconds
     // (a decode side under 0.3 of the prefill side stays behind tiles that alternate their
     // priority: measured 5-8% better than beside on such mixes, which the model calls even)
     if ((mode == 1 && !f.prio) || mode == 3) {
@@ -476,6 +467,7 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
             auto list_work = [&](int32_t whole, int32_t range_steps, int32_t ranges) {
                 work.clear();
                 pos_of.clear();
+                for (int32_t l = 0; l < layers; ++l) {
                 for (int32_t pos = 0; pos < whole; ++pos)
                     if (steps_at(pos) > 0) {
                         work.push_back((float)((steps_at(pos) + 8) * us_per_step));
@@ -489,6 +481,7 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
                             pos_of.push_back(pos);
                         }
                     }
+                }
             };
             list_work(0, p.range_steps, p.max_ranges);
             std::vector<double> free_at;
@@ -513,7 +506,7 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
             }
             if (beside && mode != 1 && !work.empty()) t_whole = std::max(play_tiles(work, groups, t_dec, free_at, &started), t_dec);
             t_beside = t_whole;
-            if (beside && p.max_ranges == 1 && !work.empty() && g_forced_tail_whole.load() != -2) {
+            if (beside && p.max_ranges == 1 && !work.empty() && layers == 1 && g_forced_tail_whole.load() != -2) {
                 // the tiles of the last round, cut: from the first tile that starts when the
                 // decode side is at least 0.85 done
                 size_t first = 0;
@@ -565,12 +558,12 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
 }
 
 static FusePlan plan_fusion(const cs_batch* b, const DecodePlan& d, PrefillPlan& p, int32_t Hq, int32_t Hkv,
-                            int32_t D, int32_t mode) {
-    const FusePlan f = plan_fusion_by_model(b, d, p, Hq, Hkv, D, mode);
+                            int32_t D, int32_t mode, int32_t layers) {
+    const FusePlan f = plan_fusion_by_model(b, d, p, Hq, Hkv, D, mode, layers);
     const int32_t forced_whole = g_forced_tail_whole.load(), forced_ranges = g_forced_tail_ranges.load();
     if (forced_whole >= 0 && forced_ranges >= 1 && f.arrangement != 0) {
         // measurement and test knob: cut the launch positions from forced_whole on into forced_ranges
-        p = plan_prefill(b, Hq, Hkv, D);
+        p = plan_prefill(b, Hq, Hkv, D, layers);
         p.n_ordered = 0;
         p.cut_first_pos = std::min(forced_whole, p.num_slots);
         int32_t tail_steps = 1;
@@ -580,7 +573,7 @@ static FusePlan plan_fusion(const cs_batch* b, const DecodePlan& d, PrefillPlan&
         }
         p.range_steps = (tail_steps + forced_ranges - 1) / forced_ranges;
         p.max_ranges = p.cut_first_pos < p.num_slots ? (tail_steps + p.range_steps - 1) / p.range_steps : 1;
-        p.bytes = p.max_ranges > 1 ? (size_t)(p.num_slots - p.cut_first_pos) * Hkv * p.max_ranges * kTileCols * 16 * (D + 4) * sizeof(float) : 0;
+        p.bytes = p.max_ranges > 1 ? (size_t)layers * (p.num_slots - p.cut_first_pos) * Hkv * p.max_ranges * kTileCols * 16 * (D + 4) * sizeof(float) : 0;
     }
     return f;
 }
@@ -590,11 +583,11 @@ static FusePlan plan_fusion(const cs_batch* b, const DecodePlan& d, PrefillPlan&
 // 4 us), a kernel of its own 5 us behind the last: so in place where the workgroups end about
 // together -- all resident at once, or a workgroup per CU that walks its pairs first -- and in a
 // kernel where they run in rounds and each round would pay.
-static bool decode_merges_in_place(const DecodePlan& d, const PrefillPlan& p, const FusePlan& f, int32_t Hkv, int32_t D) {
+static bool decode_merges_in_place(const DecodePlan& d, const PrefillPlan& p, const FusePlan& f, int32_t Hkv, int32_t D, int32_t layers) {
     if (!d.in_args || d.num_multi == 0) return false;
-    const int64_t cus = device_cus(), wgs = (int64_t)d.total_items * Hkv;
+    const int64_t cus = device_cus(), wgs = (int64_t)d.total_items * Hkv * layers;
     if (f.arrangement == 2) return wgs <= (int64_t)kMaxPairsInPlace * std::min<int64_t>(f.persistent_wgs, wgs);
-    if (f.arrangement == 1) return wgs + (int64_t)p.num_slots * p.max_ranges * Hkv <= 2 * cus;
+    if (f.arrangement == 1) return wgs + (int64_t)p.num_slots * p.max_ranges * Hkv * layers <= 2 * cus;
     return wgs <= cus * (D == 128 ? (d.pages_ahead == 2 ? 2 : 3) : 4);
 }
 
@@ -606,14 +599,15 @@ uint64_t next_launch_number() {
 
 static size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
 
-DecodeWorkspace decode_workspace(const DecodePlan& p, int32_t Hq, int32_t Hkv, int32_t D) {
+DecodeWorkspace decode_workspace(const DecodePlan& p, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers) {
     DecodeWorkspace w = {};
     if (p.num_decode == 0 || p.num_multi == 0) return w;   // nothing is cut: no item list, no partials
     size_t off = 0;
-    w.items = off;    off += align16((size_t)p.total_items * (p.in_args ? Hkv * sizeof(uint64_t) : 8 * sizeof(int32_t)));
+    const size_t n = (size_t)p.total_items * layers;
+    w.items = off;    off += align16(p.in_args ? n * Hkv * sizeof(uint64_t) : (size_t)p.total_items * 8 * sizeof(int32_t));
     // partials are indexed by item; only items of multi-item sequences are ever written
-    w.part_ml = off;  off += align16((size_t)p.total_items * Hq * 2 * sizeof(float));
-    w.part_o = off;   off += align16((size_t)p.total_items * Hq * D * sizeof(float));
+    w.part_ml = off;  off += align16(n * Hq * 2 * sizeof(float));
+    w.part_o = off;   off += align16(n * Hq * D * sizeof(float));
     w.total = off;
     return w;
 }
@@ -646,56 +640,60 @@ int cs_kv_append(const cs_kv_pool* pool, int32_t layer, const cs_batch* batch,
     return launch_append(*pool, layer, *batch, k_new, v_new, (hipStream_t)stream);
 }
 
-static int attention_shape_ok(int32_t Hq, int32_t Hkv, int32_t D) {
+}  // extern "C"
+int cs::attention_shape_ok(int32_t Hq, int32_t Hkv, int32_t D) {
     if (Hq <= 0 || Hkv <= 0) return CS_ERR_INVALID_ARG;
     if (Hq % Hkv != 0) return CS_ERR_INVALID_ARG;
     if (!shape_supported(Hkv, D) || Hq / Hkv > kMaxGroup) return CS_ERR_UNSUPPORTED;
     return CS_OK;
 }
+extern "C" {
 
 // The launch plan of a batch: a pure function of the host lengths, the shape, the chip and the
 // measurement knobs.  The workspace query and the attention call of one layer, and the calls of
 // the next layers, ask for the same plan again and again (an item list of up to 880 entries and a
-// sort each time), so each thread remembers the last two it made, keyed by everything the plan
-// depends on, the lengths compared value by value.
-struct Plans {
-    DecodePlan d;
-    PrefillPlan p;
-    FusePlan f;
-    size_t decode_bytes, need;
-};
+// sort each time), so each thread remembers the last few it made (an iteration of cs_run_layers asks
+// for up to five: the whole batch and its online prefix, each for one layer and for several in one
+// launch, and for the layers left over), keyed by everything the plan depends on, the lengths
+// compared value by value.
 struct PlanMemo {
     bool valid = false;
-    int32_t S = 0, T = 0, Hq = 0, Hkv = 0, D = 0, split = 0, ahead = 0, cus = 0, fuse = 0, tail_whole = -1, tail_ranges = 0;
+    int32_t S = 0, T = 0, Hq = 0, Hkv = 0, D = 0, layers = 0, split = 0, ahead = 0, cus = 0, fuse = 0, tail_whole = -1, tail_ranges = 0;
     std::vector<int32_t> ctx, cu;
     Plans plans;
 };
-static const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D) {
-    static thread_local PlanMemo memo[2];
+}  // extern "C"
+
+namespace cs {
+const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers) {
+    constexpr int kMemos = 6;
+    static thread_local PlanMemo memo[kMemos];
     static thread_local int next = 0;
     const int32_t S = b->num_seqs, split = g_forced_split.load(), ahead = g_forced_ahead.load(), cus = device_cus();
     const int32_t fuse = g_fuse_mixed.load(), tail_whole = g_forced_tail_whole.load(), tail_ranges = g_forced_tail_ranges.load();
     for (PlanMemo& m : memo)
-        if (m.valid && m.fuse == fuse && m.tail_whole == tail_whole && m.tail_ranges == tail_ranges && m.S == S && m.T == b->num_tokens && m.Hq == Hq && m.Hkv == Hkv && m.D == D && m.split == split &&
-            m.ahead == ahead && m.cus == cus && memcmp(m.ctx.data(), b->h_ctx_lens, sizeof(int32_t) * S) == 0 &&
-            memcmp(m.cu.data(), b->h_cu_q_lens, sizeof(int32_t) * (S + 1)) == 0)
+        if (m.valid && m.fuse == fuse && m.tail_whole == tail_whole && m.tail_ranges == tail_ranges && m.S == S && m.T == b->num_tokens && m.Hq == Hq && m.Hkv == Hkv && m.D == D &&
+            m.layers == layers && m.split == split && m.ahead == ahead && m.cus == cus &&
+            memcmp(m.ctx.data(), b->h_ctx_lens, sizeof(int32_t) * S) == 0 && memcmp(m.cu.data(), b->h_cu_q_lens, sizeof(int32_t) * (S + 1)) == 0)
             return m.plans;
     PlanMemo& m = memo[next];
-    next ^= 1;
+    next = (next + 1) % kMemos;
     m.valid = false;
-    m.S = S; m.T = b->num_tokens; m.Hq = Hq; m.Hkv = Hkv; m.D = D; m.split = split; m.ahead = ahead; m.cus = cus; m.fuse = fuse; m.tail_whole = tail_whole; m.tail_ranges = tail_ranges;
+    m.S = S; m.T = b->num_tokens; m.Hq = Hq; m.Hkv = Hkv; m.D = D; m.layers = layers; m.split = split; m.ahead = ahead; m.cus = cus; m.fuse = fuse; m.tail_whole = tail_whole; m.tail_ranges = tail_ranges;
     m.ctx.assign(b->h_ctx_lens, b->h_ctx_lens + S);
     m.cu.assign(b->h_cu_q_lens, b->h_cu_q_lens + S + 1);
-    m.plans.d = plan_decode(b, Hkv, D);
-    m.plans.p = m.plans.d.num_prefill ? plan_prefill(b, Hq, Hkv, D) : PrefillPlan{};
-    m.plans.f = plan_fusion(b, m.plans.d, m.plans.p, Hq, Hkv, D, fuse);
-    m.plans.d.merges_in_place = decode_merges_in_place(m.plans.d, m.plans.p, m.plans.f, Hkv, D);
-    m.plans.decode_bytes = decode_workspace(m.plans.d, Hq, Hkv, D).total;
+    m.plans.d = plan_decode(b, Hkv, D, layers);
+    m.plans.p = m.plans.d.num_prefill ? plan_prefill(b, Hq, Hkv, D, layers) : PrefillPlan{};
+    m.plans.f = plan_fusion(b, m.plans.d, m.plans.p, Hq, Hkv, D, fuse, layers);
+    m.plans.d.merges_in_place = decode_merges_in_place(m.plans.d, m.plans.p, m.plans.f, Hkv, D, layers);
+    m.plans.decode_bytes = decode_workspace(m.plans.d, Hq, Hkv, D, layers).total;
     m.plans.need = m.plans.decode_bytes + m.plans.p.bytes;
     m.valid = true;
     return m.plans;
 }
+}  // namespace cs
 
+extern "C" {
 size_t cs_paged_attention_workspace_bytes(const cs_batch* batch, int32_t Hq, int32_t Hkv, int32_t D) {
     if (attention_shape_ok(Hq, Hkv, D) != CS_OK) return 0;
     if (validate_batch(nullptr, batch) != CS_OK || batch->num_seqs == 0) return 0;
@@ -704,12 +702,14 @@ size_t cs_paged_attention_workspace_bytes(const cs_batch* batch, int32_t Hq, int
 
 // The first num_online_seqs sequences of a batch over the same arrays (what is left of an
 // iteration once it is preempted: paper Sec. 4.3).
-static cs_batch online_prefix(const cs_batch& b, int32_t num_online_seqs) {
+}  // extern "C"
+cs_batch cs::online_prefix(const cs_batch& b, int32_t num_online_seqs) {
     cs_batch cur = b;
     cur.num_seqs = num_online_seqs;
     cur.num_tokens = num_online_seqs > 0 ? b.h_cu_q_lens[num_online_seqs] : 0;
     return cur;
 }
+extern "C" {
 
 size_t cs_run_layers_workspace_bytes(const cs_batch* batch, int32_t num_online_seqs, int32_t Hq, int32_t Hkv, int32_t D) {
     if (attention_shape_ok(Hq, Hkv, D) != CS_OK) return 0;
@@ -722,7 +722,8 @@ size_t cs_run_layers_workspace_bytes(const cs_batch* batch, int32_t num_online_s
     return need;
 }
 
-static int attention_mixed(const cs_kv_pool* pool, int32_t layer, const cs_batch* batch,
+}  // extern "C"
+int cs::attention_mixed(const cs_kv_pool* pool, int32_t layer, const cs_batch* batch,
                            const void* q, void* out, int32_t Hq, float softmax_scale,
                            void* workspace, size_t workspace_bytes, void* stream, bool f16) {
     int rc = validate_pool(pool);
@@ -756,6 +757,7 @@ static int attention_mixed(const cs_kv_pool* pool, int32_t layer, const cs_batch
     }
     return launch_decode(*pool, layer, *batch, plan, q, out, Hq, softmax_scale, workspace, st, f16);
 }
+extern "C" {
 
 int cs_paged_attention_mixed(const cs_kv_pool* pool, int32_t layer, const cs_batch* batch,
                              const void* q, void* out, int32_t Hq, float softmax_scale,
@@ -876,81 +878,6 @@ int cs_kv_ckpt_load_run(const cs_kv_pool* pool, int32_t l0, int32_t l1, const in
                                         hipMemcpyHostToDevice, (hipStream_t)stream);
     if (e != hipSuccess) return hip_failed(e, "checkpoint host-to-device copy");
     return launch_page_copy(*pool, l0, l1, ids, n, staging, false, (hipStream_t)stream, true);
-}
-
-static int run_layers(const cs_kv_pool* pool, int32_t l0, int32_t l1, const cs_batch* batch,
-                      const void* q, const void* k_new, const void* v_new, void* out,
-                      int64_t q_stride, int64_t kv_stride, int32_t Hq, float scale,
-                      void* workspace, size_t workspace_bytes, const cs_safepoint* sp,
-                      int32_t* preempted_before_layer, void* stream, bool f16) {
-    if (preempted_before_layer) *preempted_before_layer = -1;
-    int rc = validate_pool(pool);
-    if (rc) return rc;
-    if (l0 < 0 || l1 < l0 || l1 > pool->num_layers || q_stride < 0 || kv_stride < 0) return CS_ERR_INVALID_ARG;
-    rc = validate_batch(pool, batch);
-    if (rc) return rc;
-    if (sp && (sp->check_every <= 0 || sp->num_online_seqs < 0 || sp->num_online_seqs > batch->num_seqs))
-        return CS_ERR_INVALID_ARG;
-    // Everything that can refuse the iteration is checked before its first layer is enqueued.  The
-    // workspace must hold the full batch's plan AND the online prefix's: fewer sequences are cut
-    // finer (more partials), so the prefix can need more than the whole.
-    if (l1 > l0 && batch->num_tokens > 0) {
-        rc = attention_shape_ok(Hq, pool->num_kv_heads, pool->head_dim);
-        if (rc) return rc;
-        if (!q || !out || !k_new || !v_new) return CS_ERR_INVALID_ARG;
-        if (!(scale > 0.f) || scale > 3.0e38f) return CS_ERR_INVALID_ARG;
-        const size_t need = cs_run_layers_workspace_bytes(batch, sp ? sp->num_online_seqs : 0, Hq, pool->num_kv_heads,
-                                                          pool->head_dim);
-        if (need > 0 && (!workspace || ((uintptr_t)workspace & 15))) return CS_ERR_INVALID_ARG;
-        if (workspace_bytes < need) return CS_ERR_WORKSPACE_TOO_SMALL;
-    }
-    cs_batch cur = *batch;
-    bool preempted = false;
-    for (int32_t l = l0; l < l1; ++l) {
-        if (sp && !preempted && (l - l0) % sp->check_every == 0) {
-            // safepoint: between two layers nothing of the iteration is half done
-            if (sp->sync_at_safepoint) {
-                const hipError_t e = hipStreamSynchronize((hipStream_t)stream);
-                if (e != hipSuccess) return hip_failed(e, "safepoint synchronise");
-            }
-            bool raise = sp->flag && *sp->flag != 0;
-            if (!raise && sp->poll) raise = sp->poll(sp->poll_arg) != 0;
-            if (raise) {
-                // drop the offline tail: same arrays, fewer sequences
-                preempted = true;
-                cur = online_prefix(*batch, sp->num_online_seqs);
-                if (preempted_before_layer) *preempted_before_layer = l;
-            }
-        }
-        const int64_t i = l - l0;
-        const uint16_t* ql = (const uint16_t*)q + i * q_stride;
-        const uint16_t* kl = (const uint16_t*)k_new + i * kv_stride;
-        const uint16_t* vl = (const uint16_t*)v_new + i * kv_stride;
-        uint16_t* ol = (uint16_t*)out + i * q_stride;
-        rc = cs_kv_append(pool, l, &cur, kl, vl, stream);
-        if (rc) return rc;
-        rc = attention_mixed(pool, l, &cur, ql, ol, Hq, scale, workspace, workspace_bytes, stream, f16);
-        if (rc) return rc;
-    }
-    return CS_OK;
-}
-
-int cs_run_layers(const cs_kv_pool* pool, int32_t l0, int32_t l1, const cs_batch* batch,
-                  const void* q, const void* k_new, const void* v_new, void* out,
-                  int64_t q_stride, int64_t kv_stride, int32_t Hq, float scale,
-                  void* workspace, size_t workspace_bytes, const cs_safepoint* sp,
-                  int32_t* preempted_before_layer, void* stream) {
-    return run_layers(pool, l0, l1, batch, q, k_new, v_new, out, q_stride, kv_stride, Hq, scale, workspace,
-                      workspace_bytes, sp, preempted_before_layer, stream, false);
-}
-
-int cs_run_layers_f16(const cs_kv_pool* pool, int32_t l0, int32_t l1, const cs_batch* batch,
-                      const void* q, const void* k_new, const void* v_new, void* out,
-                      int64_t q_stride, int64_t kv_stride, int32_t Hq, float scale,
-                      void* workspace, size_t workspace_bytes, const cs_safepoint* sp,
-                      int32_t* preempted_before_layer, void* stream) {
-    return run_layers(pool, l0, l1, batch, q, k_new, v_new, out, q_stride, kv_stride, Hq, scale, workspace,
-                      workspace_bytes, sp, preempted_before_layer, stream, true);
 }
 
 int cs_debug_copy(void* dst, const void* src, size_t bytes, void* stream) {

@@ -81,18 +81,29 @@ struct DecodePlan {
     bool    merges_in_place;   // the workgroups merge the cut sequences themselves, no kernel follows
     ItemsInArgs arg_items;     // total_items words
 };
-DecodePlan plan_decode(const cs_batch* batch, int32_t num_kv_heads, int32_t head_dim);
+// layers: how many layers one launch holds (the grid is that many times as large).
+DecodePlan plan_decode(const cs_batch* batch, int32_t num_kv_heads, int32_t head_dim, int32_t layers = 1);
 // Workspace layout (all 16-byte aligned): announcements of the partials (item list in the kernel
 // arguments: 8 bytes per item and kv head, cs_arrive.h) or the item list | partial (max, sum) |
 // partial outputs.  All zero when nothing is cut.
 struct DecodeWorkspace {
     size_t items, part_ml, part_o, total;
 };
-DecodeWorkspace decode_workspace(const DecodePlan& p, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim);
+DecodeWorkspace decode_workspace(const DecodePlan& p, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim, int32_t layers = 1);
 // A number no other launch of this process gets (cs_arrive.h).
 uint64_t next_launch_number();
 
-// Kernel launchers (defined next to their kernels).
+// The layers of one launch: n of them from the launch's first on; elements from one layer's pool, q
+// and out, k_new and v_new to the next one's.
+struct LayerSpan {
+    int32_t n;
+    int64_t pool, q, kv;
+};
+
+// Kernel launchers (defined next to their kernels).  Those with a LayerSpan do n layers in one
+// launch; their plans are made for that many layers.
+int launch_append_layers(const cs_kv_pool& pool, int32_t layer, const LayerSpan& span, const cs_batch& b,
+                         const void* k_new, const void* v_new, hipStream_t st);
 int launch_append(const cs_kv_pool& pool, int32_t layer, const cs_batch& b,
                   const void* k_new, const void* v_new, hipStream_t st);
 int launch_page_copy(const cs_kv_pool& pool, int32_t layer_begin, int32_t layer_end,
@@ -122,7 +133,7 @@ struct PrefillPlan {
     int32_t num_slots;         // slots from base_slot on: the grid's extent; partials are indexed by slot - base_slot
     size_t  bytes;             // workspace for the partials (0 when nothing is cut)
 };
-PrefillPlan plan_prefill(const cs_batch* batch, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim);
+PrefillPlan plan_prefill(const cs_batch* batch, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim, int32_t layers = 1);
 int launch_prefill(const cs_kv_pool& pool, int32_t layer, const cs_batch& b, const PrefillPlan& plan,
                    const void* q, void* out, int32_t Hq, float scale, void* workspace, hipStream_t st, bool f16);
 // One launch for a batch that holds both chunks and decode tokens.  persistent_wgs == 0: the
@@ -138,5 +149,14 @@ int launch_mixed(const cs_kv_pool& pool, int32_t layer, const cs_batch& b, const
                  const PrefillPlan& pplan, const void* q, void* out, int32_t Hq, float scale,
                  void* decode_workspace_base, void* prefill_workspace, hipStream_t st, bool f16,
                  int32_t tile_priority, int32_t persistent_wgs);
+int launch_decode_layers(const cs_kv_pool& pool, int32_t layer, const LayerSpan& span, const cs_batch& b, const DecodePlan& plan,
+                         const void* q, void* out, int32_t Hq, float scale, void* workspace, hipStream_t st, bool f16,
+                         bool merge_only);
+int launch_prefill_layers(const cs_kv_pool& pool, int32_t layer, const LayerSpan& span, const cs_batch& b, const PrefillPlan& plan,
+                          const void* q, void* out, int32_t Hq, float scale, void* workspace, hipStream_t st, bool f16);
+int launch_mixed_layers(const cs_kv_pool& pool, int32_t layer, const LayerSpan& span, const cs_batch& b, const DecodePlan& dplan,
+                        const PrefillPlan& pplan, const void* q, void* out, int32_t Hq, float scale,
+                        void* decode_workspace_base, void* prefill_workspace, hipStream_t st, bool f16,
+                        int32_t tile_priority, int32_t persistent_wgs);
 
 }  // namespace cs

@@ -327,8 +327,9 @@ __global__ __launch_bounds__(kAppendThreads) void append_page_kernel(
     int32_t Hkv, int32_t D, int32_t S,
     const int32_t* __restrict__ block_tables, int32_t max_blocks,
     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens,
-    const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new)
+    const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, int64_t next_layer, int64_t next_kv)
 {
+    layer_base += blockIdx.y * next_layer; k_new += blockIdx.y * next_kv; v_new += blockIdx.y * next_kv;   // grid.y: layers
     append_page_block<PS>((int32_t)blockIdx.x, layer_base, page_stride, num_pages, Hkv, D, S, block_tables, max_blocks,
                           ctx_lens, cu_q_lens, k_new, v_new);
 }
@@ -338,8 +339,9 @@ __global__ __launch_bounds__(kAppendThreads) void append_token_kernel(
     int32_t Hkv, int32_t D, int32_t S, int32_t T,
     const int32_t* __restrict__ block_tables, int32_t max_blocks,
     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens,
-    const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, int32_t page_size)
+    const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, int32_t page_size, int64_t next_layer, int64_t next_kv)
 {
+    layer_base += blockIdx.y * next_layer; k_new += blockIdx.y * next_kv; v_new += blockIdx.y * next_kv;
     append_token_block((int32_t)blockIdx.x, layer_base, page_stride, num_pages, Hkv, D, S, T, block_tables, max_blocks,
                        ctx_lens, cu_q_lens, k_new, v_new, page_size);
 }
@@ -353,8 +355,9 @@ __global__ __launch_bounds__(kAppendThreads) void append_mixed_kernel(
     int32_t Hkv, int32_t D, int32_t S, int32_t T,
     const int32_t* __restrict__ block_tables, int32_t max_blocks,
     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens,
-    const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, uint32_t page_blocks)
+    const uint16_t* __restrict__ k_new, const uint16_t* __restrict__ v_new, uint32_t page_blocks, int64_t next_layer, int64_t next_kv)
 {
+    layer_base += blockIdx.y * next_layer; k_new += blockIdx.y * next_kv; v_new += blockIdx.y * next_kv;
     if (blockIdx.x < page_blocks)
         append_page_block<PS>((int32_t)blockIdx.x, layer_base, page_stride, num_pages, Hkv, D, S, block_tables, max_blocks,
                               ctx_lens, cu_q_lens, k_new, v_new);
@@ -365,6 +368,12 @@ __global__ __launch_bounds__(kAppendThreads) void append_mixed_kernel(
 
 int launch_append(const cs_kv_pool& pool, int32_t layer, const cs_batch& b,
                   const void* k_new, const void* v_new, hipStream_t st)
+{
+    return launch_append_layers(pool, layer, LayerSpan{1, 0, 0, 0}, b, k_new, v_new, st);
+}
+
+int launch_append_layers(const cs_kv_pool& pool, int32_t layer, const LayerSpan& span, const cs_batch& b,
+                         const void* k_new, const void* v_new, hipStream_t st)
 {
     if (b.num_tokens == 0) return CS_OK;
     bool any_single = false, any_chunk = false;
@@ -382,31 +391,33 @@ int launch_append(const cs_kv_pool& pool, int32_t layer, const cs_batch& b,
     const uint16_t* kn = (const uint16_t*)k_new;
     const uint16_t* vn = (const uint16_t*)v_new;
     if (any_chunk && any_single) {
-        const dim3 grid((uint32_t)(page_blocks + token_blocks));
+        const dim3 grid((uint32_t)(page_blocks + token_blocks), (uint32_t)span.n);
         if (pool.page_size == 16)
             hipLaunchKernelGGL(append_mixed_kernel<16>, grid, dim3(kAppendThreads), 0, st,
                                layer_base, pool.page_stride, pool.num_pages, pool.num_kv_heads, pool.head_dim,
                                b.num_seqs, b.num_tokens, b.block_tables, b.max_blocks_per_seq, b.ctx_lens, b.cu_q_lens,
-                               kn, vn, (uint32_t)page_blocks);
+                               kn, vn, (uint32_t)page_blocks, span.pool, span.kv);
         else
             hipLaunchKernelGGL(append_mixed_kernel<8>, grid, dim3(kAppendThreads), 0, st,
                                layer_base, pool.page_stride, pool.num_pages, pool.num_kv_heads, pool.head_dim,
                                b.num_seqs, b.num_tokens, b.block_tables, b.max_blocks_per_seq, b.ctx_lens, b.cu_q_lens,
-                               kn, vn, (uint32_t)page_blocks);
+                               kn, vn, (uint32_t)page_blocks, span.pool, span.kv);
     } else if (any_chunk) {
         if (pool.page_size == 16)
-            hipLaunchKernelGGL(append_page_kernel<16>, dim3((uint32_t)page_blocks), dim3(kAppendThreads), 0, st,
+            hipLaunchKernelGGL(append_page_kernel<16>, dim3((uint32_t)page_blocks, (uint32_t)span.n), dim3(kAppendThreads), 0, st,
                                layer_base, pool.page_stride, pool.num_pages, pool.num_kv_heads, pool.head_dim,
-                               b.num_seqs, b.block_tables, b.max_blocks_per_seq, b.ctx_lens, b.cu_q_lens, kn, vn);
+                               b.num_seqs, b.block_tables, b.max_blocks_per_seq, b.ctx_lens, b.cu_q_lens, kn, vn,
+                               span.pool, span.kv);
         else
-            hipLaunchKernelGGL(append_page_kernel<8>, dim3((uint32_t)page_blocks), dim3(kAppendThreads), 0, st,
+            hipLaunchKernelGGL(append_page_kernel<8>, dim3((uint32_t)page_blocks, (uint32_t)span.n), dim3(kAppendThreads), 0, st,
                                layer_base, pool.page_stride, pool.num_pages, pool.num_kv_heads, pool.head_dim,
-                               b.num_seqs, b.block_tables, b.max_blocks_per_seq, b.ctx_lens, b.cu_q_lens, kn, vn);
+                               b.num_seqs, b.block_tables, b.max_blocks_per_seq, b.ctx_lens, b.cu_q_lens, kn, vn,
+                               span.pool, span.kv);
     } else if (any_single) {
-        hipLaunchKernelGGL(append_token_kernel, dim3((uint32_t)token_blocks), dim3(kAppendThreads), 0, st,
+        hipLaunchKernelGGL(append_token_kernel, dim3((uint32_t)token_blocks, (uint32_t)span.n), dim3(kAppendThreads), 0, st,
                            layer_base, pool.page_stride, pool.num_pages, pool.num_kv_heads, pool.head_dim,
                            b.num_seqs, b.num_tokens, b.block_tables, b.max_blocks_per_seq, b.ctx_lens,
-                           b.cu_q_lens, kn, vn, pool.page_size);
+                           b.cu_q_lens, kn, vn, pool.page_size, span.pool, span.kv);
     }
     return check_launch("append kernels");
 }

@@ -49,7 +49,7 @@ __global__ __launch_bounds__(kPlanThreads) void decode_plan_kernel(
     }
 }
 
-// grid = items * Hkv workgroups, kv head fastest (the heads of one page are neighbours
+// grid = (items * Hkv, layers) workgroups, kv head fastest (the heads of one page are neighbours
 // in memory, so neighbouring workgroups share DRAM pages and translations).
 template <int D, class Src, class E, int kAhead, int PS>
 __global__ __launch_bounds__(kDecodeThreads, 2) void decode_split_kernel(
@@ -59,33 +59,36 @@ __global__ __launch_bounds__(kDecodeThreads, 2) void decode_split_kernel(
     const Src src,
     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens,
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out,
-    float scale_log2e, const DecodePartials part)
+    float scale_log2e, const DecodePartials part, int64_t next_layer, int64_t next_q)
 {
     __shared__ DecodeLds<D> lds;
-    const int32_t item = blockIdx.x / Hkv, g = blockIdx.x - item * Hkv;
-    decode_item<D, Src, E, kAhead, PS>(lds, layer_base, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
-                           cu_q_lens, q, out, scale_log2e, part, item, g);
+    const int32_t item = blockIdx.x / Hkv, g = blockIdx.x - item * Hkv, n_items = gridDim.x / Hkv;
+    decode_item<D, Src, E, kAhead, PS>(lds, layer_base + blockIdx.y * next_layer, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
+                           cu_q_lens, q + blockIdx.y * next_q, out + blockIdx.y * next_q, scale_log2e,
+                           part.of_layer(blockIdx.y, n_items, Hkv * G, Hkv, D), item, g);
     if constexpr (std::is_same_v<Src, ItemsInArgs>) {
         if (part.words)
-            merge_in_place<D, E>(lds, part, src, [](int32_t) { return (int32_t)blockIdx.x; }, 1, ctx_lens, cu_q_lens, Hkv, G, out);
+            merge_in_place<D, E>(lds, part, src, [](int32_t) { return (int32_t)(blockIdx.y * gridDim.x + blockIdx.x); }, 1, ctx_lens,
+                                 cu_q_lens, Hkv, G, out, n_items, next_q);
     }
 }
 
-// Merge of the partials of the cut sequences where the workgroups do not do it themselves: grid =
-// items * Hkv as above; the workgroup of a cut sequence's first item merges it.
+// Merge of the partials of the cut sequences where the workgroups do not do it themselves: grid as
+// above; the workgroup of a cut sequence's first item merges it.
 template <int D, class Src, class E>
 __global__ __launch_bounds__(kDecodeThreads) void decode_merge_kernel(
     int32_t Hkv, int32_t G, const Src src, const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens,
-    uint16_t* __restrict__ out, const DecodePartials part)
+    uint16_t* __restrict__ out, const DecodePartials part, int64_t next_q)
 {
-    const int32_t item = blockIdx.x / Hkv, g = blockIdx.x - item * Hkv, Hq = Hkv * G;
+    const int32_t n_items = gridDim.x / Hkv, item = blockIdx.x / Hkv, g = blockIdx.x - item * Hkv, Hq = Hkv * G;
     DecodeItem it;
     if (!fetch_item(src, item, ctx_lens, cu_q_lens, it) || it.n_splits == 1 || item != it.first_item) return;
-    merge_pieces<D, E>(part, it.first_item, it.n_splits, Hq, g, G, out + (int64_t)it.token * Hq * D);
+    merge_pieces<D, E>(part.of_layer(blockIdx.y, n_items, Hq, Hkv, D), it.first_item, it.n_splits, Hq, g, G,
+                       out + blockIdx.y * next_q + (int64_t)it.token * Hq * D);
 }
 
 template <class E>
-static int launch_decode_as(const cs_kv_pool& pool, int32_t layer, const cs_batch& b, const DecodePlan& plan,
+static int launch_decode_as(const cs_kv_pool& pool, int32_t layer, const LayerSpan& span, const cs_batch& b, const DecodePlan& plan,
                             const void* q, void* out, int32_t Hq, float scale, void* workspace, hipStream_t st,
                             bool merge_only)
 {
@@ -93,25 +96,25 @@ static int launch_decode_as(const cs_kv_pool& pool, int32_t layer, const cs_batc
     const int32_t Hkv = pool.num_kv_heads, D = pool.head_dim, G = Hq / Hkv;
     const uint16_t* layer_base = (const uint16_t*)pool.base + (int64_t)layer * pool.layer_stride;
     const float scale_log2e = scale * 1.4426950408889634f;
-    const DecodeWorkspace w = decode_workspace(plan, Hq, Hkv, D);
+    const DecodeWorkspace w = decode_workspace(plan, Hq, Hkv, D, span.n);
     char* ws = (char*)workspace;
     const bool cut = plan.num_multi > 0, in_place = cut && plan.merges_in_place && !merge_only;
     const DecodePartials part = {(float*)(ws + w.part_o), (float*)(ws + w.part_ml), in_place ? (uint64_t*)ws : nullptr,
                                  in_place ? next_launch_number() : 0};
     const uint32_t n_items = plan.in_args || cut ? plan.total_items : b.num_seqs;
-    dim3 grid(n_items * (uint32_t)Hkv);
+    dim3 grid(n_items * (uint32_t)Hkv, (uint32_t)span.n);
 #define CS_LAUNCH_DECODE_P(DD, SRC, src, AH, PS)                                                        \
     hipLaunchKernelGGL((decode_split_kernel<DD, SRC, E, AH, PS>), grid, dim3(kDecodeThreads), 0, st, layer_base, \
                        pool.page_stride, pool.num_pages, Hkv, G, b.block_tables, b.max_blocks_per_seq, \
                        src, b.ctx_lens, b.cu_q_lens, (const uint16_t*)q, (uint16_t*)out,               \
-                       scale_log2e, part);
+                       scale_log2e, part, span.pool, span.q);
 #define CS_LAUNCH_DECODE_A(DD, SRC, src, AH)                                                            \
     if (pool.page_size == 16) { CS_LAUNCH_DECODE_P(DD, SRC, src, AH, 16) } else { CS_LAUNCH_DECODE_P(DD, SRC, src, AH, 8) }
 #define CS_LAUNCH_DECODE(DD, SRC, src)                                                                 \
     if (plan.pages_ahead == 2) { CS_LAUNCH_DECODE_A(DD, SRC, src, 2) } else { CS_LAUNCH_DECODE_A(DD, SRC, src, 1) }
 #define CS_LAUNCH_MERGE(DD, SRC, src)                                                                  \
     hipLaunchKernelGGL((decode_merge_kernel<DD, SRC, E>), grid, dim3(kDecodeThreads), 0, st, Hkv, G, src, b.ctx_lens, \
-                       b.cu_q_lens, (uint16_t*)out, part);
+                       b.cu_q_lens, (uint16_t*)out, part, span.q);
     if (plan.in_args) {
         // (merge_only: the fused mixed-batch kernel has already done the items' work)
         if (!merge_only) {
@@ -138,12 +141,19 @@ static int launch_decode_as(const cs_kv_pool& pool, int32_t layer, const cs_batc
     return check_launch("decode kernels");
 }
 
+int launch_decode_layers(const cs_kv_pool& pool, int32_t layer, const LayerSpan& span, const cs_batch& b, const DecodePlan& plan,
+                         const void* q, void* out, int32_t Hq, float scale, void* workspace, hipStream_t st, bool f16,
+                         bool merge_only)
+{
+    return f16 ? launch_decode_as<F16>(pool, layer, span, b, plan, q, out, Hq, scale, workspace, st, merge_only)
+               : launch_decode_as<Bf16>(pool, layer, span, b, plan, q, out, Hq, scale, workspace, st, merge_only);
+}
+
 int launch_decode(const cs_kv_pool& pool, int32_t layer, const cs_batch& b, const DecodePlan& plan,
                   const void* q, void* out, int32_t Hq, float scale, void* workspace, hipStream_t st, bool f16,
                   bool merge_only)
 {
-    return f16 ? launch_decode_as<F16>(pool, layer, b, plan, q, out, Hq, scale, workspace, st, merge_only)
-               : launch_decode_as<Bf16>(pool, layer, b, plan, q, out, Hq, scale, workspace, st, merge_only);
+    return launch_decode_layers(pool, layer, LayerSpan{1, 0, 0, 0}, b, plan, q, out, Hq, scale, workspace, st, f16, merge_only);
 }
 
 }  // namespace cs

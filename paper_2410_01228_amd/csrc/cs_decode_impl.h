@@ -237,6 +237,11 @@ struct DecodePartials {
     float* ml;
     uint64_t* words;
     uint64_t launch;
+    // those of layer `l` of a launch of several layers with n_items items each
+    __device__ __forceinline__ DecodePartials of_layer(int32_t l, int32_t n_items, int32_t Hq, int32_t Hkv, int32_t D) const {
+        const int64_t i = (int64_t)l * n_items;
+        return {o + i * Hq * D, ml + i * Hq * 2, words ? words + i * Hkv : nullptr, launch};
+    }
 };
 
 // Merge of the n_splits partials of one (cut sequence, kv head), by one workgroup: a lane per (head,
@@ -447,26 +452,30 @@ __device__ __forceinline__ void decode_item(
     }
 }
 
-// The end of a workgroup that has worked off pairs pair_at(0) .. pair_at(n_pairs - 1) (item * Hkv + kv
-// head; -1: none): announces the partials it left, and merges the sequences it finds complete.  All
+// The end of a workgroup that has worked off pairs pair_at(0) .. pair_at(n_pairs - 1) ((layer of the
+// launch * n_items + item) * Hkv + kv head; -1: none): announces the partials it left, and merges the sequences it finds complete.  All
 // announcements go out together and behind the last pair, so a workgroup that walks several pairs
 // does not stop between them.
 template <int D, class E, class Src, class PairAt>
 __device__ __forceinline__ void merge_in_place(
     DecodeLds<D>& lds, const DecodePartials& part, const Src& src, PairAt pair_at, int32_t n_pairs,
-    const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens, int32_t Hkv, int32_t G, uint16_t* __restrict__ out)
+    const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens, int32_t Hkv, int32_t G, uint16_t* __restrict__ out,
+    int32_t n_items, int64_t next_q)
 {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int32_t Hq = Hkv * G;
+    int32_t layer;
     auto piece_of = [&](int32_t k, DecodeItem& it, int32_t& item, int32_t& g) {      // is pair k a piece of a cut sequence?
         const int32_t pair = pair_at(k);
         if (pair < 0) return false;
         item = pair / Hkv;
         g = pair - item * Hkv;
+        layer = item / n_items;
+        item -= layer * n_items;
         return fetch_item(src, item, ctx_lens, cu_q_lens, it) && it.n_splits > 1;
     };
     auto words_of = [&](const DecodeItem& it, int32_t g) {
-        return Announcements(Shared(part.words + (int64_t)it.first_item * Hkv + g, (uint32_t)it.n_splits * Hkv * 8), 0,
+        return Announcements(Shared(part.words + ((int64_t)layer * n_items + it.first_item) * Hkv + g, (uint32_t)it.n_splits * Hkv * 8), 0,
                              Hkv * 8, it.n_splits, part.launch);
     };
     DecodeItem it;
@@ -484,7 +493,8 @@ __device__ __forceinline__ void merge_in_place(
     for (int32_t k = 0; k < n_pairs; ++k) {
         if (!lds.last[k]) continue;
         piece_of(k, it, item, g);
-        merge_pieces<D, E>(part, it.first_item, it.n_splits, Hq, g, G, out + (int64_t)it.token * Hq * D);
+        merge_pieces<D, E>(part.of_layer(layer, n_items, Hq, Hkv, D), it.first_item, it.n_splits, Hq, g, G,
+                           out + layer * next_q + (int64_t)it.token * Hq * D);
         if (wave == 0) words_of(it, g).clear();
     }
 }

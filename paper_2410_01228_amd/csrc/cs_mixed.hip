@@ -31,7 +31,7 @@ union MixedLds {
 // tiles of positions 0 .. cut_first_pos-1, then, range-major like the prefill kernel's own grid,
 // the key ranges of the positions behind them (cut_first_pos == 0: every tile longer than
 // range_steps is cut; == num_slots with max_ranges == 1: none is).  Decode workgroup j takes the pairs j, 2*dec_wgs-1-j, 2*dec_wgs+j, ... of the
-// n_decode (item, kv head) pairs: the items are sorted longest first, so walking the rounds back
+// n_decode ((layer, item), kv head) pairs: the items of a layer are sorted longest first, so walking the rounds back
 // and forth evens the sums; with dec_wgs == n_decode that is one pair each.
 template <int D, class E, int kPriority, int PS>
 __global__ __launch_bounds__(kPrefillThreads, 2) void mixed_kernel(
@@ -42,12 +42,22 @@ __global__ __launch_bounds__(kPrefillThreads, 2) void mixed_kernel(
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float scale_log2e,
     int32_t range_steps, int32_t base_slot, int32_t num_slots, int32_t cut_first_pos, int32_t max_ranges,
     float* __restrict__ prefill_part, uint32_t dec_first, uint32_t dec_wgs, uint32_t n_decode, int32_t backwards,
-    const ItemsInArgs items, const DecodePartials part)
+    const ItemsInArgs items, const DecodePartials part,
+    int32_t layers, int64_t next_layer, int64_t next_q)
 {
     __shared__ MixedLds<D> lds;
     if (blockIdx.x < dec_first || blockIdx.x >= dec_first + dec_wgs) {
-        const uint32_t ti = blockIdx.x < dec_first ? blockIdx.x : blockIdx.x - dec_wgs;
+        uint32_t ti = blockIdx.x < dec_first ? blockIdx.x : blockIdx.x - dec_wgs;
         const uint32_t wgs_whole = (uint32_t)cut_first_pos * Hkv, wgs_per_range = (uint32_t)(num_slots - cut_first_pos) * Hkv;
+        if (layers > 1) {                                // layer after layer
+            const uint32_t per_layer = wgs_whole + wgs_per_range * max_ranges;
+            const uint32_t l = ti / per_layer;
+            ti -= l * per_layer;
+            layer_base += l * next_layer;
+            q += l * next_q;
+            out += l * next_q;
+            prefill_part += (int64_t)l * wgs_per_range * max_ranges * kPartialFloats<D>;
+        }
         // a whole tile: one range longer than any tile (and small enough to add a tile's steps to)
         int32_t pos, g, range = 0, steps_per_range = 1 << 30;
         float* part_tile = nullptr;
@@ -68,6 +78,7 @@ __global__ __launch_bounds__(kPrefillThreads, 2) void mixed_kernel(
                            ctx_lens, cu_q_lens, q, out, scale_log2e, steps_per_range, part_tile, part.launch, g, b, range);
     } else {
         const uint32_t j = blockIdx.x - dec_first;
+        const int32_t n_items = n_decode / ((uint32_t)layers * Hkv);
         auto pair_at = [&](int32_t round) -> int32_t {
             const uint32_t w = (uint32_t)round * dec_wgs + ((round & 1) ? dec_wgs - 1 - j : j);
             return w < n_decode ? (int32_t)w : -1;
@@ -76,33 +87,37 @@ __global__ __launch_bounds__(kPrefillThreads, 2) void mixed_kernel(
         for (; (uint32_t)round * dec_wgs < n_decode; ++round) {
             const int32_t w = pair_at(round);
             if (w < 0) continue;
-            const int32_t item = w / Hkv, g = w - item * Hkv;
+            int32_t item = w / Hkv;
+            const int32_t g = w - item * Hkv, l = item / n_items;
+            item -= l * n_items;
             // one page ahead, with loads the compiler can count (a workgroup that shares its CU
             // with a tile must stream by itself); a deeper queue only delays the tile's own
             // copies, which share the CU's memory pipeline
-            decode_item<D, ItemsInArgs, E, 1, PS, true>(lds.decode, layer_base, page_stride, num_pages, Hkv, G, block_tables, max_blocks,
-                                           items, ctx_lens, cu_q_lens, q, out, scale_log2e, part, item, g);
+            decode_item<D, ItemsInArgs, E, 1, PS, true>(lds.decode, layer_base + l * next_layer, page_stride, num_pages, Hkv, G, block_tables,
+                                           max_blocks, items, ctx_lens, cu_q_lens, q + l * next_q, out + l * next_q, scale_log2e,
+                                           part.of_layer(l, n_items, Hkv * G, Hkv, D), item, g);
             __syncthreads();     // the next pair reuses the merge buffers
         }
-        if (part.words) merge_in_place<D, E>(lds.decode, part, items, pair_at, round, ctx_lens, cu_q_lens, Hkv, G, out);
+        if (part.words) merge_in_place<D, E>(lds.decode, part, items, pair_at, round, ctx_lens, cu_q_lens, Hkv, G, out,
+                                              n_items, next_q);
     }
 }
 
 template <class E>
-static int launch_mixed_as(const cs_kv_pool& pool, int32_t layer, const cs_batch& b, const DecodePlan& dplan,
+static int launch_mixed_as(const cs_kv_pool& pool, int32_t layer, const LayerSpan& span, const cs_batch& b, const DecodePlan& dplan,
                            const PrefillPlan& pplan, const void* q, void* out, int32_t Hq, float scale,
                            void* decode_ws, void* prefill_ws, hipStream_t st, int32_t prio, int32_t persistent_wgs)
 {
     const int32_t Hkv = pool.num_kv_heads, D = pool.head_dim, G = Hq / Hkv;
     const uint16_t* layer_base = (const uint16_t*)pool.base + (int64_t)layer * pool.layer_stride;
     const float scale_log2e = scale * 1.4426950408889634f;
-    const int64_t n_prefill = ((int64_t)pplan.cut_first_pos + (int64_t)(pplan.num_slots - pplan.cut_first_pos) * pplan.max_ranges) * Hkv;
-    const int64_t n_decode = (int64_t)dplan.total_items * Hkv;
+    const int64_t n_prefill = ((int64_t)pplan.cut_first_pos + (int64_t)(pplan.num_slots - pplan.cut_first_pos) * pplan.max_ranges) * Hkv * span.n;
+    const int64_t n_decode = (int64_t)dplan.total_items * Hkv * span.n;
     // decode beside the tiles: a few workgroups first; behind the tiles: one per pair, last
     const int64_t dec_wgs = persistent_wgs > 0 ? std::min<int64_t>(persistent_wgs, n_decode) : n_decode;
     const int64_t dec_first = persistent_wgs > 0 ? 0 : n_prefill;
     if (n_prefill + dec_wgs > 2147483647ll) return CS_ERR_UNSUPPORTED;
-    const DecodeWorkspace w = decode_workspace(dplan, Hq, Hkv, D);
+    const DecodeWorkspace w = decode_workspace(dplan, Hq, Hkv, D, span.n);
     const DecodePartials part = {(float*)((char*)decode_ws + w.part_o), (float*)((char*)decode_ws + w.part_ml),
                                  dplan.merges_in_place ? (uint64_t*)decode_ws : nullptr, next_launch_number()};
     dim3 grid((uint32_t)(n_prefill + dec_wgs));
@@ -112,7 +127,7 @@ static int launch_mixed_as(const cs_kv_pool& pool, int32_t layer, const cs_batch
                        b.cu_q_lens, (const uint16_t*)q, (uint16_t*)out, scale_log2e, pplan.range_steps,         \
                        pplan.base_slot, pplan.num_slots, pplan.cut_first_pos, pplan.max_ranges,                 \
                        (float*)prefill_ws, (uint32_t)dec_first, (uint32_t)dec_wgs, (uint32_t)n_decode, (int32_t)pplan.backwards,    \
-                       dplan.arg_items, part);
+                       dplan.arg_items, part, span.n, span.pool, span.q);
 #define CS_LAUNCH_MIXED(DD, PRIO)                                                                            \
     if (pool.page_size == 16) { CS_LAUNCH_MIXED_P(DD, PRIO, 16) } else { CS_LAUNCH_MIXED_P(DD, PRIO, 8) }
     if (D == 128) { if (prio == 2) { CS_LAUNCH_MIXED(128, 2) } else if (prio == 1) { CS_LAUNCH_MIXED(128, 1) } else { CS_LAUNCH_MIXED(128, 0) } }
@@ -122,12 +137,20 @@ static int launch_mixed_as(const cs_kv_pool& pool, int32_t layer, const cs_batch
     return check_launch("mixed kernel");
 }
 
+int launch_mixed_layers(const cs_kv_pool& pool, int32_t layer, const LayerSpan& span, const cs_batch& b, const DecodePlan& dplan,
+                        const PrefillPlan& pplan, const void* q, void* out, int32_t Hq, float scale,
+                        void* decode_ws, void* prefill_ws, hipStream_t st, bool f16, int32_t prio, int32_t persistent_wgs)
+{
+    return f16 ? launch_mixed_as<F16>(pool, layer, span, b, dplan, pplan, q, out, Hq, scale, decode_ws, prefill_ws, st, prio, persistent_wgs)
+               : launch_mixed_as<Bf16>(pool, layer, span, b, dplan, pplan, q, out, Hq, scale, decode_ws, prefill_ws, st, prio, persistent_wgs);
+}
+
 int launch_mixed(const cs_kv_pool& pool, int32_t layer, const cs_batch& b, const DecodePlan& dplan,
                  const PrefillPlan& pplan, const void* q, void* out, int32_t Hq, float scale,
                  void* decode_ws, void* prefill_ws, hipStream_t st, bool f16, int32_t prio, int32_t persistent_wgs)
 {
-    return f16 ? launch_mixed_as<F16>(pool, layer, b, dplan, pplan, q, out, Hq, scale, decode_ws, prefill_ws, st, prio, persistent_wgs)
-               : launch_mixed_as<Bf16>(pool, layer, b, dplan, pplan, q, out, Hq, scale, decode_ws, prefill_ws, st, prio, persistent_wgs);
+    return launch_mixed_layers(pool, layer, LayerSpan{1, 0, 0, 0}, b, dplan, pplan, q, out, Hq, scale, decode_ws, prefill_ws, st, f16,
+                               prio, persistent_wgs);
 }
 
 }  // namespace cs
