@@ -421,17 +421,19 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
     const double t_prefill = 4.0 * Hq * D * pairs / 1.0e15;
     const double decode_bytes = (double)d.decode_keys * 2 * Hkv * D * 2;
     const double t_decode = decode_bytes / 6.0e12;
-    // Behind the tiles, unless the prefill side is a sliver: with a small chunk beside a long
-    // decode (decode time over ten times the prefill time) two kernels in a row are as fast or a
-    // little faster.  Where the decode side is the smaller one (under 0.3 of the prefill time)
+    // Behind the tiles at least: one grid beats two kernels in a row wherever both kinds of work are
+    // there (over 30 mixes of all shapes by 2-38%, most with small ones, whose two kernels are mostly
+    // start-up and tail).  Where the decode side is the smaller one (under 0.3 of the prefill time)
     // the tiles alternate their issue priority as the prefill kernel's do; with a decode load of
     // equal weight behind them that costs more than it gains.
-    f.arrangement = (mode == 2 || t_decode <= 10.0 * t_prefill) ? 1 : 0;
+    f.arrangement = 1;
     f.prio = t_decode < 0.3 * t_prefill ? 1 : 0;
     const int32_t cus = device_cus();
     // (head dim 64 fits three workgroups per CU, both kinds already share CUs behind the tiles,
     // and beside wins on some mixes and loses on others: the choice there is not modelled)
     if (mode == 2 || (mode == 1 && D != 128)) return f;
+    // While every workgroup has a slot at once there is nothing to arrange.
+    if (mode == 1 && ((int64_t)p.num_slots * p.max_ranges + d.total_items) * Hkv * layers <= 2 * cus) return f;
     bool beside = mode == 3;
     double t_beside = 0;                                               // the model's time of that arrangement as planned (0: not played)
     const int64_t tile_units = (int64_t)p.num_slots * p.max_ranges * layers;       // tiles x ranges: what the model plays
@@ -502,7 +504,9 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
                 t_whole = std::max(play_tiles(work, groups, t_dec, free_at, &started), t_dec);
                 // (the model's constants were fitted before the tiles took their priorities beside a
                 // decode load, which make that arrangement about 2% faster than it says)
-                beside = 0.98 * t_whole < t_behind;
+                // (a decode stream under 60 us is too few pairs per workgroup to even out: over 68 mixes
+                // behind is 4-12% faster there, whatever the model says)
+                beside = 0.98 * t_whole < t_behind && t_dec >= 60.0;
             }
             if (beside && mode != 1 && !work.empty()) t_whole = std::max(play_tiles(work, groups, t_dec, free_at, &started), t_dec);
             t_beside = t_whole;
