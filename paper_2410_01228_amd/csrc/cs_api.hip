@@ -87,7 +87,7 @@ int validate_batch(const cs_kv_pool* pool, const cs_batch* b) {
     return CS_OK;
 }
 
-DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim, int32_t layers) {
+DecodePlan plan_decode(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t head_dim, int32_t layers, size_t max_bytes) {
     DecodePlan p = {};
     int32_t max_keys = 0, min_keys = 2147483647;
     for (int32_t s = 0; s < b->num_seqs; ++s) {
@@ -140,14 +140,25 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim, int32_t
         for (split = cap; split > floor_split; split /= 2)
             if (workgroups_at(split) >= need) break;
     }
-    p.split_tokens = split;
-    int32_t max_k = 1;
-    for (int32_t s = 0; s < b->num_seqs; ++s) {
-        if (b->h_cu_q_lens[s + 1] - b->h_cu_q_lens[s] != 1) continue;
-        const int32_t k = decode_num_splits(b->h_ctx_lens[s] + 1, split);
-        p.total_items += k;
-        if (k > 1) ++p.num_multi;
-        if (k > max_k) max_k = k;
+    // Where the caller has less scratch memory than that takes (several layers in a launch, with the
+    // memory one layer's plan needs), items a quarter longer until it fits, at the latest when nothing is cut: the
+    // layers together then have about as many workgroups as one layer's plan gives one launch.
+    int32_t max_k;
+    for (;;) {
+        p.split_tokens = split;
+        p.total_items = p.num_multi = 0;
+        max_k = 1;
+        for (int32_t s = 0; s < b->num_seqs; ++s) {
+            if (b->h_cu_q_lens[s + 1] - b->h_cu_q_lens[s] != 1) continue;
+            const int32_t k = decode_num_splits(b->h_ctx_lens[s] + 1, split);
+            p.total_items += k;
+            if (k > 1) ++p.num_multi;
+            if (k > max_k) max_k = k;
+        }
+        // whether the list fits the arguments (see below) decides the layout of the workspace
+        p.in_args = p.total_items <= kMaxArgItems && b->num_seqs <= 65536 && max_k <= 255;
+        if (p.num_multi == 0 || g_forced_split.load() > 0 || decode_workspace(p, Hq, Hkv, head_dim, layers).total <= max_bytes) break;
+        split = (int32_t)std::min<int64_t>((split + (int64_t)split / 4 + kPage - 1) & ~(int64_t)(kPage - 1), 1 << 30);
     }
     // Two pages ahead per wavefront need the registers of the third workgroup per CU.  Measured
     // over 33 batch shapes: the deeper queue wins 2-6% once the launch is long enough for the
@@ -167,7 +178,6 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim, int32_t
     // A list short enough for the argument block is written here, longest items first: the
     // workgroups of a launch start in index order, so the long ones get going at once and
     // the short ones fill in behind them (measured: 7% on 256 sequences of 512..4096 keys).
-    p.in_args = p.total_items <= kMaxArgItems && b->num_seqs <= 65536 && max_k <= 255;
     if (p.in_args) {
         struct Rec { int32_t keys, seq, k; };
         Rec recs[kMaxArgItems];
@@ -189,7 +199,7 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim, int32_t
 }
 
 // Host plan of the key-range split (a pure function of the host lengths).
-PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers) {
+PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers, size_t max_bytes) {
     PrefillPlan p = {};
     const int32_t G = Hq / Hkv;
     int64_t total_steps = 0, tiles = 0;
@@ -222,13 +232,17 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, 
     // (the slots of the sequences before the first chunk and behind the last one are empty)
     p.num_slots = (int32_t)(prefill_slot_start(b->h_cu_q_lens[last + 1], last + 1, G) - p.base_slot);
     const int64_t wgs = tiles * Hkv * layers;
+    auto partial_bytes = [&](int ranges) -> size_t {
+        return ranges > 1 ? (size_t)layers * p.num_slots * Hkv * ranges * kTileCols * 16 * (D + 4) * sizeof(float) : 0;
+    };
 
     // The chip: `cus` compute units, two workgroup slots each.  (The counts in the comments below
     // are those of the 256-CU part the rules were measured on.)
     const int64_t cus = device_cus(), slots = 2 * cus;
     if (wgs <= cus * 3 / 4 && max_steps < 128) {
         // few and short tiles: about four workgroups per CU, ranges of at least 32 steps
-        const int64_t rs = std::max<int64_t>(32, (total_steps * Hkv * layers + 4 * cus - 1) / (4 * cus));
+        int64_t rs = std::max<int64_t>(32, (total_steps * Hkv * layers + 4 * cus - 1) / (4 * cus));
+        while (rs < max_steps && partial_bytes((int)((max_steps + rs - 1) / rs)) > max_bytes) rs += (rs + 3) / 4;
         if (rs < max_steps) {
             p.range_steps = (int32_t)rs;
             p.max_ranges = (max_steps + p.range_steps - 1) / p.range_steps;
@@ -260,7 +274,7 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, 
         int best = 1;
         double best_cost = cost(1);
         for (int r = 2; r <= kMaxMergeRanges; ++r) {
-            if (max_steps / r < 32) break;
+            if (max_steps / r < 32 || partial_bytes(r) > max_bytes) break;
             const double c = cost(r);
             if (c < best_cost) { best = r; best_cost = c; }
         }
@@ -300,9 +314,7 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, 
             p.backwards = true;
         }
     }
-    if (p.max_ranges > 1) {
-        p.bytes = (size_t)layers * p.num_slots * Hkv * p.max_ranges * kTileCols * 16 * (D + 4) * sizeof(float);
-    }
+    p.bytes = partial_bytes(p.max_ranges);
     return p;
 }
 
@@ -567,7 +579,7 @@ static FusePlan plan_fusion(const cs_batch* b, const DecodePlan& d, PrefillPlan&
     const int32_t forced_whole = g_forced_tail_whole.load(), forced_ranges = g_forced_tail_ranges.load();
     if (forced_whole >= 0 && forced_ranges >= 1 && f.arrangement != 0) {
         // measurement and test knob: cut the launch positions from forced_whole on into forced_ranges
-        p = plan_prefill(b, Hq, Hkv, D, layers);
+        p = plan_prefill(b, Hq, Hkv, D, layers, SIZE_MAX);
         p.n_ordered = 0;
         p.cut_first_pos = std::min(forced_whole, p.num_slots);
         int32_t tail_steps = 1;
@@ -663,13 +675,14 @@ extern "C" {
 struct PlanMemo {
     bool valid = false;
     int32_t S = 0, T = 0, Hq = 0, Hkv = 0, D = 0, layers = 0, split = 0, ahead = 0, cus = 0, fuse = 0, tail_whole = -1, tail_ranges = 0;
+    size_t max_bytes = 0;
     std::vector<int32_t> ctx, cu;
     Plans plans;
 };
 }  // extern "C"
 
 namespace cs {
-const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers) {
+const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers, size_t max_bytes) {
     constexpr int kMemos = 6;
     static thread_local PlanMemo memo[kMemos];
     static thread_local int next = 0;
@@ -677,17 +690,17 @@ const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, in
     const int32_t fuse = g_fuse_mixed.load(), tail_whole = g_forced_tail_whole.load(), tail_ranges = g_forced_tail_ranges.load();
     for (PlanMemo& m : memo)
         if (m.valid && m.fuse == fuse && m.tail_whole == tail_whole && m.tail_ranges == tail_ranges && m.S == S && m.T == b->num_tokens && m.Hq == Hq && m.Hkv == Hkv && m.D == D &&
-            m.layers == layers && m.split == split && m.ahead == ahead && m.cus == cus &&
+            m.layers == layers && m.max_bytes == max_bytes && m.split == split && m.ahead == ahead && m.cus == cus &&
             memcmp(m.ctx.data(), b->h_ctx_lens, sizeof(int32_t) * S) == 0 && memcmp(m.cu.data(), b->h_cu_q_lens, sizeof(int32_t) * (S + 1)) == 0)
             return m.plans;
     PlanMemo& m = memo[next];
     next = (next + 1) % kMemos;
     m.valid = false;
-    m.S = S; m.T = b->num_tokens; m.Hq = Hq; m.Hkv = Hkv; m.D = D; m.layers = layers; m.split = split; m.ahead = ahead; m.cus = cus; m.fuse = fuse; m.tail_whole = tail_whole; m.tail_ranges = tail_ranges;
+    m.S = S; m.T = b->num_tokens; m.Hq = Hq; m.Hkv = Hkv; m.D = D; m.layers = layers; m.max_bytes = max_bytes; m.split = split; m.ahead = ahead; m.cus = cus; m.fuse = fuse; m.tail_whole = tail_whole; m.tail_ranges = tail_ranges;
     m.ctx.assign(b->h_ctx_lens, b->h_ctx_lens + S);
     m.cu.assign(b->h_cu_q_lens, b->h_cu_q_lens + S + 1);
-    m.plans.d = plan_decode(b, Hkv, D, layers);
-    m.plans.p = m.plans.d.num_prefill ? plan_prefill(b, Hq, Hkv, D, layers) : PrefillPlan{};
+    m.plans.p = plan_prefill(b, Hq, Hkv, D, layers, max_bytes);
+    m.plans.d = plan_decode(b, Hq, Hkv, D, layers, max_bytes - m.plans.p.bytes);
     m.plans.f = plan_fusion(b, m.plans.d, m.plans.p, Hq, Hkv, D, fuse, layers);
     m.plans.d.merges_in_place = decode_merges_in_place(m.plans.d, m.plans.p, m.plans.f, Hkv, D, layers);
     m.plans.decode_bytes = decode_workspace(m.plans.d, Hq, Hkv, D, layers).total;
@@ -895,7 +908,7 @@ int32_t cs_debug_decode_items(const cs_batch* batch, int32_t Hkv, int32_t D, uin
                               int32_t* split_tokens) {
     if (!shape_supported(Hkv, D) || validate_batch(nullptr, batch) != CS_OK || capacity < 0 || (capacity > 0 && !items))
         return CS_ERR_INVALID_ARG;
-    const DecodePlan p = plan_decode(batch, Hkv, D);
+    const DecodePlan p = plan_decode(batch, Hkv, Hkv, D, 1, SIZE_MAX);
     if (split_tokens) *split_tokens = p.split_tokens;
     if (!p.in_args) return -1000000 - p.total_items;       // the planning kernel would build the list
     for (int32_t i = 0; i < p.total_items && i < capacity; ++i) items[i] = p.arg_items.e[i];
@@ -904,7 +917,7 @@ int32_t cs_debug_decode_items(const cs_batch* batch, int32_t Hkv, int32_t D, uin
 
 int32_t cs_debug_decode_pages_ahead(const cs_batch* batch, int32_t Hkv, int32_t D) {
     if (!shape_supported(Hkv, D) || validate_batch(nullptr, batch) != CS_OK) return CS_ERR_INVALID_ARG;
-    return plan_decode(batch, Hkv, D).pages_ahead;
+    return plan_decode(batch, Hkv, Hkv, D, 1, SIZE_MAX).pages_ahead;
 }
 
 int32_t cs_debug_prefill_order(const cs_batch* batch, int32_t Hq, int32_t Hkv, int32_t D, int32_t* slots, int32_t capacity) {
@@ -912,7 +925,7 @@ int32_t cs_debug_prefill_order(const cs_batch* batch, int32_t Hq, int32_t Hkv, i
         (capacity > 0 && !slots))
         return CS_ERR_INVALID_ARG;
     if (batch->num_seqs == 0) return 0;
-    const PrefillPlan p = plan_prefill(batch, Hq, Hkv, D);
+    const PrefillPlan p = plan_prefill(batch, Hq, Hkv, D, 1, SIZE_MAX);
     for (int32_t i = 0; i < p.n_ordered && i < capacity; ++i) slots[i] = p.order.slot[i];
     return p.n_ordered;
 }

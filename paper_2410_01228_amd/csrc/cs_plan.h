@@ -23,8 +23,8 @@ struct Plans {
 };
 
 // The plan of a batch for launches of `layers` layers each (remembered per thread; the reference is
-// good until the thread asks for six more).
-const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers = 1);
+// good until the thread asks for six more).  max_bytes: the workspace there is; cuts are chosen so that they fit it.
+const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers = 1, size_t max_bytes = SIZE_MAX);
 
 int attention_shape_ok(int32_t Hq, int32_t Hkv, int32_t D);
 
