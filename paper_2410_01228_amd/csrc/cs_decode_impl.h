@@ -276,8 +276,9 @@ __device__ __forceinline__ void merge_pieces(const DecodePartials& part, int32_t
             O *= keep;
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
+                if (i0 + j >= n_splits) break;                             // (not a weight of zero: an infinity in V stays one)
                 const float m = as_float(ml[j][0]);
-                const float f = m == -INFINITY || i0 + j >= n_splits ? 0.f : exp2f(m - M_new);    // a piece without keys
+                const float f = m == -INFINITY ? 0.f : exp2f(m - M_new);                          // a piece without keys
                 L += as_float(ml[j][1]) * f;
                 O += __builtin_bit_cast(f32x4, o[j]) * f;
             }

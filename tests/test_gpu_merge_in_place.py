@@ -48,3 +48,31 @@ def test_merge_in_place_and_by_kernel_agree(Hq, Hkv, D, ctx, split, chunk):
     for out in outs[1:]:
         assert torch.equal(out[:n].view(torch.int16), outs[0][:n].view(torch.int16))
     assert_attention_close(outs[-1], st.oracle_attention(), "merged in place beside tiles")
+
+
+# pieces: fewer than, exactly and more than the eight that a merge holds in flight
+@pytest.mark.parametrize("ctx", [47, 127, 160])
+@pytest.mark.parametrize("cus", [256, 2])
+def test_an_infinity_in_v_stays_one_through_the_merge(ctx, cus):
+    """The last piece's weight is not zero anywhere, so its infinite feature is infinite in the output and
+    the other features are what they are without it."""
+    sh = synth.Shape(8, 2, 128)
+    b = synth.make_batch(sh, [ctx], [1], synth.generator(98))
+    st = Step(b, 98)
+    want = st.oracle_attention()
+    st.v_new[0, 1, 77] = float("inf")
+    pool = cs.Pool(from_bits(st.prior_pool(), "cuda"), 1, b.num_pages, sh.Hkv, sh.D)
+    bb = cs.Batch(b.block_tables, b.ctx_lens, b.cu_q_lens)
+    cs.cs_kv_append(pool, 0, bb, st.k_new.cuda(), st.v_new.cuda())
+    out = torch.full((1, sh.Hq, sh.D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    cs.cs_set_decode_split_tokens(16)
+    try:
+        cs.cs_debug_set_cu_count(cus)                   # merged in place, and by a kernel
+        cs.cs_paged_attention_mixed(pool, 0, bb, st.q.cuda(), out, sh.Hq, sh.scale, cs.workspace_for(bb, sh.Hq, sh.Hkv, sh.D))
+        torch.cuda.synchronize()
+    finally:
+        cs.cs_set_decode_split_tokens(0)
+        cs.cs_debug_set_cu_count(0)
+    assert (out[0, 4:, 77] == float("inf")).all()
+    out[0, 4:, 77] = torch.from_numpy(want[0, 4:, 77]).to(out)
+    assert_attention_close(out, want, "finite features")
