@@ -94,10 +94,10 @@ constexpr int kTokenCopyThreads = 64;
 template <bool kToStaging, int D>
 __global__ __launch_bounds__(kTokenCopyThreads) void token_copy_kernel(
     uint16_t* __restrict__ pool_base, int64_t layer_stride, int64_t page_stride,
-    int32_t num_pages, int32_t layer_begin, const int32_t* __restrict__ token_slots, int32_t n,
+    int32_t num_pages, int32_t layer_begin, const int32_t* __restrict__ token_slots, int32_t n, int32_t first,
     uint16_t* __restrict__ staging, int32_t Hkv, int32_t page_shift)
 {
-    const int32_t i = blockIdx.x / Hkv, h = blockIdx.x - i * Hkv, l = blockIdx.y, lane = threadIdx.x;
+    const int32_t h = blockIdx.x % Hkv, i = first + blockIdx.x / Hkv, l = blockIdx.y, lane = threadIdx.x;
     const int32_t slot = token_slots[i];
     const int32_t page = slot >> page_shift, t = slot & ((1 << page_shift) - 1);
     if (slot < 0 || page >= num_pages) return;                   // never touch a bad slot
@@ -130,15 +130,19 @@ int launch_token_copy(const cs_kv_pool& pool, int32_t layer_begin, int32_t layer
 {
     const int32_t layers = layer_end - layer_begin;
     if (n == 0 || layers == 0) return CS_OK;
-    if ((int64_t)n * pool.num_kv_heads > 2147483647ll) return CS_ERR_UNSUPPORTED;
-    const dim3 grid((uint32_t)n * pool.num_kv_heads, (uint32_t)layers);
     const int32_t page_shift = pool.page_size == 16 ? 4 : 3;
+    // (a launch holds fewer than 2^32 lanes along x: more tokens than that go in several)
+    const int32_t max_tokens = 0x3ffffff / pool.num_kv_heads;
 #define CS_LAUNCH_TOKEN_COPY(DIR, DD)                                                                            \
     hipLaunchKernelGGL((token_copy_kernel<DIR, DD>), grid, dim3(kTokenCopyThreads), 0, st, (uint16_t*)pool.base,   \
-                       pool.layer_stride, pool.page_stride, pool.num_pages, layer_begin, token_slots, n,          \
+                       pool.layer_stride, pool.page_stride, pool.num_pages, layer_begin, token_slots, n, first,   \
                        (uint16_t*)staging, pool.num_kv_heads, page_shift);
-    if (pool.head_dim == 128) { if (to_staging) { CS_LAUNCH_TOKEN_COPY(true, 128) } else { CS_LAUNCH_TOKEN_COPY(false, 128) } }
-    else                      { if (to_staging) { CS_LAUNCH_TOKEN_COPY(true, 64) } else { CS_LAUNCH_TOKEN_COPY(false, 64) } }
+    for (int32_t first = 0, m; first < n; first += m) {
+        m = n - first < max_tokens ? n - first : max_tokens;
+        const dim3 grid((uint32_t)m * pool.num_kv_heads, (uint32_t)layers);
+        if (pool.head_dim == 128) { if (to_staging) { CS_LAUNCH_TOKEN_COPY(true, 128) } else { CS_LAUNCH_TOKEN_COPY(false, 128) } }
+        else                      { if (to_staging) { CS_LAUNCH_TOKEN_COPY(true, 64) } else { CS_LAUNCH_TOKEN_COPY(false, 64) } }
+    }
 #undef CS_LAUNCH_TOKEN_COPY
     return check_launch("token_copy_kernel");
 }
