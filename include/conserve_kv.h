@@ -227,8 +227,8 @@ int cs_kv_ckpt_load(const cs_kv_pool* pool, int32_t layer_begin, int32_t layer_e
                     const int32_t* page_ids, int32_t n, void* staging, size_t staging_bytes,
                     const void* host_buf, void* stream);
 
-/* Layer-wise preemption (Sec. 4.3, Alg. 1): the layers of one iteration are enqueued one
- * call at a time, and every `check_every` layers (a safepoint; the paper uses 4) the driver
+/* Layer-wise preemption (Sec. 4.3, Alg. 1): the layers of one iteration are enqueued in
+ * order, and every `check_every` layers (a safepoint; the paper uses 4) the driver
  * looks at a preemption signal that a scheduler thread raises when an online request
  * arrives.  Once it is raised, the remaining layers run with only the first
  * `num_online_seqs` sequences (the batch is ordered online-first, so this is a smaller
@@ -255,7 +255,13 @@ typedef struct {
  * cs_run_layers_workspace_bytes() -- the larger of what the full batch and what its online
  * prefix need (fewer sequences are cut finer, so the prefix can need more than the whole).
  * Everything that can refuse the iteration (shapes, pointers, workspace size for both plans)
- * is checked before the first layer is enqueued.  Errors as for the two calls. */
+ * is checked before the first layer is enqueued.  Errors as for the two calls.
+ * Between two safepoints up to four layers share an append launch where no layer's output overlaps
+ * another layer's output or any input (layers that share or chain buffers run one after the other; a
+ * layer's q may be its own out), and share an attention launch as far as the workspace holds the
+ * partial results of all of them: bringing up to four times the query's size makes batches
+ * with cut sequences or chunks faster.  Neither changes a bit: every layer's results are those
+ * of the two calls. */
 int cs_run_layers(const cs_kv_pool* pool, int32_t layer_begin, int32_t layer_end, const cs_batch* batch,
                   const void* q, const void* k_new, const void* v_new, void* out,
                   int64_t q_layer_stride, int64_t kv_layer_stride,

@@ -87,7 +87,22 @@ int validate_batch(const cs_kv_pool* pool, const cs_batch* b) {
     return CS_OK;
 }
 
-DecodePlan plan_decode(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t head_dim, int32_t layers, size_t max_bytes) {
+// Two pages ahead per wavefront need the registers of the third workgroup per CU.  Measured
+// over 33 batch shapes: the deeper queue wins 2-6% once the launch is long enough for the
+// steady state to dominate (from about 0.65 GB of K/V on, ~100 us), and loses 2-7% on
+// smaller launches, where start-up and tail decide and every workgroup slot counts.
+static int32_t pages_ahead_of(const DecodePlan& p, int32_t Hkv, int32_t head_dim, int32_t layers) {
+    const int32_t forced = g_forced_ahead.load();
+    if (forced == 1 || forced == 2) return forced;
+    const int64_t cus = device_cus(), wgs = (int64_t)p.total_items * Hkv * layers;
+    const int64_t kv_bytes = p.decode_keys * 2 * Hkv * head_dim * 2 * layers;
+    // equal items run in rounds over the workgroup slots: between 513 and 768 of them are one
+    // round of three per CU, but a round and a quarter of two per CU
+    if (p.uniform && wgs > 2 * cus && wgs <= 3 * cus) return 1;
+    return kv_bytes >= 650000000ll * cus / 256 ? 2 : 1;
+}
+
+DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim) {
     DecodePlan p = {};
     int32_t max_keys = 0, min_keys = 2147483647;
     for (int32_t s = 0; s < b->num_seqs; ++s) {
@@ -105,6 +120,7 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t head_
     p.split_tokens = 256;
     p.pages_ahead = 1;
     if (p.num_decode == 0) return p;
+    p.uniform = (int64_t)max_keys * 4 <= (int64_t)min_keys * 5;
     const int64_t cus = device_cus();
     int32_t split = g_forced_split.load();
     if (split <= 0) {
@@ -121,15 +137,14 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t head_
         // 3.8% -> 2.3%, worst 61% -> 17%, together with the floor rule below).
         // (the workgroup counts and byte volumes below were measured on 256 CUs and scale with the chip)
         const int32_t cap = head_dim >= 128 ? 4096 : 8192;
-        const bool uniform = (int64_t)max_keys * 4 <= (int64_t)min_keys * 5;
-        const int64_t kv_bytes = p.decode_keys * 2 * Hkv * head_dim * 2 * layers;
-        const int64_t need = uniform ? cus : kv_bytes >= 400000000ll * cus / 256 ? 3 * cus : cus * 3 / 2;
+        const int64_t kv_bytes = p.decode_keys * 2 * Hkv * head_dim * 2;
+        const int64_t need = p.uniform ? cus : kv_bytes >= 400000000ll * cus / 256 ? 3 * cus : cus * 3 / 2;
         auto workgroups_at = [&](int32_t sp) {
             int64_t items = 0;
             for (int32_t s = 0; s < b->num_seqs; ++s)
                 if (b->h_cu_q_lens[s + 1] - b->h_cu_q_lens[s] == 1)
                     items += decode_num_splits(b->h_ctx_lens[s] + 1, sp);
-            return items * Hkv * layers;
+            return items * Hkv;
         };
         // no sequence is cut into more than about 16 pieces: beyond that the partials, their merge
         // and the start-up of ever shorter items cost more than the fuller grid gains -- unless
@@ -140,44 +155,20 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t head_
         for (split = cap; split > floor_split; split /= 2)
             if (workgroups_at(split) >= need) break;
     }
-    // Where the caller has less scratch memory than that takes (several layers in a launch, with the
-    // memory one layer's plan needs), items a quarter longer until it fits, at the latest when nothing is cut: the
-    // layers together then have about as many workgroups as one layer's plan gives one launch.
-    int32_t max_k;
-    for (;;) {
-        p.split_tokens = split;
-        p.total_items = p.num_multi = 0;
-        max_k = 1;
-        for (int32_t s = 0; s < b->num_seqs; ++s) {
-            if (b->h_cu_q_lens[s + 1] - b->h_cu_q_lens[s] != 1) continue;
-            const int32_t k = decode_num_splits(b->h_ctx_lens[s] + 1, split);
-            p.total_items += k;
-            if (k > 1) ++p.num_multi;
-            if (k > max_k) max_k = k;
-        }
-        // whether the list fits the arguments (see below) decides the layout of the workspace
-        p.in_args = p.total_items <= kMaxArgItems && b->num_seqs <= 65536 && max_k <= 255;
-        if (p.num_multi == 0 || g_forced_split.load() > 0 || decode_workspace(p, Hq, Hkv, head_dim, layers).total <= max_bytes) break;
-        split = (int32_t)std::min<int64_t>((split + (int64_t)split / 4 + kPage - 1) & ~(int64_t)(kPage - 1), 1 << 30);
+    p.split_tokens = split;
+    int32_t max_k = 1;
+    for (int32_t s = 0; s < b->num_seqs; ++s) {
+        if (b->h_cu_q_lens[s + 1] - b->h_cu_q_lens[s] != 1) continue;
+        const int32_t k = decode_num_splits(b->h_ctx_lens[s] + 1, split);
+        p.total_items += k;
+        if (k > 1) ++p.num_multi;
+        if (k > max_k) max_k = k;
     }
-    // Two pages ahead per wavefront need the registers of the third workgroup per CU.  Measured
-    // over 33 batch shapes: the deeper queue wins 2-6% once the launch is long enough for the
-    // steady state to dominate (from about 0.65 GB of K/V on, ~100 us), and loses 2-7% on
-    // smaller launches, where start-up and tail decide and every workgroup slot counts.
-    {
-        const int64_t kv_bytes = p.decode_keys * 2 * Hkv * head_dim * 2 * layers;
-        p.pages_ahead = kv_bytes >= 650000000ll * cus / 256 ? 2 : 1;
-        // equal items run in rounds over the workgroup slots: between 513 and 768 of them are one
-        // round of three per CU, but a round and a quarter of two per CU
-        const bool uniform = (int64_t)max_keys * 4 <= (int64_t)min_keys * 5;
-        const int64_t wgs = (int64_t)p.total_items * Hkv * layers;
-        if (uniform && wgs > 2 * cus && wgs <= 3 * cus) p.pages_ahead = 1;
-        const int32_t forced = g_forced_ahead.load();
-        if (forced == 1 || forced == 2) p.pages_ahead = forced;
-    }
+    p.pages_ahead = pages_ahead_of(p, Hkv, head_dim, 1);
     // A list short enough for the argument block is written here, longest items first: the
     // workgroups of a launch start in index order, so the long ones get going at once and
     // the short ones fill in behind them (measured: 7% on 256 sequences of 512..4096 keys).
+    p.in_args = p.total_items <= kMaxArgItems && b->num_seqs <= 65536 && max_k <= 255;
     if (p.in_args) {
         struct Rec { int32_t keys, seq, k; };
         Rec recs[kMaxArgItems];
@@ -198,8 +189,9 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t head_
     return p;
 }
 
-// Host plan of the key-range split (a pure function of the host lengths).
-PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers, size_t max_bytes) {
+// Host plan of the key-range split (a pure function of the host lengths).  The cuts are those of
+// one layer's launch; the order of uncut tiles suits a launch of `layers` layers.
+PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers) {
     PrefillPlan p = {};
     const int32_t G = Hq / Hkv;
     int64_t total_steps = 0, tiles = 0;
@@ -231,18 +223,14 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, 
     p.base_slot = (int32_t)prefill_slot_start(b->h_cu_q_lens[first], first, G);
     // (the slots of the sequences before the first chunk and behind the last one are empty)
     p.num_slots = (int32_t)(prefill_slot_start(b->h_cu_q_lens[last + 1], last + 1, G) - p.base_slot);
-    const int64_t wgs = tiles * Hkv * layers;
-    auto partial_bytes = [&](int ranges) -> size_t {
-        return ranges > 1 ? (size_t)layers * p.num_slots * Hkv * ranges * kTileCols * 16 * (D + 4) * sizeof(float) : 0;
-    };
+    const int64_t wgs = tiles * Hkv;
 
     // The chip: `cus` compute units, two workgroup slots each.  (The counts in the comments below
     // are those of the 256-CU part the rules were measured on.)
     const int64_t cus = device_cus(), slots = 2 * cus;
     if (wgs <= cus * 3 / 4 && max_steps < 128) {
         // few and short tiles: about four workgroups per CU, ranges of at least 32 steps
-        int64_t rs = std::max<int64_t>(32, (total_steps * Hkv * layers + 4 * cus - 1) / (4 * cus));
-        while (rs < max_steps && partial_bytes((int)((max_steps + rs - 1) / rs)) > max_bytes) rs += (rs + 3) / 4;
+        const int64_t rs = std::max<int64_t>(32, (total_steps * Hkv + 4 * cus - 1) / (4 * cus));
         if (rs < max_steps) {
             p.range_steps = (int32_t)rs;
             p.max_ranges = (max_steps + p.range_steps - 1) / p.range_steps;
@@ -274,7 +262,7 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, 
         int best = 1;
         double best_cost = cost(1);
         for (int r = 2; r <= kMaxMergeRanges; ++r) {
-            if (max_steps / r < 32 || partial_bytes(r) > max_bytes) break;
+            if (max_steps / r < 32) break;
             const double c = cost(r);
             if (c < best_cost) { best = r; best_cost = c; }
         }
@@ -294,9 +282,10 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, 
     const int32_t first_round = (int32_t)(cus / Hkv);            // slot positions of the first round (a CU each)
     bool slots_fit = true;                                       // a table entry is 16 bits
     for (int32_t k = 0; k < n_listed; ++k) slots_fit = slots_fit && tile_list[k].slot < 65536;
-    if (p.max_ranges == 1 && wgs > cus) {
+    const int64_t launch_wgs = wgs * layers;
+    if (p.max_ranges == 1 && launch_wgs > cus) {
         const bool listed = tiles == n_listed && slots_fit;
-        if (listed && wgs <= slots && cus % Hkv == 0 && layers == 1) {
+        if (listed && launch_wgs <= slots && cus % Hkv == 0 && layers == 1) {
             std::stable_sort(tile_list, tile_list + n_listed, [](const Tile& a, const Tile& c) { return a.steps > c.steps; });
             const int32_t n_pair = (int32_t)tiles - first_round, n_solo = first_round - n_pair;
             for (int32_t k = 0; k < n_solo; ++k) p.order.slot[n_pair + k] = (uint16_t)tile_list[k].slot;
@@ -305,7 +294,7 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, 
                 p.order.slot[first_round + k] = (uint16_t)tile_list[n_solo + 2 * n_pair - 1 - k].slot;    // short
             }
             p.n_ordered = (int32_t)tiles;
-        } else if (wgs > slots) {
+        } else if (launch_wgs > slots) {
             if (listed) {
                 std::stable_sort(tile_list, tile_list + n_listed, [](const Tile& a, const Tile& c) { return a.steps > c.steps; });
                 for (int32_t k = 0; k < n_listed; ++k) p.order.slot[k] = (uint16_t)tile_list[k].slot;
@@ -314,7 +303,7 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, 
             p.backwards = true;
         }
     }
-    p.bytes = partial_bytes(p.max_ranges);
+    if (p.max_ranges > 1) p.bytes = (size_t)p.num_slots * Hkv * p.max_ranges * kTileCols * 16 * (D + 4) * sizeof(float);
     return p;
 }
 
@@ -418,7 +407,7 @@ static double play_tiles(const std::vector<float>& work, int32_t cus, double dec
 // decode workgroup has left stays empty.  The launch positions from the first such tile on are
 // cut into two or three key ranges, so that the pieces fill both slots; taken when the model
 // promises 6% of the whole call after the cost of the partials (it overrates what cutting gains
-// beside a decode load, so the bar is not lower).
+// beside a decode load, so the bar is not lower).  Only one layer's plan decides on cuts (layers 1).
 static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, PrefillPlan& p, int32_t Hq, int32_t Hkv,
                                      int32_t D, int32_t mode, int32_t layers) {
     FusePlan f = {0, 0, 0};
@@ -579,12 +568,12 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
 }
 
 static FusePlan plan_fusion(const cs_batch* b, const DecodePlan& d, PrefillPlan& p, int32_t Hq, int32_t Hkv,
-                            int32_t D, int32_t mode, int32_t layers) {
-    const FusePlan f = plan_fusion_by_model(b, d, p, Hq, Hkv, D, mode, layers);
+                            int32_t D, int32_t mode) {
+    const FusePlan f = plan_fusion_by_model(b, d, p, Hq, Hkv, D, mode, 1);
     const int32_t forced_whole = g_forced_tail_whole.load(), forced_ranges = g_forced_tail_ranges.load();
     if (forced_whole >= 0 && forced_ranges >= 1 && f.arrangement != 0) {
         // measurement and test knob: cut the launch positions from forced_whole on into forced_ranges
-        p = plan_prefill(b, Hq, Hkv, D, layers, SIZE_MAX);
+        p = plan_prefill(b, Hq, Hkv, D, 1);
         p.n_ordered = 0;
         p.cut_first_pos = std::min(forced_whole, p.num_slots);
         int32_t tail_steps = 1;
@@ -594,7 +583,7 @@ static FusePlan plan_fusion(const cs_batch* b, const DecodePlan& d, PrefillPlan&
         }
         p.range_steps = (tail_steps + forced_ranges - 1) / forced_ranges;
         p.max_ranges = p.cut_first_pos < p.num_slots ? (tail_steps + p.range_steps - 1) / p.range_steps : 1;
-        p.bytes = p.max_ranges > 1 ? (size_t)layers * (p.num_slots - p.cut_first_pos) * Hkv * p.max_ranges * kTileCols * 16 * (D + 4) * sizeof(float) : 0;
+        p.bytes = p.max_ranges > 1 ? (size_t)(p.num_slots - p.cut_first_pos) * Hkv * p.max_ranges * kTileCols * 16 * (D + 4) * sizeof(float) : 0;
     }
     return f;
 }
@@ -674,20 +663,37 @@ extern "C" {
 // measurement knobs.  The workspace query and the attention call of one layer, and the calls of
 // the next layers, ask for the same plan again and again (an item list of up to 880 entries and a
 // sort each time), so each thread remembers the last few it made (an iteration of cs_run_layers asks
-// for up to five: the whole batch and its online prefix, each for one layer and for several in one
+// for up to six: the whole batch and its online prefix, each for one layer, for several in one
 // launch, and for the layers left over), keyed by everything the plan depends on, the lengths
 // compared value by value.
 struct PlanMemo {
     bool valid = false;
     int32_t S = 0, T = 0, Hq = 0, Hkv = 0, D = 0, layers = 0, split = 0, ahead = 0, cus = 0, fuse = 0, tail_whole = -1, tail_ranges = 0;
-    size_t max_bytes = 0;
     std::vector<int32_t> ctx, cu;
     Plans plans;
 };
 }  // extern "C"
 
 namespace cs {
-const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers, size_t max_bytes) {
+// One layer's plan.
+static void plan_layer(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t fuse, Plans& plans) {
+    plans.d = plan_decode(b, Hkv, D);
+    plans.p = plans.d.num_prefill ? plan_prefill(b, Hq, Hkv, D, 1) : PrefillPlan{};
+    plans.f = plan_fusion(b, plans.d, plans.p, Hq, Hkv, D, fuse);
+}
+
+// One launch for several layers: `plans` is one layer's and keeps its cuts, so that every layer's
+// results are those of a launch of its own; only what does not touch them is chosen anew for the
+// larger grid.
+static void plan_for_layers(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t fuse, int32_t layers, Plans& plans) {
+    if (plans.d.num_decode > 0) plans.d.pages_ahead = pages_ahead_of(plans.d, Hkv, D, layers);
+    if (plans.d.num_prefill > 0 && plans.p.max_ranges == 1) plans.p = plan_prefill(b, Hq, Hkv, D, layers);
+    // (tiles cut from a launch position on stay in the order that the position counts in)
+    if (plans.p.cut_first_pos == 0) plans.f = plan_fusion_by_model(b, plans.d, plans.p, Hq, Hkv, D, fuse, layers);
+    plans.p.bytes *= layers;
+}
+
+const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers) {
     constexpr int kMemos = 6;
     static thread_local PlanMemo memo[kMemos];
     static thread_local int next = 0;
@@ -695,23 +701,30 @@ const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, in
     const int32_t fuse = g_fuse_mixed.load(), tail_whole = g_forced_tail_whole.load(), tail_ranges = g_forced_tail_ranges.load();
     for (PlanMemo& m : memo)
         if (m.valid && m.fuse == fuse && m.tail_whole == tail_whole && m.tail_ranges == tail_ranges && m.S == S && m.T == b->num_tokens && m.Hq == Hq && m.Hkv == Hkv && m.D == D &&
-            m.layers == layers && m.max_bytes == max_bytes && m.split == split && m.ahead == ahead && m.cus == cus &&
+            m.layers == layers && m.split == split && m.ahead == ahead && m.cus == cus &&
             memcmp(m.ctx.data(), b->h_ctx_lens, sizeof(int32_t) * S) == 0 && memcmp(m.cu.data(), b->h_cu_q_lens, sizeof(int32_t) * (S + 1)) == 0)
             return m.plans;
+    Plans plans;
+    if (layers > 1) plans = plans_for(b, Hq, Hkv, D, 1);
+    else plan_layer(b, Hq, Hkv, D, fuse, plans);
+    if (layers > 1) plan_for_layers(b, Hq, Hkv, D, fuse, layers, plans);
+    plans.d.merges_in_place = decode_merges_in_place(plans.d, plans.p, plans.f, Hkv, D, layers);
+    plans.decode_bytes = decode_workspace(plans.d, Hq, Hkv, D, layers).total;
+    plans.need = plans.decode_bytes + plans.p.bytes;
     PlanMemo& m = memo[next];
     next = (next + 1) % kMemos;
     m.valid = false;
-    m.S = S; m.T = b->num_tokens; m.Hq = Hq; m.Hkv = Hkv; m.D = D; m.layers = layers; m.max_bytes = max_bytes; m.split = split; m.ahead = ahead; m.cus = cus; m.fuse = fuse; m.tail_whole = tail_whole; m.tail_ranges = tail_ranges;
+    m.S = S; m.T = b->num_tokens; m.Hq = Hq; m.Hkv = Hkv; m.D = D; m.layers = layers; m.split = split; m.ahead = ahead; m.cus = cus; m.fuse = fuse; m.tail_whole = tail_whole; m.tail_ranges = tail_ranges;
     m.ctx.assign(b->h_ctx_lens, b->h_ctx_lens + S);
     m.cu.assign(b->h_cu_q_lens, b->h_cu_q_lens + S + 1);
-    m.plans.p = plan_prefill(b, Hq, Hkv, D, layers, max_bytes);
-    m.plans.d = plan_decode(b, Hq, Hkv, D, layers, max_bytes - m.plans.p.bytes);
-    m.plans.f = plan_fusion(b, m.plans.d, m.plans.p, Hq, Hkv, D, fuse, layers);
-    m.plans.d.merges_in_place = decode_merges_in_place(m.plans.d, m.plans.p, m.plans.f, Hkv, D, layers);
-    m.plans.decode_bytes = decode_workspace(m.plans.d, Hq, Hkv, D, layers).total;
-    m.plans.need = m.plans.decode_bytes + m.plans.p.bytes;
+    m.plans = plans;
     m.valid = true;
     return m.plans;
+}
+
+size_t workspace_for_layers(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers) {
+    const Plans& one = plans_for(b, Hq, Hkv, D, 1);
+    return decode_workspace(one.d, Hq, Hkv, D, layers).total + one.p.bytes * layers;
 }
 }  // namespace cs
 
@@ -913,7 +926,7 @@ int32_t cs_debug_decode_items(const cs_batch* batch, int32_t Hkv, int32_t D, uin
                               int32_t* split_tokens) {
     if (!shape_supported(Hkv, D) || validate_batch(nullptr, batch) != CS_OK || capacity < 0 || (capacity > 0 && !items))
         return CS_ERR_INVALID_ARG;
-    const DecodePlan p = plan_decode(batch, Hkv, Hkv, D, 1, SIZE_MAX);
+    const DecodePlan p = plan_decode(batch, Hkv, D);
     if (split_tokens) *split_tokens = p.split_tokens;
     if (!p.in_args) return -1000000 - p.total_items;       // the planning kernel would build the list
     for (int32_t i = 0; i < p.total_items && i < capacity; ++i) items[i] = p.arg_items.e[i];
@@ -922,7 +935,7 @@ int32_t cs_debug_decode_items(const cs_batch* batch, int32_t Hkv, int32_t D, uin
 
 int32_t cs_debug_decode_pages_ahead(const cs_batch* batch, int32_t Hkv, int32_t D) {
     if (!shape_supported(Hkv, D) || validate_batch(nullptr, batch) != CS_OK) return CS_ERR_INVALID_ARG;
-    return plan_decode(batch, Hkv, Hkv, D, 1, SIZE_MAX).pages_ahead;
+    return plan_decode(batch, Hkv, D).pages_ahead;
 }
 
 int32_t cs_debug_prefill_order(const cs_batch* batch, int32_t Hq, int32_t Hkv, int32_t D, int32_t* slots, int32_t capacity) {
@@ -930,7 +943,7 @@ int32_t cs_debug_prefill_order(const cs_batch* batch, int32_t Hq, int32_t Hkv, i
         (capacity > 0 && !slots))
         return CS_ERR_INVALID_ARG;
     if (batch->num_seqs == 0) return 0;
-    const PrefillPlan p = plan_prefill(batch, Hq, Hkv, D, 1, SIZE_MAX);
+    const PrefillPlan p = plan_prefill(batch, Hq, Hkv, D, 1);
     for (int32_t i = 0; i < p.n_ordered && i < capacity; ++i) slots[i] = p.order.slot[i];
     return p.n_ordered;
 }

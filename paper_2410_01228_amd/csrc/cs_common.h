@@ -76,14 +76,13 @@ struct DecodePlan {
     int32_t total_items;       // sum over decode sequences of their split count
     int32_t num_multi;         // decode sequences cut into more than one item
     int64_t decode_keys;       // total keys read by decode sequences
+    bool    uniform;           // their lengths lie within 25% of each other
     int32_t pages_ahead;       // pages a wavefront of the decode kernel prefetches (1 or 2)
     bool    in_args;           // the item list below is valid and replaces the planning kernel
     bool    merges_in_place;   // the workgroups merge the cut sequences themselves, no kernel follows
     ItemsInArgs arg_items;     // total_items words
 };
-// layers: how many layers one launch holds (the grid is that many times as large).  max_bytes: the
-// workspace there is for it.
-DecodePlan plan_decode(const cs_batch* batch, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim, int32_t layers, size_t max_bytes);
+DecodePlan plan_decode(const cs_batch* batch, int32_t num_kv_heads, int32_t head_dim);
 // Workspace layout (all 16-byte aligned): announcements of the partials (item list in the kernel
 // arguments: 8 bytes per item and kv head, cs_arrive.h) or the item list | partial (max, sum) |
 // partial outputs.  All zero when nothing is cut.
@@ -134,7 +133,7 @@ struct PrefillPlan {
     int32_t num_slots;         // slots from base_slot on: the grid's extent; partials are indexed by slot - base_slot
     size_t  bytes;             // workspace for the partials (0 when nothing is cut)
 };
-PrefillPlan plan_prefill(const cs_batch* batch, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim, int32_t layers, size_t max_bytes);
+PrefillPlan plan_prefill(const cs_batch* batch, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim, int32_t layers);
 int launch_prefill(const cs_kv_pool& pool, int32_t layer, const cs_batch& b, const PrefillPlan& plan,
                    const void* q, void* out, int32_t Hq, float scale, void* workspace, hipStream_t st, bool f16);
 // One launch for a batch that holds both chunks and decode tokens.  persistent_wgs == 0: the

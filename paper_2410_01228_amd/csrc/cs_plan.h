@@ -23,8 +23,12 @@ struct Plans {
 };
 
 // The plan of a batch for launches of `layers` layers each (remembered per thread; the reference is
-// good until the thread asks for six more).  max_bytes: the workspace there is; cuts are chosen so that they fit it.
-const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers = 1, size_t max_bytes = SIZE_MAX);
+// good until the thread asks for six more).  Sequences and tiles are cut as for one layer, whatever
+// `layers` is: how many layers share a launch changes no bit of their results.
+const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers = 1);
+
+// The workspace a launch of `layers` layers needs: plans_for(..., layers).need without making that plan.
+size_t workspace_for_layers(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers);
 
 int attention_shape_ok(int32_t Hq, int32_t Hkv, int32_t D);
 

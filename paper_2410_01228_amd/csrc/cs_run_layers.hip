@@ -6,11 +6,10 @@
 using namespace cs;
 
 // Between two safepoints the batch cannot change and the caller has all layers' inputs in place, so up
-// to this many layers go into one append launch and one attention launch.  A small step's layer
-// is mostly start-up, tail and the gaps between its launches; four of them in one grid also fill the
-// chip without cutting sequences (24 decodes of 200-3000 keys + a 200-token chunk, 32/8 heads:
-// 47 -> 31 us a layer).  Four is the paper's distance between safepoints: with one at every fourth
-// layer or none at all the launches, and so the bits of the results, are the same.
+// to this many layers go into one append launch, and into one attention launch where the workspace
+// holds the partial results of all of them.  A small step's layer is mostly start-up, tail and the
+// gaps between its launches.  Every layer is cut as in a launch of its own, so its results are, bit for
+// bit, those of cs_kv_append + cs_paged_attention_mixed, whatever shares its launch.
 constexpr int32_t kLayersPerLaunch = 4;
 
 // Whether the layers' tensors can be worked on in any order: every layer has an output of its own,
@@ -29,29 +28,21 @@ static bool layers_are_apart(const cs_batch& b, int32_t layers, const void* q, c
            clear_of_out(v_new, kv_stride, kv_elems);
 }
 
-// Append and attention of layers [l, l + n) in one launch each.  The caller must bring what one layer's
-// plan needs; the plan for n layers cuts sequences and tiles only as finely as fits that memory, which
-// still leaves as many workgroups as one layer has alone (taking fewer layers instead, each cut finely:
-// 8 decodes of 736-2765 keys, 28/4 heads, 28 layers 536 -> 269 us; 11 of 212-630 keys, 48 layers
-// (40/8), 843 -> 307 us; 25 drawn iterations 1.21x in the geometric mean, the slowest 0.99x).
-// CS_ERR_WORKSPACE_TOO_SMALL, nothing enqueued, where a forced plan needs more than there is.
-static int layers_in_one_launch(const cs_kv_pool& pool, int32_t l, int32_t n, const cs_batch& b, const void* q, const void* k_new,
-                                const void* v_new, void* out, int64_t q_stride, int64_t kv_stride, int32_t Hq, float scale,
-                                void* workspace, size_t workspace_bytes, hipStream_t st, bool f16) {
-    const Plans& plans = plans_for(&b, Hq, pool.num_kv_heads, pool.head_dim, n, workspace_bytes);
-    if (plans.need > workspace_bytes) return CS_ERR_WORKSPACE_TOO_SMALL;
-    const LayerSpan span = {n, pool.layer_stride, q_stride, kv_stride};
-    int rc = launch_append_layers(pool, l, span, b, k_new, v_new, st);
-    if (rc) return rc;
+// Attention of layers [l, l + n) in one launch; the workspace holds what it needs
+// (workspace_for_layers).
+static int attention_of_layers(const cs_kv_pool& pool, int32_t l, int32_t n, const cs_batch& b, const void* q, void* out,
+                               int64_t q_stride, int32_t Hq, float scale, void* workspace, hipStream_t st, bool f16) {
+    const Plans& plans = plans_for(&b, Hq, pool.num_kv_heads, pool.head_dim, n);
+    const LayerSpan span = {n, pool.layer_stride, q_stride, 0};
     void* prefill_ws = (char*)workspace + plans.decode_bytes;
     if (plans.f.arrangement != 0) {
-        rc = launch_mixed_layers(pool, l, span, b, plans.d, plans.p, q, out, Hq, scale, workspace, prefill_ws, st, f16, plans.f.prio,
-                                 plans.f.arrangement == 2 ? plans.f.persistent_wgs : 0);
+        const int rc = launch_mixed_layers(pool, l, span, b, plans.d, plans.p, q, out, Hq, scale, workspace, prefill_ws, st, f16,
+                                           plans.f.prio, plans.f.arrangement == 2 ? plans.f.persistent_wgs : 0);
         if (rc || plans.d.num_multi == 0 || plans.d.merges_in_place) return rc;
         return launch_decode_layers(pool, l, span, b, plans.d, q, out, Hq, scale, workspace, st, f16, true);
     }
     if (plans.d.num_prefill > 0) {
-        rc = launch_prefill_layers(pool, l, span, b, plans.p, q, out, Hq, scale, prefill_ws, st, f16);
+        const int rc = launch_prefill_layers(pool, l, span, b, plans.p, q, out, Hq, scale, prefill_ws, st, f16);
         if (rc) return rc;
     }
     return launch_decode_layers(pool, l, span, b, plans.d, q, out, Hq, scale, workspace, st, f16, false);
@@ -103,29 +94,29 @@ static int run_layers(const cs_kv_pool* pool, int32_t l0, int32_t l1, const cs_b
                 if (preempted_before_layer) *preempted_before_layer = l;
             }
         }
-        const int64_t i = l - l0;
-        const uint16_t* ql = (const uint16_t*)q + i * q_stride;
-        const uint16_t* kl = (const uint16_t*)k_new + i * kv_stride;
-        const uint16_t* vl = (const uint16_t*)v_new + i * kv_stride;
-        uint16_t* ol = (uint16_t*)out + i * q_stride;
-        // the layers up to the next safepoint, or as many as the workspace allows
+        auto q_of = [&](const void* base, int32_t layer) { return (uint16_t*)base + (int64_t)(layer - l0) * q_stride; };
+        auto kv_of = [&](const void* base, int32_t layer) { return (const uint16_t*)base + (int64_t)(layer - l0) * kv_stride; };
         int32_t n = apart ? std::min(kLayersPerLaunch, l1 - l) : 1;
         if (sp && !preempted) n = std::min(n, sp->check_every - (l - l0) % sp->check_every);
-        for (; n > 1; n /= 2) {
-            rc = cur.num_tokens == 0 ? CS_OK
-                : layers_in_one_launch(*pool, l, n, cur, ql, kl, vl, ol, q_stride, kv_stride, Hq, scale, workspace, workspace_bytes,
-                                       (hipStream_t)stream, f16);
-            if (rc == CS_OK) break;
-            if (rc != CS_ERR_WORKSPACE_TOO_SMALL) return rc;
+        if (n > 1 && cur.num_tokens == 0) {
+            l += n;
+            continue;
         }
-        if (n <= 1) {
-            n = 1;
-            rc = cs_kv_append(pool, l, &cur, kl, vl, stream);
-            if (rc) return rc;
-            rc = attention_mixed(pool, l, &cur, ql, ol, Hq, scale, workspace, workspace_bytes, stream, f16);
+        if (n > 1) {
+            const LayerSpan span = {n, pool->layer_stride, q_stride, kv_stride};
+            rc = launch_append_layers(*pool, l, span, cur, kv_of(k_new, l), kv_of(v_new, l), (hipStream_t)stream);
+        } else {
+            rc = cs_kv_append(pool, l, &cur, kv_of(k_new, l), kv_of(v_new, l), stream);
+        }
+        if (rc) return rc;
+        // their attention, as many of them at a time as the workspace has room for
+        for (const int32_t end = l + n; l < end; l += n) {
+            n = end - l;
+            while (n > 1 && workspace_for_layers(&cur, Hq, pool->num_kv_heads, pool->head_dim, n) > workspace_bytes) --n;
+            rc = n > 1 ? attention_of_layers(*pool, l, n, cur, q_of(q, l), q_of(out, l), q_stride, Hq, scale, workspace, (hipStream_t)stream, f16)
+                       : attention_mixed(pool, l, &cur, q_of(q, l), q_of(out, l), Hq, scale, workspace, workspace_bytes, stream, f16);
             if (rc) return rc;
         }
-        l += n;
     }
     return CS_OK;
 }

@@ -65,6 +65,32 @@ def test_layers_in_one_launch_match_single_calls(sh, ctx, ql, L, every):
         assert torch.equal(pool.tensor.view(torch.int16), twin.tensor.view(torch.int16))
 
 
+# the same shapes and a many-piece batch: every grouping that safepoints, a remainder and the workspace lead
+# to, against the single calls, bit for bit
+@pytest.mark.parametrize("sh,ctx,ql", [
+    (synth.Shape(8, 2, 128), [5000, 17, 300], [1, 1, 1]),
+    (synth.Shape(28, 4, 128), [6000, 100], [40, 33]),
+    (synth.Shape(32, 8, 128), [700, 0], [300, 900]),
+    (synth.Shape(32, 8, 128), [900, 2500, 31, 400], [1, 1, 1, 200]),
+    (synth.Shape(16, 4, 128), [2500, 0, 0, 0], [512, 512, 512, 512]),      # whole alone, but several layers' grid would like cuts
+    (synth.Shape(64, 8, 128), [8651, 3000, 12160], [1, 1, 22]),
+    (synth.Shape(8, 2, 64), [90, 0, 1200], [1, 50, 1])])
+def test_how_layers_are_grouped_changes_no_bit(sh, ctx, ql):
+    L = 7
+    b, bb, pool, q, k, v = setup(sh, ctx, ql, L, 320)
+    want = layer_by_layer(sh, bb, cs.Pool(pool.tensor.clone(), L, b.num_pages, sh.Hkv, sh.D), q, k, v)
+    need = cs.cs_run_layers_workspace_bytes(bb, 1, sh.Hq, sh.Hkv, sh.D)
+    flag = ctypes.c_int32(0)
+    for size in (need, 2 * need, 3 * need, 4 * need):
+        ws = torch.empty(max(16, size), dtype=torch.uint8, device="cuda")
+        for every in (None, 1, 3, 4):
+            sp = cs.cs_safepoint(ctypes.addressof(flag), cs.POLL_FN(0), None, every, 1, 0) if every else None
+            out = torch.full_like(q, float("nan"))
+            cs.cs_run_layers(pool, 0, L, bb, q, k, v, out, sh.Hq, sh.scale, ws, sp)
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(torch.int16), want.view(torch.int16)), (size, every)
+
+
 def test_layers_that_share_or_chain_their_tensors_run_one_after_the_other():
     sh, L = synth.Shape(8, 2, 128), 4
     b, bb, pool, q, k, v = setup(sh, [500, 60, 33], [1, 20, 1], L, 311)
