@@ -245,8 +245,8 @@ struct DecodePartials {
 };
 
 // Merge of the n_splits partials of one (cut sequence, kv head), by one workgroup: a lane per (head,
-// 4 features), up to 8 pieces' loads in flight at once.  o0, ml0: the partials of the first item's
-// first head of the group; piece i lies i * Hq rows further on.
+// 4 features), up to 8 pieces' loads in flight at once.  Every piece is weighted against the maximum
+// of all of them, in the order of the pieces: with more than 8 the maxima are read twice.
 template <int D, class E>
 __device__ __forceinline__ void merge_pieces(const DecodePartials& part, int32_t first_item, int32_t n_splits, int32_t Hq,
                                              int32_t g, int32_t G, uint16_t* __restrict__ out_row)
@@ -259,6 +259,13 @@ __device__ __forceinline__ void merge_pieces(const DecodePartials& part, int32_t
         const int head = idx / kQuads, quad = idx - head * kQuads;
         float M = -INFINITY, L = 0.f;
         f32x4 O = {0.f, 0.f, 0.f, 0.f};
+        for (int32_t i0 = 0; n_splits > 8 && i0 < n_splits; i0 += 8) {
+            a_u32x2 ml[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) ml[j] = pm.load2(((uint32_t)min(i0 + j, n_splits - 1) * Hq + head) * 8);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) M = fmaxf(M, as_float(ml[j][0]));
+        }
         for (int32_t i0 = 0; i0 < n_splits; i0 += 8) {
             a_u32x2 ml[8];
             a_u32x4 o[8];
@@ -268,21 +275,18 @@ __device__ __forceinline__ void merge_pieces(const DecodePartials& part, int32_t
                 ml[j] = pm.load2(row * 8);
                 o[j] = po.load4(row * (D * 4) + quad * 16);
             }
-            float M_new = M;
+            if (n_splits <= 8) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j) M_new = fmaxf(M_new, as_float(ml[j][0]));
-            const float keep = M == -INFINITY ? 0.f : exp2f(M - M_new);
-            L *= keep;
-            O *= keep;
+                for (int j = 0; j < 8; ++j) M = fmaxf(M, as_float(ml[j][0]));
+            }
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 if (i0 + j >= n_splits) break;                             // (not a weight of zero: an infinity in V stays one)
                 const float m = as_float(ml[j][0]);
-                const float f = m == -INFINITY ? 0.f : exp2f(m - M_new);                          // a piece without keys
+                const float f = m == -INFINITY ? 0.f : exp2f(m - M);                              // a piece without keys
                 L += as_float(ml[j][1]) * f;
                 O += __builtin_bit_cast(f32x4, o[j]) * f;
             }
-            M = M_new;
         }
         u32x2 w = {0u, 0u};
         if (L > 0.f) w = u32x2{ E::pack(O[0] / L, O[1] / L), E::pack(O[2] / L, O[3] / L) };

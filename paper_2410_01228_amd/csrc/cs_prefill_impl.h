@@ -595,24 +595,34 @@ __device__ __forceinline__ void prefill_tile(
                 __syncthreads();
                 if (!lds.last) return;
             }
-            // in the order of the ranges, whichever of them this is
+            // every range weighted against the maximum of all, in the order of the ranges, whichever of
+            // them this is (fused multiply-adds, as a loop over all ranges in memory would be); exp2f, not the
+            // bare instruction: a range 2^126 and more below it still counts where the others have nothing
             f32x4 sum[kNCT][D / 16];
             float M[kNCT], L[kNCT];
 #pragma unroll
             for (int c = 0; c < kNCT; ++c) {
-                M[c] = kNoMax;
+                M[c] = fmaxf(kNoMax, m_run[c]);
                 L[c] = 0.f;
 #pragma unroll
                 for (int dt = 0; dt < D / 16; ++dt) sum[c][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
             auto add = [&](int c, float m, float l, const f32x4 (&v)[D / 16]) {
-                const float M_new = fmaxf(M[c], m);
-                const float keep = __builtin_amdgcn_exp2f(M[c] - M_new), f = __builtin_amdgcn_exp2f(m - M_new);
-                M[c] = M_new;
-                L[c] = L[c] * keep + l * f;
+                const float f = exp2f(m - M[c]);                 // 0 for a range the row sees nothing of
+                L[c] = __builtin_fmaf(l, f, L[c]);
 #pragma unroll
-                for (int dt = 0; dt < D / 16; ++dt) sum[c][dt] = sum[c][dt] * keep + v[dt] * f;
+                for (int dt = 0; dt < D / 16; ++dt)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum[c][dt][e] = __builtin_fmaf(v[dt][e], f, sum[c][dt][e]);
             };
+            auto row_of = [&](int r, int c) -> uint32_t {
+                return (uint32_t)r * kRangeBytes + ((wave * kNCT + c) * 16 + (lane & 15)) * (kPartRow * 4);
+            };
+            for (int r = 0; r < n_ranges; ++r) {
+                if (r == range) continue;
+#pragma unroll
+                for (int c = 0; c < kNCT; ++c) M[c] = fmaxf(M[c], as_float(part.load2(row_of(r, c) + D * 4)[0]));
+            }
             for (int r = 0; r < n_ranges; ++r) {
                 if (r == range) {
 #pragma unroll
@@ -622,7 +632,7 @@ __device__ __forceinline__ void prefill_tile(
                     f32x4 v[kNCT][D / 16];
 #pragma unroll
                     for (int c = 0; c < kNCT; ++c) {
-                        const uint32_t row = (uint32_t)r * kRangeBytes + ((wave * kNCT + c) * 16 + (lane & 15)) * (kPartRow * 4);
+                        const uint32_t row = row_of(r, c);
                         ml[c] = part.load2(row + D * 4);
 #pragma unroll
                         for (int dt = 0; dt < D / 16; ++dt)

@@ -76,3 +76,75 @@ def test_an_infinity_in_v_stays_one_through_the_merge(ctx, cus):
     assert (out[0, 4:, 77] == float("inf")).all()
     out[0, 4:, 77] = torch.from_numpy(want[0, 4:, 77]).to(out)
     assert_attention_close(out, want, "finite features")
+
+
+@pytest.mark.parametrize("cus", [256, 2])               # merged in place, and by a kernel
+def test_every_piece_is_weighted_against_the_maximum_of_all(cus):
+    """The merge's own arithmetic, redone in torch from the partials that the call leaves in its
+    workspace: weights 2^(m - M) with the maximum M of ALL pieces, the sums as fused multiply-adds in
+    the order of the pieces (also beyond the eight that are loaded together), one division.  The
+    fused multiply-add is taken in 64 bits and rounded to 32, which the rounding to fp16 (the finer of the two types) does not see."""
+    sh, split = synth.Shape(32, 8, 128), 16
+    ctx = [16 * 9 - 1 + 5 * s for s in range(40)]       # 9 to 21 pieces
+    b = synth.make_batch(sh, ctx, [1] * len(ctx), synth.generator(99))
+    st = Step(b, 99, q_gain=3.0, dtype=torch.float16)
+    pool = cs.Pool(from_bits(st.prior_pool(), "cuda", torch.float16), 1, b.num_pages, sh.Hkv, sh.D)
+    bb = cs.Batch(b.block_tables, b.ctx_lens, b.cu_q_lens)
+    cs.cs_kv_append(pool, 0, bb, st.k_new.cuda(), st.v_new.cuda())
+    out = torch.full((b.T, sh.Hq, sh.D), float("nan"), dtype=torch.float16, device="cuda")
+    cs.cs_set_decode_split_tokens(split)
+    try:
+        cs.cs_debug_set_cu_count(cus)
+        items, n, _ = cs.cs_debug_decode_items(bb, sh.Hkv, sh.D)
+        ws = torch.empty(cs.cs_paged_attention_workspace_bytes(bb, sh.Hq, sh.Hkv, sh.D), dtype=torch.uint8, device="cuda")
+        cs.cs_paged_attention_mixed_f16(pool, 0, bb, st.q.cuda(), out, sh.Hq, sh.scale, ws)
+        torch.cuda.synchronize()
+    finally:
+        cs.cs_set_decode_split_tokens(0)
+        cs.cs_debug_set_cu_count(0)
+    f = ws.view(torch.float32)                          # ... | (max, sum) of every item | outputs of every item
+    o = f[-n * sh.Hq * sh.D:].view(n, sh.Hq, sh.D)
+    ml = f[-n * sh.Hq * (sh.D + 2):-n * sh.Hq * sh.D].view(n, sh.Hq, 2)
+    at = 0
+    while at < n:
+        s, _, k = items[at]
+        assert k > 8
+        M = ml[at:at + k, :, 0].amax(0)
+        L, O = torch.zeros_like(M), torch.zeros_like(o[0])
+        for i in range(at, at + k):
+            w = torch.exp2(ml[i, :, 0] - M)
+            L = (ml[i, :, 1].double() * w.double() + L.double()).float()
+            O = (o[i].double() * w.double()[:, None] + O.double()).float()
+        assert torch.equal(out[s].view(torch.int16), (O / L[:, None]).half().view(torch.int16))
+        at += k
+
+
+def test_a_tile_range_far_below_the_others_still_counts():
+    """A chunk whose tiles are cut in two ranges: the keys of the first score about 130 octaves below those
+    of the second, and only the first range's first key has a value, 2^127, in one feature.  What is
+    left of it after the softmax, 2^127 * 2^-130.6 / (keys of the second range), is an ordinary number."""
+    sh, C, P, low = synth.Shape(32, 8, 128), 2000, 40, 1024
+    b = synth.make_batch(sh, [C], [P], synth.generator(5))
+    st = Step(b, 5)
+    bb = cs.Batch(b.block_tables, b.ctx_lens, b.cu_q_lens)
+    _, first, ranges = cs.cs_debug_mixed_tail_cut(bb, sh.Hq, sh.Hkv, sh.D)
+    assert first == 0 and ranges == 2 and (C + P + 63) // 64 * 32 == low   # (so the first range ends at key 1024)
+    pool = cs.Pool(torch.zeros_like(from_bits(st.prior_pool(), "cuda")), 1, b.num_pages, sh.Hkv, sh.D)
+    prior = cs.Batch(b.block_tables, torch.zeros(1, dtype=torch.int32), torch.tensor([0, C], dtype=torch.int32))
+    k = torch.zeros((C + P, sh.Hkv, sh.D), dtype=torch.bfloat16, device="cuda")
+    v = torch.zeros_like(k)
+    k[low:, :, 0] = 32.0
+    v[0, :, 5] = 2.0 ** 127
+    cs.cs_kv_append(pool, 0, prior, k[:C].contiguous(), v[:C].contiguous())
+    cs.cs_kv_append(pool, 0, bb, k[C:].contiguous(), v[C:].contiguous())
+    q = torch.zeros((P, sh.Hq, sh.D), dtype=torch.bfloat16, device="cuda")
+    q[:, :, 0] = 32.0
+    out = torch.full_like(q, float("nan"))
+    cs.cs_paged_attention_mixed(pool, 0, bb, q, out, sh.Hq, sh.scale, cs.workspace_for(bb, sh.Hq, sh.Hkv, sh.D))
+    torch.cuda.synchronize()
+    high = torch.arange(C + 1 - low, C + P + 1 - low, dtype=torch.float64)            # keys of the second range that row t sees
+    want = 2.0 ** 127 * torch.exp(torch.tensor(-32.0 * 32.0 * sh.scale, dtype=torch.float64)) / high
+    got = out[:, :, 5].double().cpu()
+    # the weight is a denormal of 19 bits, the exponent -130.6 has 2^-17 of an octave; the output is bf16
+    assert (got / want[:, None] - 1).abs().max() <= 2.0 ** -8
+    assert (out[:, :, :5] == 0).all() and (out[:, :, 6:] == 0).all()
