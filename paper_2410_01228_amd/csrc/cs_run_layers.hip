@@ -29,7 +29,8 @@ static bool layers_are_apart(const cs_batch& b, int32_t layers, const void* q, c
 }
 
 // Attention of layers [l, l + n) in one launch; the workspace holds what it needs
-// (workspace_for_layers).
+// (workspace_for_layers), and its pointer has been checked if that is anything: several layers need
+// memory only where one does.
 static int attention_of_layers(const cs_kv_pool& pool, int32_t l, int32_t n, const cs_batch& b, const void* q, void* out,
                                int64_t q_stride, int32_t Hq, float scale, void* workspace, hipStream_t st, bool f16) {
     const Plans& plans = plans_for(&b, Hq, pool.num_kv_heads, pool.head_dim, n);

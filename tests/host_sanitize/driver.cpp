@@ -1,6 +1,8 @@
 // Host-side exercise of libconserve_kv under AddressSanitizer / UndefinedBehaviorSanitizer.
-// Everything here returns before a kernel launch: the page map, the launch-plan queries and the
-// argument checks.  Device pointers are fakes that are never dereferenced on the host.
+// The page map, the launch-plan queries and the argument checks return before a kernel launch; the
+// iterations over layers go through to stand-ins of the launchers, which hold what each launch
+// would use against the workspace of the call.  Device pointers are fakes that are never
+// dereferenced on the host.
 // Prints "ok <count>" and exits 0; any sanitizer report makes the process exit non-zero.
 #include <cstdint>
 #include <cstdio>
@@ -9,6 +11,7 @@
 #include <random>
 #include <vector>
 #include "conserve_kv.h"
+#include "launch_window.h"
 
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "check failed line %d: %s\n", __LINE__, #c); std::exit(3); } } while (0)
 
@@ -23,6 +26,23 @@ static cs_batch make_batch(const std::vector<int32_t>& ctx, const std::vector<in
     b.h_ctx_lens = ctx.data();
     b.h_cu_q_lens = cu.data();
     return b;
+}
+
+// One iteration over `layers` layers, not preempted, through the stand-ins.
+static int iterate(const cs_batch& b, const int* sh, int32_t layers, const void* workspace, size_t bytes, int32_t check_every) {
+    cs_kv_pool pool = {(void*)0x100000, layers, 1 << 22, 16, sh[1], sh[2], 0, 0};
+    pool.page_stride = 2ll * sh[1] * pool.page_size * sh[2];
+    pool.layer_stride = pool.page_stride * pool.num_pages;
+    const int32_t flag = 0;
+    const cs_safepoint sp = {&flag, nullptr, nullptr, check_every, b.num_seqs / 2, 0};
+    const int64_t q_elems = (int64_t)b.num_tokens * sh[0] * sh[2], kv_elems = (int64_t)b.num_tokens * sh[1] * sh[2];
+    g_window = LaunchWindow{true, workspace, bytes, 0, 0, 0};
+    int32_t first = 7;
+    const int rc = cs_run_layers(&pool, 0, layers, &b, (void*)(1ll << 44), (void*)(2ll << 44), (void*)(3ll << 44), (void*)(4ll << 44),
+                                 q_elems, kv_elems, sh[0], 0.1f, (void*)workspace, bytes, check_every > 0 ? &sp : nullptr, &first, nullptr);
+    g_window.open = false;
+    CHECK(rc != CS_OK || first == -1);
+    return rc;
 }
 
 int main() {
@@ -78,7 +98,45 @@ int main() {
                                                     need - 1, nullptr);
             CHECK(rc == CS_ERR_WORKSPACE_TOO_SMALL || rc == CS_ERR_INVALID_ARG);
         }
+        // an iteration of several layers, with the least workspace the call accepts and with more
+        if (S <= 300 && b.num_tokens > 0) {
+            const int32_t layers = 1 + (int32_t)(rng() % 9), every = (int32_t)(rng() % 5);
+            const size_t least = std::max(need, cs_run_layers_workspace_bytes(&b, S / 2, sh[0], sh[1], sh[2]));
+            bool decodes = false, chunks = false;
+            for (int s = 0; s < S; ++s) { decodes |= cu[s + 1] - cu[s] == 1; chunks |= cu[s + 1] - cu[s] > 1; }
+            for (const size_t bytes : {least, 2 * least, 4 * least + 64}) {
+                CHECK(iterate(b, sh, layers, (void*)0x70000, bytes, every) == CS_OK);
+                CHECK(g_window.layers_appended == layers && g_window.layers_decoded == (decodes ? layers : 0) &&
+                      g_window.layers_prefilled == (chunks ? layers : 0));
+            }
+            // a pointer that the call has no reason to look at must not be used, whatever size comes with it
+            if (least == 0) {
+                CHECK(iterate(b, sh, layers, nullptr, (size_t)1 << 30, every) == CS_OK);
+                CHECK(iterate(b, sh, layers, (void*)0x70001, (size_t)1 << 30, every) == CS_OK);
+            }
+        }
         checks += 8;
+    }
+    // batches that need no workspace layer by layer, but whose larger grids would gain from cuts
+    {
+        struct Case { int sh[3]; std::vector<int32_t> ctx, q; };
+        const Case cases[] = {{{16, 4, 128}, {2500, 0, 0, 0}, {512, 512, 512, 512}},
+                              {{64, 8, 128}, {41, 2395}, {392, 5}},
+                              {{40, 8, 128}, {2603, 5, 190}, {5, 107, 637}}};
+        cs_debug_set_cu_count(0);
+        cs_set_mixed_fusion(1);
+        cs_debug_set_tail_cut(-1, 0);
+        for (const Case& c : cases) {
+            std::vector<int32_t> cu(1, 0);
+            for (int32_t q : c.q) cu.push_back(cu.back() + q);
+            cs_batch b = make_batch(c.ctx, cu, 1000);
+            CHECK(cs_run_layers_workspace_bytes(&b, 0, c.sh[0], c.sh[1], c.sh[2]) == 0);
+            for (int32_t layers = 1; layers <= 8; ++layers) {
+                CHECK(iterate(b, c.sh, layers, nullptr, (size_t)1 << 30, 0) == CS_OK);
+                CHECK(iterate(b, c.sh, layers, (void*)0x70008, (size_t)1 << 30, 0) == CS_OK);
+                checks += 2;
+            }
+        }
     }
     cs_debug_set_cu_count(0);
     cs_set_mixed_fusion(1);

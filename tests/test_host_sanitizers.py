@@ -1,11 +1,12 @@
 """The host side of the library under AddressSanitizer and UndefinedBehaviorSanitizer.
 
 The argument checks, the launch planning (work-item lists, key ranges, tile order, the memo of
-the last plans) and the page map are host code in two files without any device code
-(csrc/cs_api.hip, csrc/cs_page_map.hip).  They are compiled here for the host only with both
+the last plans), the iteration over layers and the page map are host code in three files without any
+device code (csrc/cs_api.hip, csrc/cs_run_layers.hip, csrc/cs_page_map.hip).  They are compiled here for the host only with both
 sanitizers, linked with stand-ins for the kernel launchers, and driven through the C ABI by
 tests/host_sanitize/driver.cpp: random batches of every shape planned for three chip sizes, the
-largest sequence count, and a few thousand random page-map operations checked against a plain
+largest sequence count, iterations of several layers whose launches must stay within the workspace
+they were given, and a few thousand random page-map operations checked against a plain
 model.  Any sanitizer report fails the test.  No GPU is needed (GPU sanitizers are not used)."""
 import os
 import shutil
@@ -22,9 +23,9 @@ CLANG = "/opt/rocm/lib/llvm/bin/clang++"
 @pytest.mark.skipif(shutil.which("hipcc") is None or not os.path.exists(CLANG), reason="no ROCm toolchain")
 def test_host_logic_is_clean_under_asan_and_ubsan(tmp_path):
     san = ["-fsanitize=address,undefined", "-fno-sanitize-recover=undefined", "-fno-omit-frame-pointer", "-O1", "-g", "-std=c++17"]
-    inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
+    inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I", HERE]
     objs = []
-    for src in (os.path.join(CSRC, "cs_api.hip"), os.path.join(CSRC, "cs_page_map.hip"), os.path.join(HERE, "stubs.hip")):
+    for src in (os.path.join(CSRC, "cs_api.hip"), os.path.join(CSRC, "cs_run_layers.hip"), os.path.join(CSRC, "cs_page_map.hip"), os.path.join(HERE, "stubs.hip")):
         obj = str(tmp_path / (os.path.basename(src) + ".o"))
         subprocess.run(["hipcc", "--offload-arch=gfx950", "--cuda-host-only", "-fPIC", *san, *inc, "-c", src, "-o", obj],
                        check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
