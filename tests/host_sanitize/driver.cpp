@@ -11,6 +11,7 @@
 #include <random>
 #include <vector>
 #include "conserve_kv.h"
+#include "cs_plan.h"
 #include "launch_window.h"
 
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "check failed line %d: %s\n", __LINE__, #c); std::exit(3); } } while (0)
@@ -108,6 +109,16 @@ int main() {
                 CHECK(iterate(b, sh, layers, (void*)0x70000, bytes, every) == CS_OK);
                 CHECK(g_window.layers_appended == layers && g_window.layers_decoded == (decodes ? layers : 0) &&
                       g_window.layers_prefilled == (chunks ? layers : 0));
+            }
+            // layers that share a launch are cut as each would be alone, and need as many times its memory at most
+            const cs::Plans one = cs::plans_for(&b, sh[0], sh[1], sh[2]);
+            for (int32_t n = 2; n <= 4; ++n) {
+                const cs::Plans& many = cs::plans_for(&b, sh[0], sh[1], sh[2], n);
+                CHECK(many.need == cs::workspace_for_layers(&b, sh[0], sh[1], sh[2], n) && many.need <= n * one.need);
+                CHECK(many.d.split_tokens == one.d.split_tokens && many.d.total_items == one.d.total_items && many.d.num_multi == one.d.num_multi);
+                CHECK(std::equal(one.d.arg_items.e, one.d.arg_items.e + (one.d.in_args ? one.d.total_items : 0), many.d.arg_items.e));
+                CHECK(many.p.range_steps == one.p.range_steps && many.p.max_ranges == one.p.max_ranges);
+                CHECK(many.p.cut_first_pos == one.p.cut_first_pos && (one.p.cut_first_pos == 0 || many.p.backwards == one.p.backwards));
             }
             // a pointer that the call has no reason to look at must not be used, whatever size comes with it
             if (least == 0) {

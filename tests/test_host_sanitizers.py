@@ -34,7 +34,8 @@ def test_host_logic_is_clean_under_asan_and_ubsan(tmp_path):
         assert "__hip_fatbin" not in undefined, os.path.basename(src) + " now holds device code"
         objs.append(obj)
     drv = str(tmp_path / "driver.o")
-    subprocess.run([CLANG, *san, *inc, "-c", os.path.join(HERE, "driver.cpp"), "-o", drv], check=True)
+    subprocess.run(["hipcc", "--offload-arch=gfx950", "--cuda-host-only", "-fPIC", *san, *inc, "-x", "hip", "-c", os.path.join(HERE, "driver.cpp"),
+                    "-o", drv], check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
     exe = str(tmp_path / "driver")
     subprocess.run([CLANG, "-fsanitize=address,undefined", drv, *objs, "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib",
                     "-o", exe], check=True)
