@@ -77,8 +77,9 @@ static int run_layers(const cs_kv_pool* pool, int32_t l0, int32_t l1, const cs_b
     }
     cs_batch cur = *batch;
     bool preempted = false;
-    const bool apart = l1 > l0 && layers_are_apart(*batch, l1 - l0, q, k_new, v_new, out, q_stride, kv_stride, Hq, pool->num_kv_heads,
-                                                   pool->head_dim);
+    const bool apart = l1 > l0 && batch->num_tokens > 0 &&
+                       layers_are_apart(*batch, l1 - l0, q, k_new, v_new, out, q_stride, kv_stride, Hq, pool->num_kv_heads,
+                                        pool->head_dim);
     for (int32_t l = l0; l < l1;) {
         if (sp && !preempted && (l - l0) % sp->check_every == 0) {
             // safepoint: between two layers nothing of the iteration is half done
@@ -99,7 +100,7 @@ static int run_layers(const cs_kv_pool* pool, int32_t l0, int32_t l1, const cs_b
         auto kv_of = [&](const void* base, int32_t layer) { return (const uint16_t*)base + (int64_t)(layer - l0) * kv_stride; };
         int32_t n = apart ? std::min(kLayersPerLaunch, l1 - l) : 1;
         if (sp && !preempted) n = std::min(n, sp->check_every - (l - l0) % sp->check_every);
-        if (n > 1 && cur.num_tokens == 0) {
+        if (n > 1 && cur.num_tokens == 0) {                // no online work left
             l += n;
             continue;
         }

@@ -363,6 +363,21 @@ def test_run_layers_checks_the_workspace_of_both_plans_before_anything_is_enqueu
     assert lib.cs_run_layers_workspace_bytes(ctypes.byref(b), 16, 33, Hkv, D) == 0
 
 
+@pytest.mark.parametrize("S", [0, 2])
+@pytest.mark.parametrize("layers", [1, 2, 4, 7])
+def test_an_iteration_without_tokens_is_refused_for_the_heads_that_the_single_calls_refuse(S, layers):
+    lib = cs.lib()
+    p = _pool(L=8, P=16, Hkv=2, D=64)
+    zeros = (ctypes.c_int32 * (S + 1))()
+    b = cs.cs_batch(S, 0, 0x2000, 4, 0x3000, 0x4000, ctypes.addressof(zeros), ctypes.addressof(zeros))
+    first = ctypes.c_int32(7)
+    for Hq, want in ((4, cs.CS_OK), (5, cs.CS_ERR_INVALID_ARG), (0, cs.CS_ERR_INVALID_ARG), (34, cs.CS_ERR_UNSUPPORTED)):
+        x, f = 0x10000, ctypes.c_float(0.1)
+        assert lib.cs_paged_attention_mixed(ctypes.byref(p), 0, ctypes.byref(b), x, 2 * x, Hq, f, None, 0, None) == want
+        assert lib.cs_run_layers(ctypes.byref(p), 0, layers, ctypes.byref(b), x, 2 * x, 3 * x, 4 * x, 256, 256, Hq, f, None, 0, None,
+                                 ctypes.byref(first), None) == want
+
+
 def test_plans_scale_with_the_compute_unit_count():
     """The launch plans size their grids by the device's compute-unit count (256 where no device
     answers).  With the count faked, the same batches are planned for a chip half and twice as
