@@ -614,7 +614,7 @@ DecodeWorkspace decode_workspace(const DecodePlan& p, int32_t Hq, int32_t Hkv, i
     if (p.num_decode == 0 || p.num_multi == 0) return w;   // nothing is cut: no item list, no partials
     size_t off = 0;
     const size_t n = (size_t)p.total_items * layers;
-    w.items = off;    off += align16(p.in_args ? n * Hkv * sizeof(uint64_t) : (size_t)p.total_items * 8 * sizeof(int32_t));
+    w.items = off;    off += align16(!p.in_args ? (size_t)p.total_items * 8 * sizeof(int32_t) : p.merges_in_place ? n * Hkv * sizeof(uint64_t) : 0);
     // partials are indexed by item; only items of multi-item sequences are ever written
     w.part_ml = off;  off += align16(n * Hq * 2 * sizeof(float));
     w.part_o = off;   off += align16(n * Hq * D * sizeof(float));
@@ -711,6 +711,14 @@ const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, in
     plans.d.merges_in_place = decode_merges_in_place(plans.d, plans.p, plans.f, Hkv, D, layers);
     plans.decode_bytes = decode_workspace(plans.d, Hq, Hkv, D, layers).total;
     plans.need = plans.decode_bytes + plans.p.bytes;
+    if (layers == 1 && plans.d.merges_in_place && plans.need > (size_t)CS_STATIC_SCRATCH_BYTES) {
+        // a kernel merges without announcements: no batch is refused the static scratch for them
+        plans.d.merges_in_place = false;
+        const size_t bare = decode_workspace(plans.d, Hq, Hkv, D, 1).total;
+        plans.d.merges_in_place = bare + plans.p.bytes > (size_t)CS_STATIC_SCRATCH_BYTES;
+        if (!plans.d.merges_in_place) plans.decode_bytes = bare;
+        plans.need = plans.decode_bytes + plans.p.bytes;
+    }
     PlanMemo& m = memo[next];
     next = (next + 1) % kMemos;
     m.valid = false;
@@ -724,7 +732,9 @@ const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, in
 
 size_t workspace_for_layers(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers) {
     const Plans& one = plans_for(b, Hq, Hkv, D, 1);
-    return decode_workspace(one.d, Hq, Hkv, D, layers).total + one.p.bytes * layers;
+    DecodePlan d = one.d;
+    d.merges_in_place = true;                          // (whether they are depends on the arrangement)
+    return decode_workspace(d, Hq, Hkv, D, layers).total + one.p.bytes * layers;
 }
 }  // namespace cs
 

@@ -83,9 +83,9 @@ struct DecodePlan {
     ItemsInArgs arg_items;     // total_items words
 };
 DecodePlan plan_decode(const cs_batch* batch, int32_t num_kv_heads, int32_t head_dim);
-// Workspace layout (all 16-byte aligned): announcements of the partials (item list in the kernel
-// arguments: 8 bytes per item and kv head, cs_arrive.h) or the item list | partial (max, sum) |
-// partial outputs.  All zero when nothing is cut.
+// Workspace layout (all 16-byte aligned): announcements of the partials (where they are merged in
+// place: 8 bytes per item and kv head, cs_arrive.h) or, unless it travels in the kernel arguments, the item
+// list | partial (max, sum) | partial outputs.  All zero when nothing is cut.
 struct DecodeWorkspace {
     size_t items, part_ml, part_o, total;
 };

@@ -27,7 +27,8 @@ struct Plans {
 // `layers` is: how many layers share a launch changes no bit of their results.
 const Plans& plans_for(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers = 1);
 
-// The workspace a launch of `layers` layers needs: plans_for(..., layers).need without making that plan.
+// The workspace a launch of `layers` layers may need: at least plans_for(..., layers).need, without making
+// that plan; nothing where one layer needs nothing.
 size_t workspace_for_layers(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers);
 
 int attention_shape_ok(int32_t Hq, int32_t Hkv, int32_t D);

@@ -363,6 +363,15 @@ def test_run_layers_checks_the_workspace_of_both_plans_before_anything_is_enqueu
     assert lib.cs_run_layers_workspace_bytes(ctypes.byref(b), 16, 33, Hkv, D) == 0
 
 
+def test_announcements_of_partials_refuse_no_batch_the_static_scratch():
+    """15 cut sequences whose partials all but fill the static scratch (67.07 MB of 67.11 MB): the words
+    that announce partials to workgroups that merge in place would not fit beside them."""
+    ctx = [49029, 26349, 14657, 39414, 70887, 27356, 19148, 2895, 68373, 65932, 65489, 6573, 38332, 19344, 26191, 16231]
+    b, keep = _batch(ctx, [1] * 15 + [10], max_blocks=1 << 13)
+    lib = cs.lib()
+    assert 67_000_000 < lib.cs_paged_attention_workspace_bytes(ctypes.byref(b), 32, 32, 128) <= lib.cs_static_scratch_bytes()
+
+
 @pytest.mark.parametrize("S", [0, 2])
 @pytest.mark.parametrize("layers", [1, 2, 4, 7])
 def test_an_iteration_without_tokens_is_refused_for_the_heads_that_the_single_calls_refuse(S, layers):
