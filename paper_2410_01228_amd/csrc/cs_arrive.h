@@ -1,7 +1,7 @@
 // "Last one merges": the workgroups that share a cut decode sequence or a cut prefill tile each
-// leave a partial, announce it, and whoever finds all of them announced merges them.  A merge kernel
-// of its own costs 5 us (decode) to 15 us (tiles) behind every launch; done this way most merges
-// run while other workgroups still compute, and one launch is gone.
+// leave a partial, announce it, and whoever finds all of them announced merges them.  That saves a merge
+// kernel's launch, and where other workgroups still compute the merge itself; where neither weighs
+// enough (the rules are beside the launch planning) a kernel merges and nothing is announced.
 //
 // Partials cross from one XCD's L2 to another's, so they are written through (store at agent scope:
 // sc1) and read past the reader's caches (load at agent scope), and a wavefront waits for its stores

@@ -132,17 +132,23 @@ struct PrefillPlan {
     int32_t base_slot;         // first workgroup slot that can belong to a prefill sequence (set whenever there is a chunk)
     int32_t num_slots;         // slots from base_slot on: the grid's extent; partials are indexed by slot - base_slot
     size_t  bytes;             // workspace for the partials (0 when nothing is cut)
+    bool    merges_in_place;   // the fused grid merges cut tiles itself, no kernel follows
 };
 PrefillPlan plan_prefill(const cs_batch* batch, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim, int32_t layers);
 int launch_prefill(const cs_kv_pool& pool, int32_t layer, const cs_batch& b, const PrefillPlan& plan,
                    const void* q, void* out, int32_t Hq, float scale, void* workspace, hipStream_t st, bool f16);
+// The merge of the partials of cut tiles alone (what launch_prefill ends with when tiles are cut).
+int launch_prefill_merge(const cs_kv_pool& pool, const LayerSpan& span, const cs_batch& b, const PrefillPlan& plan, void* out, int32_t Hq,
+                         void* workspace, hipStream_t st, bool f16);
 // One launch for a batch that holds both chunks and decode tokens.  persistent_wgs == 0: the
 // prefill workgroups first, one workgroup per decode (item, kv head) pair behind them, so that
 // decode work fills the slots the uneven prefill tiles leave empty instead of waiting for the
 // last of them.  persistent_wgs > 0: that many decode workgroups first (the host passes the CU
 // count: one per CU), each walking several pairs, the tiles beside them.  Needs the item list
 // in the kernel arguments (dplan.in_args).  Tiles cut into key ranges bring one workgroup per
-// range; tiles and cut decode sequences are merged by whichever of their workgroups finishes last.
+// range; tiles and cut decode sequences are merged by whichever of their workgroups finishes last
+// where the plans say so, else the caller merges them afterwards (launch_prefill_merge, launch_decode
+// with merge_only).
 // tile_priority: 0, or the higher of the two issue priorities the tile wavefronts alternate between
 // (1 or 2; decode wavefronts stay at 0).
 int launch_mixed(const cs_kv_pool& pool, int32_t layer, const cs_batch& b, const DecodePlan& dplan,

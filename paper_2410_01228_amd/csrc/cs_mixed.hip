@@ -42,7 +42,7 @@ __global__ __launch_bounds__(kPrefillThreads, 2) void mixed_kernel(
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float scale_log2e,
     int32_t range_steps, int32_t base_slot, int32_t num_slots, int32_t cut_first_pos, int32_t max_ranges,
     float* __restrict__ prefill_part, uint32_t dec_first, uint32_t dec_wgs, uint32_t n_decode, int32_t backwards,
-    const ItemsInArgs items, const DecodePartials part,
+    const ItemsInArgs items, const DecodePartials part, uint64_t tiles_launch,
     int32_t layers, int64_t next_layer, int64_t next_q)
 {
     __shared__ MixedLds<D> lds;
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kPrefillThreads, 2) void mixed_kernel(
         }
         const int32_t b = base_slot + (backwards ? num_slots - 1 - pos : pos);   // backwards: longest tiles first
         prefill_tile<D, E, kPriority, PS, true, true>(lds.prefill, layer_base, page_stride, num_pages, Hkv, G, S, block_tables, max_blocks,
-                           ctx_lens, cu_q_lens, q, out, scale_log2e, steps_per_range, part_tile, part.launch, g, b, range);
+                           ctx_lens, cu_q_lens, q, out, scale_log2e, steps_per_range, part_tile, tiles_launch, g, b, range);
     } else {
         const uint32_t j = blockIdx.x - dec_first;
         const int32_t n_items = n_decode / ((uint32_t)layers * Hkv);
@@ -127,7 +127,7 @@ static int launch_mixed_as(const cs_kv_pool& pool, int32_t layer, const LayerSpa
                        b.cu_q_lens, (const uint16_t*)q, (uint16_t*)out, scale_log2e, pplan.range_steps,         \
                        pplan.base_slot, pplan.num_slots, pplan.cut_first_pos, pplan.max_ranges,                 \
                        (float*)prefill_ws, (uint32_t)dec_first, (uint32_t)dec_wgs, (uint32_t)n_decode, (int32_t)pplan.backwards,    \
-                       dplan.arg_items, part, span.n, span.pool, span.q);
+                       dplan.arg_items, part, pplan.merges_in_place ? part.launch : 0, span.n, span.pool, span.q);
 #define CS_LAUNCH_MIXED(DD, PRIO)                                                                            \
     if (pool.page_size == 16) { CS_LAUNCH_MIXED_P(DD, PRIO, 16) } else { CS_LAUNCH_MIXED_P(DD, PRIO, 8) }
     if (D == 128) { if (prio == 2) { CS_LAUNCH_MIXED(128, 2) } else if (prio == 1) { CS_LAUNCH_MIXED(128, 1) } else { CS_LAUNCH_MIXED(128, 0) } }

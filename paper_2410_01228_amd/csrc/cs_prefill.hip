@@ -6,14 +6,14 @@ namespace cs {
 
 // grid.x = slots * Hkv, kv head fastest (the slots from base_slot on: no sequence before it has a
 // chunk); grid.y = key ranges; grid.z = layers
-template <int D, class E, int PS, bool kMayCut>
+template <int D, class E, int PS>
 __global__ __launch_bounds__(kPrefillThreads, 2) void prefill_kernel(
     const uint16_t* __restrict__ layer_base, int64_t page_stride, int32_t num_pages,
     int32_t Hkv, int32_t G, int32_t S,
     const int32_t* __restrict__ block_tables, int32_t max_blocks,
     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens,
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out, float scale_log2e,
-    int32_t range_steps, int32_t base_slot, float* __restrict__ part, uint64_t launch, int32_t n_ordered, const SlotOrder order,
+    int32_t range_steps, int32_t base_slot, float* __restrict__ part, int32_t n_ordered, const SlotOrder order,
     int32_t backwards, int64_t next_layer, int64_t next_q, int64_t next_part)
 {
     __shared__ PrefillLds<D> lds;
@@ -22,14 +22,98 @@ __global__ __launch_bounds__(kPrefillThreads, 2) void prefill_kernel(
     const int32_t b = n_ordered > 0 ? (int32_t)order.slot[pos]
                                     : base_slot + (backwards ? (int32_t)(gridDim.x / Hkv) - 1 - pos : pos);
     // (with key ranges the grid has no order table: cut position = slot position)
-    prefill_tile<D, E, 1, PS, false, kMayCut>(lds, layer_base + blockIdx.z * next_layer, page_stride, num_pages, Hkv, G, S, block_tables, max_blocks, ctx_lens, cu_q_lens,
+    prefill_tile<D, E, 1, PS, false, false>(lds, layer_base + blockIdx.z * next_layer, page_stride, num_pages, Hkv, G, S, block_tables, max_blocks, ctx_lens, cu_q_lens,
                        q + blockIdx.z * next_q, out + blockIdx.z * next_q, scale_log2e, range_steps,
-                       partials_of<D>(part + blockIdx.z * next_part, b - base_slot, Hkv, g, gridDim.y), launch, g, b,
+                       partials_of<D>(part + blockIdx.z * next_part, b - base_slot, Hkv, g, gridDim.y), 0, g, b,
                        blockIdx.y);
+}
+
+// Merge of the key-range partials of the tiles that were cut: grid.x = Hkv * cut tiles (launch
+// positions cut_first_pos .. num_slots-1, the same numbering as the kernel that wrote them),
+// grid.y = kMergeParts row groups of a tile, grid.z = layers; one lane per (query row, 4 features), so a
+// wavefront reads whole 512-byte runs of a partial's rows, and rows without a token are left out.  (Merged by the last range's workgroup instead, alone on its CU,
+// chunks of 2-600 tokens on 500-60000 keys took 7% longer in the geometric mean of 140, 39% at worst: 2-3
+// tokens on 0.6-12K keys, 64/8 heads, 48 -> 65 us.)
+constexpr int kMergeParts = 4;
+template <int D, class E>
+__global__ __launch_bounds__(kPrefillThreads) void prefill_merge_kernel(
+    int32_t Hkv, int32_t G, int32_t S, const int32_t* __restrict__ ctx_lens,
+    const int32_t* __restrict__ cu_q_lens, uint16_t* __restrict__ out,
+    int32_t range_steps, int32_t max_ranges, int32_t base_slot, int32_t num_slots, int32_t cut_first_pos,
+    int32_t backwards, const float* __restrict__ part, int64_t next_q, int64_t next_part)
+{
+    out += blockIdx.z * next_q;
+    part += blockIdx.z * next_part;
+    constexpr int kPartRow = D + 4;
+    constexpr int kQuads = D / 4;                                  // lanes per query row
+    constexpr int kRows = kTileCols * 16 / kMergeParts;            // rows of this workgroup
+    const int32_t g = blockIdx.x % Hkv, cut_pos = blockIdx.x / Hkv, pos = cut_first_pos + cut_pos;
+    const int32_t b = base_slot + (backwards ? num_slots - 1 - pos : pos);
+    int32_t lo = 0, hi = S;
+    while (hi - lo > 1) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (prefill_slot_start(cu_q_lens[mid], mid, G) <= b) lo = mid; else hi = mid;
+    }
+    const int32_t s = lo;
+    const int32_t t_seq = cu_q_lens[s];
+    const int32_t q_len = cu_q_lens[s + 1] - t_seq;
+    if (q_len <= 1) return;
+    const int32_t n_ct = ((q_len + 15) >> 4) * G;
+    const int32_t ct0 = (int32_t)(b - prefill_slot_start(t_seq, s, G)) * kTileCols;
+    if (ct0 >= n_ct) return;
+    const int32_t tb_max = (min(ct0 + kTileCols, n_ct) - 1) / G;
+    const int32_t n_keys = ctx_lens[s] + min(q_len, (tb_max + 1) * 16);
+    const int32_t n_steps = (n_keys + kKeysPerStep - 1) / kKeysPerStep;
+    const int32_t n_ranges = (n_steps + range_steps - 1) / range_steps;
+    if (n_ranges <= 1) return;                               // written directly by the tile kernel
+    const float* tile = partials_of<D>(const_cast<float*>(part), cut_pos, Hkv, g, max_ranges);
+    const int64_t rstride = (int64_t)kTileCols * 16 * kPartRow;
+    const int32_t Hq = Hkv * G;
+    for (int32_t idx = threadIdx.x; idx < kRows * kQuads; idx += kPrefillThreads) {
+        const int32_t row_id = blockIdx.y * kRows + idx / kQuads, quad = idx % kQuads;
+        const int32_t ct = ct0 + (row_id >> 4);
+        const int32_t tb = ct / G, hh = ct - tb * G;
+        const int32_t tl = tb * 16 + (row_id & 15);
+        if (ct >= n_ct || tl >= q_len) continue;
+        const float* base = tile + row_id * kPartRow;
+        float M = kNoMax;
+        for (int32_t r = 0; r < n_ranges; ++r) M = fmaxf(M, base[r * rstride + D]);
+        float L = 0.f;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int32_t r = 0; r < n_ranges; ++r) {
+            const float* p = base + r * rstride;
+            const float f = exp2f(p[D] - M);                 // 0 for a range the row sees nothing of
+            L += p[D + 1] * f;
+            const f32x4 v = *(const f32x4*)(p + quad * 4);
+            acc += v * f;
+        }
+        const float inv = 1.f / L;
+        uint16_t* dst = out + ((int64_t)(t_seq + tl) * Hq + g * G + hh) * D + quad * 4;
+        u32x2 w = { E::pack(acc[0] * inv, acc[1] * inv), E::pack(acc[2] * inv, acc[3] * inv) };
+        *(u32x2*)dst = w;
+    }
 }
 
 // (plan_prefill, the host plan of the key-range split and the tile order, is in cs_api.hip with
 // the other launch planning.)
+
+template <class E>
+static void launch_merge_as(const cs_kv_pool& pool, const LayerSpan& span, const cs_batch& b, const PrefillPlan& plan, void* out,
+                            int32_t Hq, void* workspace, hipStream_t st)
+{
+    const int32_t Hkv = pool.num_kv_heads, D = pool.head_dim, G = Hq / Hkv;
+    const float* part = (const float*)workspace;
+    dim3 mgrid((uint32_t)Hkv * (uint32_t)(plan.num_slots - plan.cut_first_pos), kMergeParts, (uint32_t)span.n);
+    const int64_t next_part = (int64_t)(plan.bytes / sizeof(float)) / span.n;
+    if (D == 128)
+        hipLaunchKernelGGL((prefill_merge_kernel<128, E>), mgrid, dim3(kPrefillThreads), 0, st, Hkv, G, b.num_seqs,
+                           b.ctx_lens, b.cu_q_lens, (uint16_t*)out, plan.range_steps, plan.max_ranges,
+                           plan.base_slot, plan.num_slots, plan.cut_first_pos, (int32_t)plan.backwards, part, span.q, next_part);
+    else
+        hipLaunchKernelGGL((prefill_merge_kernel<64, E>), mgrid, dim3(kPrefillThreads), 0, st, Hkv, G, b.num_seqs,
+                           b.ctx_lens, b.cu_q_lens, (uint16_t*)out, plan.range_steps, plan.max_ranges,
+                           plan.base_slot, plan.num_slots, plan.cut_first_pos, (int32_t)plan.backwards, part, span.q, next_part);
+}
 
 template <class E>
 static int launch_prefill_as(const cs_kv_pool& pool, int32_t layer, const LayerSpan& span, const cs_batch& b, const PrefillPlan& plan,
@@ -43,19 +127,25 @@ static int launch_prefill_as(const cs_kv_pool& pool, int32_t layer, const LayerS
     dim3 grid((uint32_t)Hkv * slots, (uint32_t)plan.max_ranges, (uint32_t)span.n);
     const int64_t next_part = (int64_t)(plan.bytes / sizeof(float)) / span.n;
     float* part = (float*)workspace;
-#define CS_LAUNCH_PREFILL_C(DD, PS, CUT)                                                                            \
-    hipLaunchKernelGGL((prefill_kernel<DD, E, PS, CUT>), grid, dim3(kPrefillThreads), 0, st, layer_base, pool.page_stride, \
+#define CS_LAUNCH_PREFILL(DD, PS)                                                                                   \
+    hipLaunchKernelGGL((prefill_kernel<DD, E, PS>), grid, dim3(kPrefillThreads), 0, st, layer_base, pool.page_stride, \
                        pool.num_pages, Hkv, G, b.num_seqs, b.block_tables, b.max_blocks_per_seq,                   \
                        b.ctx_lens, b.cu_q_lens, (const uint16_t*)q, (uint16_t*)out, scale_log2e,                   \
-                       plan.range_steps, plan.base_slot, part, next_launch_number(), plan.n_ordered, plan.order, (int32_t)plan.backwards, \
+                       plan.range_steps, plan.base_slot, part, plan.n_ordered, plan.order, (int32_t)plan.backwards, \
                        span.pool, span.q, next_part);
-#define CS_LAUNCH_PREFILL(DD, PS)                                                                                   \
-    if (plan.max_ranges > 1) { CS_LAUNCH_PREFILL_C(DD, PS, true) } else { CS_LAUNCH_PREFILL_C(DD, PS, false) }
     if (pool.page_size == 16) { if (D == 128) { CS_LAUNCH_PREFILL(128, 16) } else { CS_LAUNCH_PREFILL(64, 16) } }
     else                      { if (D == 128) { CS_LAUNCH_PREFILL(128, 8) } else { CS_LAUNCH_PREFILL(64, 8) } }
 #undef CS_LAUNCH_PREFILL
-#undef CS_LAUNCH_PREFILL_C
+    if (plan.max_ranges > 1) launch_merge_as<E>(pool, span, b, plan, out, Hq, workspace, st);
     return check_launch("prefill kernels");
+}
+
+int launch_prefill_merge(const cs_kv_pool& pool, const LayerSpan& span, const cs_batch& b, const PrefillPlan& plan, void* out, int32_t Hq,
+                         void* workspace, hipStream_t st, bool f16)
+{
+    if (f16) launch_merge_as<F16>(pool, span, b, plan, out, Hq, workspace, st);
+    else launch_merge_as<Bf16>(pool, span, b, plan, out, Hq, workspace, st);
+    return check_launch("prefill merge kernel");
 }
 
 int launch_prefill_layers(const cs_kv_pool& pool, int32_t layer, const LayerSpan& span, const cs_batch& b, const PrefillPlan& plan,

@@ -133,9 +133,10 @@ struct PrefillLds {
 // grids whose other wavefronts are mostly tiles too, or become so once a decode workgroup per CU
 // is done; 2: the same and always above decode wavefronts, which stay at 0; with decode work of
 // equal weight queued behind the tiles either costs more than it gains).
-// kMayCut: false where the host cuts no tile of the launch (the code behind the loop would change
-// the loop's register allocation for the worse).
-template <int D, class E, int kPriority, int PS, bool kLaneAddr16, bool kMayCut>
+// kMergeInGrid: whether a launch may merge cut tiles itself (only the fused grid's: the code behind the
+// loop changes the loop's register allocation); it does where `launch` is not 0, else it leaves the
+// partials to prefill_merge_kernel.
+template <int D, class E, int kPriority, int PS, bool kLaneAddr16, bool kMergeInGrid>
 __device__ __forceinline__ void prefill_tile(
     PrefillLds<D>& lds,
     const uint16_t* __restrict__ layer_base, int64_t page_stride, int32_t num_pages,
@@ -561,12 +562,26 @@ __device__ __forceinline__ void prefill_tile(
     if (kPriority) __builtin_amdgcn_s_setprio(0);
     wait_vmcnt<0>();                                   // no copy may outlive the workgroup's LDS
 
-    // ---- a cut tile: the last of its ranges to get here adds the others' partials (unnormalised
-    // output, running max and sum per query row) to its registers; one that finds another range
-    // missing leaves its own.  The announcements lie in the padding of each range's first row. ----
-    if constexpr (kMayCut) {
+    // ---- a cut tile leaves the partial of its range: unnormalised output, running max and sum per
+    // query row ----
+    if (n_ranges > 1 && (!kMergeInGrid || launch == 0)) {
+        if (part_tile == nullptr) return;                 // (a cut tile always has a block: a planning error must not write)
+        float* wg = part_tile + (int64_t)range * (kTileCols * 16 * kPartRow);
+#pragma unroll
+        for (int c = 0; c < kNCT; ++c) {
+            float* row = wg + ((wave * kNCT + c) * 16 + (lane & 15)) * kPartRow;
+#pragma unroll
+            for (int dt = 0; dt < D / 16; ++dt) *(f32x4*)(row + dt * 16 + (lane >> 4) * 4) = o[c][dt];
+            if (lane < 16) { row[D] = m_run[c]; row[D + 1] = lacc[c][0]; }
+        }
+        return;
+    }
+    // ---- or, merged in the grid, the last of its ranges to get here adds the others' partials to its
+    // registers; one that finds another range missing leaves its own.  The announcements lie in the
+    // padding of each range's first row. ----
+    if constexpr (kMergeInGrid) {
         if (n_ranges > 1) {
-            if (part_tile == nullptr) return;             // (a cut tile always has a block: a planning error must not write)
+            if (part_tile == nullptr) return;
             constexpr uint32_t kRangeBytes = kTileCols * 16 * kPartRow * 4;
             const Shared part(part_tile, (uint32_t)n_ranges * kRangeBytes);
             const Announcements words(part, (D + 2) * 4, kRangeBytes, n_ranges, launch);
@@ -596,7 +611,7 @@ __device__ __forceinline__ void prefill_tile(
                 if (!lds.last) return;
             }
             // every range weighted against the maximum of all, in the order of the ranges, whichever of
-            // them this is (fused multiply-adds, as a loop over all ranges in memory would be); exp2f, not the
+            // them this is (fused multiply-adds, as in prefill_merge_kernel); exp2f, not the
             // bare instruction: a range 2^126 and more below it still counts where the others have nothing
             f32x4 sum[kNCT][D / 16];
             float M[kNCT], L[kNCT];
@@ -618,10 +633,17 @@ __device__ __forceinline__ void prefill_tile(
             auto row_of = [&](int r, int c) -> uint32_t {
                 return (uint32_t)r * kRangeBytes + ((wave * kNCT + c) * 16 + (lane & 15)) * (kPartRow * 4);
             };
-            for (int r = 0; r < n_ranges; ++r) {
-                if (r == range) continue;
+            for (int r0 = 0; r0 < n_ranges; r0 += 8) {            // (past the last range: the last again)
+                a_u32x2 ml[8][kNCT];
 #pragma unroll
-                for (int c = 0; c < kNCT; ++c) M[c] = fmaxf(M[c], as_float(part.load2(row_of(r, c) + D * 4)[0]));
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int c = 0; c < kNCT; ++c) ml[j][c] = part.load2(row_of(min(r0 + j, n_ranges - 1), c) + D * 4);
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int c = 0; c < kNCT; ++c)
+                        M[c] = fmaxf(M[c], min(r0 + j, n_ranges - 1) == range ? m_run[c] : as_float(ml[j][c][0]));
             }
             for (int r = 0; r < n_ranges; ++r) {
                 if (r == range) {

@@ -37,8 +37,10 @@ static int attention_of_layers(const cs_kv_pool& pool, int32_t l, int32_t n, con
     const LayerSpan span = {n, pool.layer_stride, q_stride, 0};
     void* prefill_ws = (char*)workspace + plans.decode_bytes;
     if (plans.f.arrangement != 0) {
-        const int rc = launch_mixed_layers(pool, l, span, b, plans.d, plans.p, q, out, Hq, scale, workspace, prefill_ws, st, f16,
-                                           plans.f.prio, plans.f.arrangement == 2 ? plans.f.persistent_wgs : 0);
+        int rc = launch_mixed_layers(pool, l, span, b, plans.d, plans.p, q, out, Hq, scale, workspace, prefill_ws, st, f16,
+                                     plans.f.prio, plans.f.arrangement == 2 ? plans.f.persistent_wgs : 0);
+        if (rc == CS_OK && plans.p.max_ranges > 1 && !plans.p.merges_in_place)
+            rc = launch_prefill_merge(pool, span, b, plans.p, out, Hq, prefill_ws, st, f16);
         if (rc || plans.d.num_multi == 0 || plans.d.merges_in_place) return rc;
         return launch_decode_layers(pool, l, span, b, plans.d, q, out, Hq, scale, workspace, st, f16, true);
     }

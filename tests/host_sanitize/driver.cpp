@@ -129,6 +129,28 @@ int main() {
         }
         checks += 8;
     }
+    // cut tiles: a kernel merges them where one workgroup's work on them would show, the grid where two
+    // ranges make it short or decode work still runs
+    {
+        struct Case { int32_t decodes, keys, chunk, prefix; bool in_place; };
+        const Case cases[] = {{1, 40, 3, 26000, false}, {4, 500, 8, 17000, false}, {8, 900, 5, 3000, false},
+                              {24, 1600, 200, 1000, true}, {64, 4000, 24, 17000, true}, {128, 8000, 3, 26000, true}};
+        const int sh[3] = {32, 8, 128};
+        cs_debug_set_cu_count(256);
+        cs_set_mixed_fusion(1);
+        cs_debug_set_tail_cut(-1, 0);
+        for (const Case& c : cases) {
+            std::vector<int32_t> ctx(c.decodes, c.keys), cu(1, 0);
+            for (int32_t s = 0; s < c.decodes; ++s) cu.push_back(s + 1);
+            ctx.push_back(c.prefix);
+            cu.push_back(c.decodes + c.chunk);
+            cs_batch b = make_batch(ctx, cu, 1 << 14);
+            const cs::Plans& p = cs::plans_for(&b, sh[0], sh[1], sh[2]);
+            CHECK(p.p.max_ranges > 1 && p.f.arrangement != 0 && p.p.merges_in_place == c.in_place);
+            ++checks;
+        }
+        cs_debug_set_cu_count(0);
+    }
     // batches that need no workspace layer by layer, but whose larger grids would gain from cuts
     {
         struct Case { int sh[3]; std::vector<int32_t> ctx, q; };

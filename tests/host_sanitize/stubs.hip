@@ -61,6 +61,12 @@ int launch_mixed_layers(const cs_kv_pool& pool, int32_t, const LayerSpan& span, 
     return CS_OK;
 }
 
+int launch_prefill_merge(const cs_kv_pool&, const LayerSpan&, const cs_batch&, const PrefillPlan& plan, void*, int32_t, void* ws, hipStream_t, bool) {
+    used("prefill merge", ws, plan.bytes);
+    if (plan.max_ranges <= 1 || plan.merges_in_place) fail("given a merge that nobody needs");
+    return CS_OK;
+}
+
 int launch_decode(const cs_kv_pool& pool, int32_t layer, const cs_batch& b, const DecodePlan& plan, const void* q, void* out, int32_t Hq,
                   float scale, void* ws, hipStream_t st, bool f16, bool merge_only) {
     return launch_decode_layers(pool, layer, LayerSpan{1, 0, 0, 0}, b, plan, q, out, Hq, scale, ws, st, f16, merge_only);

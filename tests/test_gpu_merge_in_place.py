@@ -119,6 +119,38 @@ def test_every_piece_is_weighted_against_the_maximum_of_all(cus):
         at += k
 
 
+# ranges: 2, 4, 16; a chunk that leaves most rows of its tiles without a token
+@pytest.mark.parametrize("chunk,prefix,ranges", [(40, 2000, 2), (200, 3000, 4), (5, 30000, 16)])
+def test_tiles_merged_in_the_grid_and_by_kernel_agree(chunk, prefix, ranges):
+    """The same chunk alone (a kernel merges its tiles), beside one short decode (a kernel too, from three
+    ranges on) and beside a decode stream that outlasts it (the grid does): the same bits."""
+    sh, outs = synth.Shape(32, 8, 128), []
+    g = torch.Generator(device="cuda").manual_seed(7)
+    q, k, v = (synth.randn_bf16((chunk, h, sh.D), g, "cuda") for h in (sh.Hq, sh.Hkv, sh.Hkv))
+    prior = [synth.randn_bf16((prefix, sh.Hkv, sh.D), g, "cuda") for _ in range(2)]
+    for decodes, keys in ((0, 0), (1, 50), (64, 3000)):
+        ctx = [prefix] + [keys] * decodes
+        b = synth.make_batch(sh, ctx, [chunk] + [1] * decodes, synth.generator(8 + decodes))
+        pool = cs.Pool.empty(1, b.num_pages, sh.Hkv, sh.D)
+        pool.tensor.normal_(generator=g)
+        bb = cs.Batch(b.block_tables, b.ctx_lens, b.cu_q_lens)
+        assert cs.cs_debug_mixed_tail_cut(bb, sh.Hq, sh.Hkv, sh.D)[1:] == (0, ranges)
+        first = cs.Batch(b.block_tables[:1], torch.zeros(1, dtype=torch.int32), torch.tensor([0, prefix], dtype=torch.int32))
+        cs.cs_kv_append(pool, 0, first, *prior)
+        pad = [torch.cat([x, torch.zeros((decodes, *x.shape[1:]), dtype=x.dtype, device="cuda")]) for x in (q, k, v)]
+        cs.cs_kv_append(pool, 0, bb, pad[1], pad[2])
+        ws = cs.workspace_for(bb, sh.Hq, sh.Hkv, sh.D)
+        ws.random_(0, 256, generator=g)
+        for _ in range(2):
+            out = torch.full_like(pad[0], float("nan"))
+            cs.cs_paged_attention_mixed(pool, 0, bb, pad[0], out, sh.Hq, sh.scale, ws)
+            torch.cuda.synchronize()
+            outs.append(out[:chunk])
+    assert torch.isfinite(outs[0].float()).all()
+    for out in outs[1:]:
+        assert torch.equal(out.view(torch.int16), outs[0].view(torch.int16))
+
+
 def test_a_tile_range_far_below_the_others_still_counts():
     """A chunk whose tiles are cut in two ranges: the keys of the first score about 130 octaves below those
     of the second, and only the first range's first key has a value, 2^127, in one feature.  What is
