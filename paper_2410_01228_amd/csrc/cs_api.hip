@@ -590,13 +590,15 @@ static FusePlan plan_fusion(const cs_batch* b, const DecodePlan& d, PrefillPlan&
 
 // Where the partials of cut decode sequences are merged.  In place costs every workgroup three round
 // trips to memory at its end (stores acknowledged, announcement acknowledged, the others' read; about
-// 4 us), a kernel of its own 5 us behind the last: so in place where the workgroups end about
-// together -- all resident at once, or a workgroup per CU that walks its pairs first -- and in a
-// kernel where they run in rounds and each round would pay.
+// 4 us), a kernel of its own 5 us behind the last: so in place where all workgroups are resident at once
+// and end about together, and in a kernel where they run in rounds and each round would pay.  Decode
+// workgroups beside the tiles, one per CU, could merge behind the last of their pairs, but whoever ends
+// last then merges sequence after sequence: slower than a kernel on 130 of 150 mixes, by 1-2% on average
+// whatever the number of rounds, 7% at worst (40/8 heads, 928 pairs: 89 -> 95 us).
 static bool decode_merges_in_place(const DecodePlan& d, const PrefillPlan& p, const FusePlan& f, int32_t Hkv, int32_t D, int32_t layers) {
     if (!d.in_args || d.num_multi == 0) return false;
     const int64_t cus = device_cus(), wgs = (int64_t)d.total_items * Hkv * layers;
-    if (f.arrangement == 2) return wgs <= (int64_t)kMaxPairsInPlace * std::min<int64_t>(f.persistent_wgs, wgs);
+    if (f.arrangement == 2) return false;
     if (f.arrangement == 1) return wgs + (int64_t)p.num_slots * p.max_ranges * Hkv * layers <= 2 * cus;
     return wgs <= cus * (D == 128 ? (d.pages_ahead == 2 ? 2 : 3) : 4);
 }

@@ -65,7 +65,6 @@ __host__ __device__ inline int64_t prefill_slot_start(int32_t cu_q, int32_t s, i
 // pieces of that sequence (24-31).  The list must fit the 4 KiB argument block of a launch.
 constexpr int kMaxArgItems = 880;
 struct ItemsInArgs { uint32_t e[kMaxArgItems]; };
-constexpr int kMaxPairsInPlace = 64;         // (item, kv head) pairs a workgroup can walk and still merge in place
 
 // Plan of the decode path, a pure function of the host lengths (used by both the
 // workspace query and the launch).

@@ -63,13 +63,12 @@ __global__ __launch_bounds__(kDecodeThreads, 2) void decode_split_kernel(
 {
     __shared__ DecodeLds<D> lds;
     const int32_t item = blockIdx.x / Hkv, g = blockIdx.x - item * Hkv, n_items = gridDim.x / Hkv;
+    const DecodePartials mine = part.of_layer(blockIdx.y, n_items, Hkv * G, Hkv, D);
+    out += blockIdx.y * next_q;
     decode_item<D, Src, E, kAhead, PS>(lds, layer_base + blockIdx.y * next_layer, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
-                           cu_q_lens, q + blockIdx.y * next_q, out + blockIdx.y * next_q, scale_log2e,
-                           part.of_layer(blockIdx.y, n_items, Hkv * G, Hkv, D), item, g);
+                           cu_q_lens, q + blockIdx.y * next_q, out, scale_log2e, mine, item, g);
     if constexpr (std::is_same_v<Src, ItemsInArgs>) {
-        if (part.words)
-            merge_in_place<D, E>(lds, part, src, [](int32_t) { return (int32_t)(blockIdx.y * gridDim.x + blockIdx.x); }, 1, ctx_lens,
-                                 cu_q_lens, Hkv, G, out, n_items, next_q);
+        if (part.words) merge_in_place<D, E>(lds, mine, src, item, g, ctx_lens, cu_q_lens, Hkv, G, out);
     }
 }
 

@@ -225,7 +225,7 @@ struct DecodeLds {
     float o[kDecodeWaves][kMaxGroup][D];
     float m[kDecodeWaves][kMaxGroup];
     float l[kDecodeWaves][kMaxGroup];
-    int32_t last[kMaxPairsInPlace];                   // which of its pairs' sequences this workgroup merges
+    int32_t last;                                     // whether this workgroup merges its sequence
 };
 
 // Where the items of cut sequences leave their partials: floats [item][Hq][D] and [item][Hq][2]
@@ -457,51 +457,32 @@ __device__ __forceinline__ void decode_item(
     }
 }
 
-// The end of a workgroup that has worked off pairs pair_at(0) .. pair_at(n_pairs - 1) ((layer of the
-// launch * n_items + item) * Hkv + kv head; -1: none): announces the partials it left, and merges the sequences it finds complete.  All
-// announcements go out together and behind the last pair, so a workgroup that walks several pairs
-// does not stop between them.
-template <int D, class E, class Src, class PairAt>
+// The end of a workgroup that has worked off item `item` and kv head g: if that is a piece of a cut
+// sequence, announces the partial it left, and merges the sequence if it finds it complete.  part, out: of
+// the layer.
+template <int D, class E, class Src>
 __device__ __forceinline__ void merge_in_place(
-    DecodeLds<D>& lds, const DecodePartials& part, const Src& src, PairAt pair_at, int32_t n_pairs,
-    const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens, int32_t Hkv, int32_t G, uint16_t* __restrict__ out,
-    int32_t n_items, int64_t next_q)
+    DecodeLds<D>& lds, const DecodePartials& part, const Src& src, int32_t item, int32_t g,
+    const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens, int32_t Hkv, int32_t G, uint16_t* __restrict__ out)
 {
+    DecodeItem it;
+    if (!fetch_item(src, item, ctx_lens, cu_q_lens, it) || it.n_splits == 1) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int32_t Hq = Hkv * G;
-    int32_t layer;
-    auto piece_of = [&](int32_t k, DecodeItem& it, int32_t& item, int32_t& g) {      // is pair k a piece of a cut sequence?
-        const int32_t pair = pair_at(k);
-        if (pair < 0) return false;
-        item = pair / Hkv;
-        g = pair - item * Hkv;
-        layer = item / n_items;
-        item -= layer * n_items;
-        return fetch_item(src, item, ctx_lens, cu_q_lens, it) && it.n_splits > 1;
-    };
-    auto words_of = [&](const DecodeItem& it, int32_t g) {
-        return Announcements(Shared(part.words + ((int64_t)layer * n_items + it.first_item) * Hkv + g, (uint32_t)it.n_splits * Hkv * 8), 0,
-                             Hkv * 8, it.n_splits, part.launch);
-    };
-    DecodeItem it;
-    int32_t item, g;
+    const Announcements words(Shared(part.words + (int64_t)it.first_item * Hkv + g, (uint32_t)it.n_splits * Hkv * 8), 0, Hkv * 8,
+                              it.n_splits, part.launch);
     wait_stores();
     __syncthreads();
-    for (int32_t k = wave; k < n_pairs; k += kDecodeWaves)
-        if (piece_of(k, it, item, g)) words_of(it, g).announce(item - it.first_item);
-    wait_stores();
-    for (int32_t k = wave; k < n_pairs; k += kDecodeWaves) {
-        const bool last = piece_of(k, it, item, g) && words_of(it, g).all();
-        if ((threadIdx.x & 63) == 0) lds.last[k] = last;
+    if (wave == 0) {
+        words.announce(item - it.first_item);
+        wait_stores();
+        const bool last = words.all();
+        if ((threadIdx.x & 63) == 0) lds.last = last;
     }
     __syncthreads();
-    for (int32_t k = 0; k < n_pairs; ++k) {
-        if (!lds.last[k]) continue;
-        piece_of(k, it, item, g);
-        merge_pieces<D, E>(part.of_layer(layer, n_items, Hq, Hkv, D), it.first_item, it.n_splits, Hq, g, G,
-                           out + layer * next_q + (int64_t)it.token * Hq * D);
-        if (wave == 0) words_of(it, g).clear();
-    }
+    if (!lds.last) return;
+    merge_pieces<D, E>(part, it.first_item, it.n_splits, Hq, g, G, out + (int64_t)it.token * Hq * D);
+    if (wave == 0) words.clear();
 }
 
 }  // namespace cs

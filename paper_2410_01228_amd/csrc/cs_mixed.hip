@@ -79,27 +79,23 @@ __global__ __launch_bounds__(kPrefillThreads, 2) void mixed_kernel(
     } else {
         const uint32_t j = blockIdx.x - dec_first;
         const int32_t n_items = n_decode / ((uint32_t)layers * Hkv);
-        auto pair_at = [&](int32_t round) -> int32_t {
-            const uint32_t w = (uint32_t)round * dec_wgs + ((round & 1) ? dec_wgs - 1 - j : j);
-            return w < n_decode ? (int32_t)w : -1;
-        };
-        int32_t round = 0;
-        for (; (uint32_t)round * dec_wgs < n_decode; ++round) {
-            const int32_t w = pair_at(round);
-            if (w < 0) continue;
+        for (uint32_t base = 0, round = 0; base < n_decode; base += dec_wgs, ++round) {
+            const uint32_t w = base + ((round & 1) ? dec_wgs - 1 - j : j);
+            if (w >= n_decode) continue;
             int32_t item = w / Hkv;
             const int32_t g = w - item * Hkv, l = item / n_items;
             item -= l * n_items;
+            const DecodePartials mine = part.of_layer(l, n_items, Hkv * G, Hkv, D);
             // one page ahead, with loads the compiler can count (a workgroup that shares its CU
             // with a tile must stream by itself); a deeper queue only delays the tile's own
             // copies, which share the CU's memory pipeline
             decode_item<D, ItemsInArgs, E, 1, PS, true>(lds.decode, layer_base + l * next_layer, page_stride, num_pages, Hkv, G, block_tables,
                                            max_blocks, items, ctx_lens, cu_q_lens, q + l * next_q, out + l * next_q, scale_log2e,
-                                           part.of_layer(l, n_items, Hkv * G, Hkv, D), item, g);
+                                           mine, item, g);
+            // (in place only where every workgroup has one pair)
+            if (part.words) merge_in_place<D, E>(lds.decode, mine, items, item, g, ctx_lens, cu_q_lens, Hkv, G, out + l * next_q);
             __syncthreads();     // the next pair reuses the merge buffers
         }
-        if (part.words) merge_in_place<D, E>(lds.decode, part, items, pair_at, round, ctx_lens, cu_q_lens, Hkv, G, out,
-                                              n_items, next_q);
     }
 }
 

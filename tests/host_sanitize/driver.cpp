@@ -147,6 +147,15 @@ int main() {
             cs_batch b = make_batch(ctx, cu, 1 << 14);
             const cs::Plans& p = cs::plans_for(&b, sh[0], sh[1], sh[2]);
             CHECK(p.p.max_ranges > 1 && p.f.arrangement != 0 && p.p.merges_in_place == c.in_place);
+            // cut decode sequences: never where decode workgroups walk several pairs beside the tiles
+            for (int32_t mode = 2; mode <= 3; ++mode) {
+                cs_set_mixed_fusion(mode);
+                cs_set_decode_split_tokens(256);
+                const cs::Plans& forced = cs::plans_for(&b, sh[0], sh[1], sh[2]);
+                CHECK(forced.f.arrangement == (forced.d.in_args ? mode - 1 : 0) && (mode == 2 || !forced.d.merges_in_place));
+                cs_set_mixed_fusion(1);
+                cs_set_decode_split_tokens(0);
+            }
             ++checks;
         }
         cs_debug_set_cu_count(0);
