@@ -422,9 +422,9 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
     const double t_prefill = 4.0 * Hq * D * pairs / 1.0e15;
     const double decode_bytes = (double)d.decode_keys * 2 * Hkv * D * 2;
     const double t_decode = decode_bytes / 6.0e12;
-    // Behind the tiles, where nothing below says otherwise: one grid beats two kernels in a row by 2-38%
-    // over 30 mixes of all shapes, most of them small ones, whose two kernels are mostly start-up and
-    // tail.  Where the decode side is the smaller one (under 0.3 of the prefill time)
+    // Behind the tiles at least: one grid beats two kernels in a row wherever both kinds of work are
+    // there (over 30 mixes of all shapes by 2-38%, most with small ones, whose two kernels are mostly
+    // start-up and tail).  Where the decode side is the smaller one (under 0.3 of the prefill time)
     // the tiles alternate their issue priority as the prefill kernel's do; with a decode load of
     // equal weight behind them that costs more than it gains.
     f.arrangement = 1;
@@ -435,11 +435,6 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
     if (mode == 2 || (mode == 1 && D != 128)) return f;
     // While every workgroup has a slot at once there is nothing to arrange.
     if (mode == 1 && ((int64_t)p.num_slots * p.max_ranges + d.total_items) * Hkv * layers <= 2 * cus) return f;
-    // A sliver of prefill work (decode time over eight times the prefill time, tiles for at most half the
-    // CUs) is no reason to hold the decode side to one workgroup per CU: behind the tiles is 6% faster
-    // than beside in the geometric mean of 20 such mixes, the best 14%, the worst 2% slower (81 decodes of
-    // 2.54 GB + 2 x 23 tokens, 32/8 heads, 478 -> 431 us).  With more tiles than that either may win.
-    if (mode == 1 && t_decode > 8.0 * t_prefill && (int64_t)p.num_slots * Hkv * layers <= cus / 2) return f;
     bool beside = mode == 3;
     double t_beside = 0;                                               // the model's time of that arrangement as planned (0: not played)
     const int64_t tile_units = (int64_t)p.num_slots * p.max_ranges * layers;       // tiles x ranges: what the model plays
