@@ -393,6 +393,30 @@ static double play_tiles(const std::vector<float>& work, int32_t cus, double dec
     return end;
 }
 
+// How evenly the decode work of a fused grid comes out, in the mean of a CU: what the longest of the
+// decode workgroups beside the tiles walks (one per CU, the pairs dealt back and forth), and when the
+// last pair ends where two slots of every CU take the pairs in order, as behind the tiles.  (Items on
+// groups of CUs, one per kv head, as above.)
+static void play_pairs(const cs_batch* b, const DecodePlan& d, int32_t Hkv, int32_t layers, double* beside, double* behind) {
+    const int32_t groups = std::max(1, device_cus() / Hkv), n = d.total_items * layers;
+    std::vector<double> walked((size_t)groups, 0.0), ends(2 * (size_t)groups, 0.0);      // (ends: a heap, the earliest on top)
+    double sum = 0;
+    for (int32_t i = 0; i < n; ++i) {
+        const uint32_t w = d.arg_items.e[i % d.total_items];
+        const int32_t keys = b->h_ctx_lens[w & 0xffffu] + 1, piece = (int32_t)((w >> 16) & 0xffu), k = (int32_t)(w >> 24);
+        const int32_t chunk = k > 1 ? decode_chunk_keys(keys, k) : keys;
+        const double len = (double)(std::min<int64_t>(keys, (int64_t)(piece + 1) * chunk) - std::min<int64_t>(keys, (int64_t)piece * chunk));
+        const int32_t at = i % groups;
+        walked[(size_t)((i / groups) & 1 ? groups - 1 - at : at)] += len;
+        std::pop_heap(ends.begin(), ends.end(), std::greater<double>());
+        ends.back() += len;
+        std::push_heap(ends.begin(), ends.end(), std::greater<double>());
+        sum += len;
+    }
+    *beside = *std::max_element(walked.begin(), walked.end()) * groups / sum;
+    *behind = *std::max_element(ends.begin(), ends.end()) * 2 * groups / sum;
+}
+
 // The choice between "behind" and "beside" comes from playing both grids (play_tiles).  A tile
 // workgroup of n steps takes (n + 8) * 0.88 us (a 32-key step at head dim 128 beside another
 // tile).  Behind: the decode bytes flow at 6.5 TB/s times min(1, free slots / (1.56 CUs)) into
@@ -422,9 +446,9 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
     const double t_prefill = 4.0 * Hq * D * pairs / 1.0e15;
     const double decode_bytes = (double)d.decode_keys * 2 * Hkv * D * 2;
     const double t_decode = decode_bytes / 6.0e12;
-    // Behind the tiles at least: one grid beats two kernels in a row wherever both kinds of work are
-    // there (over 30 mixes of all shapes by 2-38%, most with small ones, whose two kernels are mostly
-    // start-up and tail).  Where the decode side is the smaller one (under 0.3 of the prefill time)
+    // Behind the tiles, where nothing below says otherwise: over 853 mixes of four model shapes two
+    // kernels in a row are 15% slower in the geometric mean than the better of the two grids, and more
+    // than 3% faster on 8 of them.  Where the decode side is the smaller one (under 0.3 of the prefill time)
     // the tiles alternate their issue priority as the prefill kernel's do; with a decode load of
     // equal weight behind them that costs more than it gains.
     f.arrangement = 1;
@@ -433,8 +457,23 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
     // (head dim 64 fits three workgroups per CU, both kinds already share CUs behind the tiles,
     // and beside wins on some mixes and loses on others: the choice there is not modelled)
     if (mode == 2 || (mode == 1 && D != 128)) return f;
-    // While every workgroup has a slot at once there is nothing to arrange.
-    if (mode == 1 && ((int64_t)p.num_slots * p.max_ranges + d.total_items) * Hkv * layers <= 2 * cus) return f;
+    // Few tiles leave most slots to the decode side, whichever way it is arranged, and the model below
+    // knows nothing of how evenly its pairs come out.  Beside streams about 4% faster (a decode workgroup
+    // has its CU's memory pipeline almost to itself), behind evens out what dealing the pairs cannot: so
+    // beside where its workgroups come out nearly even, or much evener than the slots behind.  Over the 853
+    // mixes (1-256 decodes of 40-32K keys, 1-8 chunks of 2-2600 tokens), off the faster of the two grids:
+    // the model alone 1.3% on average and more than 5% on 87; always behind for slivers of prefill work and
+    // for streams under 60 us 1.5% and 91; this rule 0.6% and 36.  (40/8 heads, 151 decodes of 3.73 GB +
+    // two chunks of 96 tiles: beside 549 us, behind 602; 28/4, 78 decodes of 1.43 GB + 68 tiles: 262, 249.)
+    // While every workgroup has a slot at once, beside must promise more.
+    const int64_t tile_wgs = (int64_t)p.num_slots * Hkv * layers;
+    const bool resident = ((int64_t)p.num_slots * p.max_ranges + d.total_items) * Hkv * layers <= 2 * cus;
+    const bool few = tile_wgs <= (layers * t_decode < 65e-6 ? cus : t_decode > 8.0 * t_prefill ? cus / 2 : 0);
+    if (mode == 1 && (resident || few)) {
+        double even_beside, even_behind;
+        play_pairs(b, d, Hkv, layers, &even_beside, &even_behind);
+        if (resident ? even_beside >= 0.65 * even_behind : even_beside >= 1.05 && even_beside >= 0.88 * even_behind) return f;
+    }
     bool beside = mode == 3;
     double t_beside = 0;                                               // the model's time of that arrangement as planned (0: not played)
     const int64_t tile_units = (int64_t)p.num_slots * p.max_ranges * layers;       // tiles x ranges: what the model plays
@@ -505,9 +544,7 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
                 t_whole = std::max(play_tiles(work, groups, t_dec, free_at, &started), t_dec);
                 // (the model's constants were fitted before the tiles took their priorities beside a
                 // decode load, which make that arrangement about 2% faster than it says)
-                // (a decode stream under 60 us is too few pairs per workgroup to even out: over 68 mixes
-                // behind is 4-12% faster there, whatever the model says)
-                beside = 0.98 * t_whole < t_behind && t_dec >= 60.0;
+                beside = 0.98 * t_whole < t_behind;
             }
             if (beside && mode != 1 && !work.empty()) t_whole = std::max(play_tiles(work, groups, t_dec, free_at, &started), t_dec);
             t_beside = t_whole;

@@ -363,6 +363,19 @@ def test_run_layers_checks_the_workspace_of_both_plans_before_anything_is_enqueu
     assert lib.cs_run_layers_workspace_bytes(ctypes.byref(b), 16, 33, Hkv, D) == 0
 
 
+@pytest.mark.parametrize("Hq,Hkv,decodes,chunks,want", [
+    (32, 8, [8191] * 128, [(0, 20)] * 2, 2),                      # pairs that deal out evenly
+    (64, 8, [8000] * 36, [(0, 8)], 2),                            # uneven, but the slots behind come out worse
+    (40, 8, [600 + 62 * i for i in range(56)], [(100, 250)] * 5, 2),      # more tiles than CUs: the model's word
+    (64, 8, [6000] * 40, [(10, 90)], 1),                          # all resident, uneven either way
+    (28, 4, [8797] * 9 + [4000] * 60, [(500, 40)] * 5, 1)])             # uneven either way
+def test_a_few_tiles_beside_decodes_that_deal_out_evenly(Hq, Hkv, decodes, chunks, want):
+    """A sliver of prefill work, or a short decode stream, does not by itself decide where the decode work
+    runs: how evenly its pairs come out in each arrangement does."""
+    b, keep = _batch(decodes + [c for c, _ in chunks], [1] * len(decodes) + [q for _, q in chunks], max_blocks=1 << 12)
+    assert cs.lib().cs_debug_mixed_arrangement(ctypes.byref(b), Hq, Hkv, 128) == want
+
+
 def test_announcements_of_partials_refuse_no_batch_the_static_scratch():
     """15 cut sequences whose partials all but fill the static scratch (67.07 MB of 67.11 MB): the words
     that announce partials to workgroups that merge in place would not fit beside them."""
