@@ -81,48 +81,64 @@ int launch_page_copy(const cs_kv_pool& pool, int32_t layer_begin, int32_t layer_
 // bytes, each in a line of its own, and the 2 KiB of V units that hold its 128 features (head dim
 // 128): 400 MB of lines for 50 MB of tokens, and on the way back as many partly written ones.  So
 // every line is asked for once and everything is in flight together: one wavefront per (token, kv
-// head, layer); a K lane moves one 16-byte unit, a V lane the 2-byte elements of features lane and
+// head or two of head dim 64, layer); a K lane moves one 16-byte unit, a V lane the 2-byte elements of features lane and
 // lane + 64 (consecutive lanes, consecutive units: 8 lines an instruction, where a lane that moved
-// 8 features touched 64 lines with each), K and V are loaded before either is stored, and all of
-// it bypasses the caches' retention (nontemporal).  256 tokens x 48 layers x 8 kv heads: gather 155
-// -> 75 us (5.4 TB/s of lines); the pair 289 -> 233 us.  What is left of the restore (155 us) is the
-// partly written lines: rewriting whole V units instead, which would not be safe beside another
-// writer of the unit, measured no faster.
+// 8 features touched 64 lines with each), and K and V are loaded before either is stored.  Only the staging
+// side streams past the caches: the lines of the page hold up to 16 neighbouring tokens, which meet in
+// the L2 (written past it, 2-byte elements cost a restore of neighbours 2-4 times as much).  Eight
+// elements a lane -> this, 1024 tokens x 48 layers x 8 kv heads, 1 / 4 / 15 neighbours a page: gather
+// 344 / 219 / 209 -> 342 / 134 / 115 us, restore 797 / 327 / 271 -> 805 / 163 / 139 us.
 // ------------------------------------------------------------------------------------
 constexpr int kTokenCopyThreads = 64;
 
 template <bool kToStaging, int D>
 __global__ __launch_bounds__(kTokenCopyThreads) void token_copy_kernel(
     uint16_t* __restrict__ pool_base, int64_t layer_stride, int64_t page_stride,
-    int32_t num_pages, int32_t layer_begin, const int32_t* __restrict__ token_slots, int32_t n, int32_t first,
-    uint16_t* __restrict__ staging, int32_t Hkv, int32_t page_shift)
+    int32_t num_pages, int32_t layer_begin, const int32_t* __restrict__ token_slots, int32_t n, int32_t first, int32_t end,
+    uint16_t* __restrict__ staging, int32_t Hkv, int32_t page_shift, int32_t streams)
 {
-    const int32_t h = blockIdx.x % Hkv, i = first + blockIdx.x / Hkv, l = blockIdx.y, lane = threadIdx.x;
+    constexpr int kHeads = 128 / D;                              // kv heads of a wavefront: as much work at head dim 64 as at 128
+    constexpr int kVPerLane = D / 64;
+    // Workgroup x runs on XCD x % 8: with fewer than 8 of them a token the list is walked in `streams` parts at
+    // once, so that the next token of the list, often a neighbour in the page, is on the same XCD's L2.
+    const int32_t per_token = (Hkv + kHeads - 1) / kHeads, hs = per_token * streams, part = (end - first + streams - 1) / streams;
+    const int32_t h0 = (int32_t)(blockIdx.x % per_token) * kHeads, l = blockIdx.y, lane = threadIdx.x;
+    const int32_t i = first + (int32_t)(blockIdx.x % hs) / per_token * part + (int32_t)(blockIdx.x / hs);
+    if (i >= end) return;
     const int32_t slot = token_slots[i];
     const int32_t page = slot >> page_shift, t = slot & ((1 << page_shift) - 1);
     if (slot < 0 || page >= num_pages) return;                   // never touch a bad slot
     const int32_t block_elems = D << page_shift;                 // one kv head's K (or V) block
-    uint16_t* kblk = pool_base + (int64_t)(layer_begin + l) * layer_stride + (int64_t)page * page_stride + (int64_t)h * block_elems;
+    uint16_t* kblk = pool_base + (int64_t)(layer_begin + l) * layer_stride + (int64_t)page * page_stride + (int64_t)h0 * block_elems;
     uint16_t* vblk = kblk + (int64_t)Hkv * block_elems;
-    uint16_t* krow = staging + (((int64_t)l * n + i) * 2 * Hkv + h) * D;
+    uint16_t* krow = staging + (((int64_t)l * n + i) * 2 * Hkv + h0) * D;
     uint16_t* vrow = krow + Hkv * D;
     // feature d of token t: K unit (d/8) * page tokens + t; V element
     // (((d/16)*groups + t/8)*16 + d%16)*8 + t%8, groups = page tokens / 8: 64 features further on is
-    // 4 * groups * 128 elements further on
-    constexpr int kVPerLane = D / 64;
-    u32x4* kp = (u32x4*)(kblk + ((lane << page_shift) + t) * 8);
+    // 4 * groups * 128 elements further on.  (The heads' rows of the staging side follow each other.)
+    const int32_t unit = lane & (D / 8 - 1), kh = lane / (D / 8);
+    const bool has_k = kh < kHeads && h0 + kh < Hkv;
+    u32x4* kp = (u32x4*)(kblk + kh * block_elems + ((unit << page_shift) + t) * 8);
     uint16_t* vp = vblk + ((lane >> 4) << (page_shift + 4)) + ((t >> 3) << 7) + ((lane & 15) << 3) + (t & 7);
     u32x4* ks = (u32x4*)krow + lane;
     u32x4 k;
-    uint16_t v[kVPerLane];
-    if (lane < D / 8) k = __builtin_nontemporal_load(kToStaging ? kp : ks);
+    uint16_t v[kHeads * kVPerLane];
+    if (has_k) k = kToStaging ? *kp : __builtin_nontemporal_load(ks);
 #pragma unroll
-    for (int j = 0; j < kVPerLane; ++j)
-        v[j] = __builtin_nontemporal_load(kToStaging ? vp + (j << (page_shift + 6)) : vrow + lane + j * 64);
-    if (lane < D / 8) __builtin_nontemporal_store(k, kToStaging ? ks : kp);
+    for (int j = 0; j < kHeads * kVPerLane; ++j) {
+        if (h0 + j / kVPerLane >= Hkv) break;
+        uint16_t* p = vp + j / kVPerLane * block_elems + (j % kVPerLane << (page_shift + 6));
+        v[j] = kToStaging ? *p : __builtin_nontemporal_load(vrow + lane + j * 64);
+    }
+    if (has_k) {
+        if constexpr (kToStaging) __builtin_nontemporal_store(k, ks); else *kp = k;
+    }
 #pragma unroll
-    for (int j = 0; j < kVPerLane; ++j)
-        __builtin_nontemporal_store(v[j], kToStaging ? vrow + lane + j * 64 : vp + (j << (page_shift + 6)));
+    for (int j = 0; j < kHeads * kVPerLane; ++j) {
+        if (h0 + j / kVPerLane >= Hkv) break;
+        uint16_t* p = vp + j / kVPerLane * block_elems + (j % kVPerLane << (page_shift + 6));
+        if constexpr (kToStaging) __builtin_nontemporal_store(v[j], vrow + lane + j * 64); else *p = v[j];
+    }
 }
 
 int launch_token_copy(const cs_kv_pool& pool, int32_t layer_begin, int32_t layer_end,
@@ -132,14 +148,16 @@ int launch_token_copy(const cs_kv_pool& pool, int32_t layer_begin, int32_t layer
     if (n == 0 || layers == 0) return CS_OK;
     const int32_t page_shift = pool.page_size == 16 ? 4 : 3;
     // (a launch holds fewer than 2^32 lanes along x: more tokens than that go in several)
-    const int32_t max_tokens = 0x3ffffff / pool.num_kv_heads;
+    const int32_t per_token = pool.head_dim == 128 ? pool.num_kv_heads : (pool.num_kv_heads + 1) / 2;
+    const int32_t streams = per_token < 8 && 8 % per_token == 0 ? 8 / per_token : 1;
+    const int32_t max_tokens = 0x3ffffff / per_token / streams * streams;
 #define CS_LAUNCH_TOKEN_COPY(DIR, DD)                                                                            \
     hipLaunchKernelGGL((token_copy_kernel<DIR, DD>), grid, dim3(kTokenCopyThreads), 0, st, (uint16_t*)pool.base,   \
-                       pool.layer_stride, pool.page_stride, pool.num_pages, layer_begin, token_slots, n, first,   \
-                       (uint16_t*)staging, pool.num_kv_heads, page_shift);
+                       pool.layer_stride, pool.page_stride, pool.num_pages, layer_begin, token_slots, n, first, first + m, \
+                       (uint16_t*)staging, pool.num_kv_heads, page_shift, streams);
     for (int32_t first = 0, m; first < n; first += m) {
         m = n - first < max_tokens ? n - first : max_tokens;
-        const dim3 grid((uint32_t)m * pool.num_kv_heads, (uint32_t)layers);
+        const dim3 grid((uint32_t)((m + streams - 1) / streams) * streams * per_token, (uint32_t)layers);
         if (pool.head_dim == 128) { if (to_staging) { CS_LAUNCH_TOKEN_COPY(true, 128) } else { CS_LAUNCH_TOKEN_COPY(false, 128) } }
         else                      { if (to_staging) { CS_LAUNCH_TOKEN_COPY(true, 64) } else { CS_LAUNCH_TOKEN_COPY(false, 64) } }
     }
