@@ -6,8 +6,8 @@
 #include "cs_common.h"
 #include "cs_plan.h"
 #include <atomic>
+#include <chrono>
 #include <functional>
-#include <random>
 #include <vector>
 #include <string.h>
 #include <stdio.h>
@@ -649,8 +649,10 @@ static bool tiles_merge_in_place(const DecodePlan& d, const PrefillPlan& p, cons
 }
 
 uint64_t next_launch_number() {
-    static std::atomic<uint64_t> next{((uint64_t)std::random_device{}() << 24) + 1};    // 56 bits
-    const uint64_t n = next.fetch_add(1, std::memory_order_relaxed) & 0xffffffffffffffull;
+    // (from the clock and where the loader put the library, spread over 64 bits: std::random_device may throw)
+    static std::atomic<uint64_t> next{((uint64_t)std::chrono::system_clock::now().time_since_epoch().count() ^ (uint64_t)(uintptr_t)&g_forced_split) *
+                                      0x9e3779b97f4a7c15ull};
+    const uint64_t n = next.fetch_add(1, std::memory_order_relaxed);
     return n ? n : next_launch_number();
 }
 

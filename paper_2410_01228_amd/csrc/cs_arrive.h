@@ -9,8 +9,8 @@
 // as a whole (agent-scope fences instead took 20 times as long on a grid of small workgroups).
 //
 // An announcement is a 64-bit word per partial, in scratch memory that nobody clears beforehand; it
-// holds the launch's number (next_launch_number: never used twice in a process, starting at a random
-// point, so whatever the memory held before is no announcement).  A workgroup stores its word, waits
+// holds the launch's number (next_launch_number: never used twice in a process, starting at an
+// arbitrary point, so whatever the memory held before is no announcement).  A workgroup stores its word, waits
 // for the acknowledgement, and reads all of them: the one whose store came last sees every word.
 // Two that see every word both merge, in the same order, and write the same bits.  Whoever merges sets the words to
 // zero again, so a launch replayed from a graph (with the same number) starts clean.  (Counting

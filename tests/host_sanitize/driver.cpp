@@ -9,6 +9,8 @@
 #include <algorithm>
 #include <cstdlib>
 #include <random>
+#include <stdexcept>
+#include <string>
 #include <vector>
 #include "conserve_kv.h"
 #include "cs_plan.h"
@@ -28,6 +30,9 @@ static cs_batch make_batch(const std::vector<int32_t>& ctx, const std::vector<in
     b.h_cu_q_lens = cu.data();
     return b;
 }
+
+// A machine without a source of randomness: nothing behind the C interface may throw for it.
+void std::random_device::_M_init(const std::string&) { throw std::runtime_error("no random device"); }
 
 // One iteration over `layers` layers, not preempted, through the stand-ins.
 static int iterate(const cs_batch& b, const int* sh, int32_t layers, const void* workspace, size_t bytes, int32_t check_every) {
@@ -49,6 +54,7 @@ static int iterate(const cs_batch& b, const int* sh, int32_t layers, const void*
 int main() {
     std::mt19937 rng(12345);
     long checks = 0;
+    for (int i = 0; i < 100; ++i) CHECK(cs::next_launch_number() != cs::next_launch_number());
     // ---- launch plans over random batches, three chip sizes, all shapes ----
     const int shapes[][3] = {{32, 8, 128}, {28, 4, 128}, {64, 8, 128}, {40, 8, 128}, {4, 2, 64}, {16, 1, 64}};
     std::vector<uint32_t> items(1024);
