@@ -463,16 +463,19 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
     // beside where its workgroups come out nearly even, or much evener than the slots behind.  Over the 853
     // mixes (1-256 decodes of 40-32K keys, 1-8 chunks of 2-2600 tokens), off the faster of the two grids:
     // the model alone 1.3% on average and more than 5% on 87; always behind for slivers of prefill work and
-    // for streams under 60 us 1.5% and 91; this rule 0.6% and 36.  (40/8 heads, 151 decodes of 3.73 GB +
+    // for streams under 60 us 1.5% and 91; this rule 0.7% and 41.  (40/8 heads, 151 decodes of 3.73 GB +
     // two chunks of 96 tiles: beside 549 us, behind 602; 28/4, 78 decodes of 1.43 GB + 68 tiles: 262, 249.)
-    // While every workgroup has a slot at once, beside must promise more.
+    // While every workgroup has a slot at once, or the stream is short, beside must promise more (24
+    // decodes of 200-2900 keys + 200 tokens, 32/8 heads: evenness 1.41 and 1.61, 43 us beside, 39 behind).
     const int64_t tile_wgs = (int64_t)p.num_slots * Hkv * layers;
     const bool resident = ((int64_t)p.num_slots * p.max_ranges + d.total_items) * Hkv * layers <= 2 * cus;
-    const bool few = tile_wgs <= (layers * t_decode < 65e-6 ? cus : t_decode > 8.0 * t_prefill ? cus / 2 : 0);
+    const bool brief = layers * t_decode < 65e-6;
+    const bool few = tile_wgs <= (brief ? cus : t_decode > 8.0 * t_prefill ? cus / 2 : 0);
     if (mode == 1 && (resident || few)) {
         double even_beside, even_behind;
         play_pairs(b, d, Hkv, layers, &even_beside, &even_behind);
-        if (resident ? even_beside >= 0.65 * even_behind : even_beside >= 1.05 && even_beside >= 0.88 * even_behind) return f;
+        const double much_evener = resident ? 0.65 : brief ? 0.8 : 0.88;
+        if (even_beside >= much_evener * even_behind && (resident || even_beside >= 1.05)) return f;
     }
     bool beside = mode == 3;
     double t_beside = 0;                                               // the model's time of that arrangement as planned (0: not played)
