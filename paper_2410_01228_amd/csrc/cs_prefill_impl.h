@@ -633,35 +633,55 @@ __device__ __forceinline__ void prefill_tile(
             auto row_of = [&](int r, int c) -> uint32_t {
                 return (uint32_t)r * kRangeBytes + ((wave * kNCT + c) * 16 + (lane & 15)) * (kPartRow * 4);
             };
-            for (int r0 = 0; r0 < n_ranges; r0 += 8) {            // (past the last range: the last again)
-                a_u32x2 ml[8][kNCT];
+            a_u32x2 ml[kNCT];
+            f32x4 v[kNCT][D / 16];
+            auto fetch = [&](int r) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
+                for (int c = 0; c < kNCT; ++c) {
+                    const uint32_t row = row_of(r, c);
+                    ml[c] = part.load2(row + D * 4);
 #pragma unroll
-                    for (int c = 0; c < kNCT; ++c) ml[j][c] = part.load2(row_of(min(r0 + j, n_ranges - 1), c) + D * 4);
+                    for (int dt = 0; dt < D / 16; ++dt) v[c][dt] = __builtin_bit_cast(f32x4, part.load4(row + (dt * 16 + (lane >> 4) * 4) * 4));
+                }
+            };
+            if (n_ranges == 2) {                                  // one trip to memory for the other's maximum and sums
+                fetch(1 - range);
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
+                for (int c = 0; c < kNCT; ++c) {
+                    M[c] = fmaxf(M[c], as_float(ml[c][0]));
+                    const float mine = exp2f(m_run[c] - M[c]), other = exp2f(as_float(ml[c][0]) - M[c]);
+                    const float f0 = range == 0 ? mine : other, f1 = range == 0 ? other : mine;
+                    auto both = [&](float own, float theirs) {
+                        return __builtin_fmaf(range == 0 ? theirs : own, f1, __builtin_fmaf(range == 0 ? own : theirs, f0, 0.f));
+                    };
+                    L[c] = both(lacc[c][0], as_float(ml[c][1]));
 #pragma unroll
-                    for (int c = 0; c < kNCT; ++c)
-                        M[c] = fmaxf(M[c], min(r0 + j, n_ranges - 1) == range ? m_run[c] : as_float(ml[j][c][0]));
-            }
-            for (int r = 0; r < n_ranges; ++r) {
-                if (r == range) {
+                    for (int dt = 0; dt < D / 16; ++dt)
 #pragma unroll
-                    for (int c = 0; c < kNCT; ++c) add(c, m_run[c], lacc[c][0], o[c]);
-                } else {
-                    a_u32x2 ml[kNCT];
-                    f32x4 v[kNCT][D / 16];
+                        for (int e = 0; e < 4; ++e) sum[c][dt][e] = both(o[c][dt][e], v[c][dt][e]);
+                }
+            } else {
+                for (int r0 = 0; r0 < n_ranges; r0 += 4) {        // (past the last range: the last again)
+                    a_u32x2 m4[4][kNCT];
 #pragma unroll
-                    for (int c = 0; c < kNCT; ++c) {
-                        const uint32_t row = row_of(r, c);
-                        ml[c] = part.load2(row + D * 4);
+                    for (int j = 0; j < 4; ++j)
 #pragma unroll
-                        for (int dt = 0; dt < D / 16; ++dt)
-                            v[c][dt] = __builtin_bit_cast(f32x4, part.load4(row + (dt * 16 + (lane >> 4) * 4) * 4));
+                        for (int c = 0; c < kNCT; ++c) m4[j][c] = part.load2(row_of(min(r0 + j, n_ranges - 1), c) + D * 4);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int c = 0; c < kNCT; ++c)
+                            M[c] = fmaxf(M[c], min(r0 + j, n_ranges - 1) == range ? m_run[c] : as_float(m4[j][c][0]));
+                }
+                for (int r = 0; r < n_ranges; ++r) {
+                    if (r == range) {
+#pragma unroll
+                        for (int c = 0; c < kNCT; ++c) add(c, m_run[c], lacc[c][0], o[c]);
+                    } else {
+                        fetch(r);
+#pragma unroll
+                        for (int c = 0; c < kNCT; ++c) add(c, as_float(ml[c][0]), as_float(ml[c][1]), v[c]);
                     }
-#pragma unroll
-                    for (int c = 0; c < kNCT; ++c) add(c, as_float(ml[c][0]), as_float(ml[c][1]), v[c]);
                 }
             }
 #pragma unroll
