@@ -32,3 +32,20 @@ def test_traffic_stays_close_to_the_algorithmic_bytes_of_the_decode_workload():
     dec_bytes, _, _ = bench.attention_work(b)
     _, traffic = bench.read_traffic("llama8b_decode", bench.KERNEL_OF[("llama8b_decode", "paged_attention_mixed")][0])
     assert 0.98 < traffic / dec_bytes < 1.05, traffic / dec_bytes
+
+
+def test_summaries_list_kernels_that_the_library_has():
+    """Every kernel of every table, with all its template arguments: a summary taken before a kernel was
+    removed or re-instantiated fails here, where a row's first characters might still match."""
+    import glob
+    import re
+    import subprocess
+    from paper_2410_01228_amd import binding
+    names = subprocess.run(["nm", "-C", binding.LIB_PATH], check=True, capture_output=True, text=True).stdout
+    have = set(re.findall(r"cs::__device_stub__(\w+(?:<[^()]*>)?)\(", names))
+    assert have
+    for path in glob.glob(os.path.join(ROOT, "profiles", "*.txt")):
+        for line in open(path):
+            row = re.match(r"cs::(\w+(?:<.*?>)?)\s{2,}\d", line)
+            if row:
+                assert row.group(1) in have, (os.path.basename(path), row.group(1))
