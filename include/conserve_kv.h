@@ -13,8 +13,9 @@
  *     cs_set_decode_split_tokens / cs_set_decode_pages_ahead / cs_set_mixed_fusion /
  *     cs_debug_set_cu_count / cs_debug_set_tail_cut, which are process-wide, change launch plans and workspace sizes,
  *     and are meant for benchmarks and tests only (a serving process leaves them alone); and,
- *     invisible to the caller, each thread's memo of the last launch plans it made and each
- *     device's compute-unit count, asked once;
+ *     invisible to the caller, each thread's memo of the last launch plans it made, each
+ *     device's compute-unit count, asked once, and a process-wide count of launches, whose
+ *     numbers tell a launch's marks in the workspace from whatever lay there before;
  *   - every pointer is owned by the caller and must stay valid until the enqueued work has
  *     run.  "device" pointers are HIP device memory of the current device, "host" pointers
  *     are ordinary host memory read during the call only;
@@ -123,7 +124,8 @@ int cs_kv_append(const cs_kv_pool* pool, int32_t layer, const cs_batch* batch,
                  const void* k_new, const void* v_new, void* stream);
 
 /* Workspace the attention call needs for this batch: the fp32 partial results of decode
- * sequences cut into work items and of prefill tiles cut into key ranges (the launch plan is
+ * sequences cut into work items and of prefill tiles cut into key ranges, and marks that tell
+ * workgroups which of them are there (the launch plan is
  * made here from the host arrays of `batch` and the shape, and again, identically, in the
  * attention call, which finds it remembered).  Zero for many batches; a few MB to a few hundred
  * MB when chunks of up to a few thousand tokens are cut to fill the chip.  Returns 0 on bad
@@ -259,9 +261,9 @@ typedef struct {
  * Between two safepoints up to four layers share an append launch where no layer's output overlaps
  * another layer's output or any input (layers that share or chain buffers run one after the other; a
  * layer's q may be its own out), and share an attention launch as far as the workspace holds the
- * partial results of all of them: bringing up to four times the query's size makes batches
- * with cut sequences or chunks faster.  Neither changes a bit: every layer's results are those
- * of the two calls. */
+ * partial results of all of them: with 4 1/8 times the query's size + 256 bytes all four do, which
+ * batches with cut sequences or chunks gain from.  Neither changes a bit: every layer's results
+ * are those of the two calls. */
 int cs_run_layers(const cs_kv_pool* pool, int32_t layer_begin, int32_t layer_end, const cs_batch* batch,
                   const void* q, const void* k_new, const void* v_new, void* out,
                   int64_t q_layer_stride, int64_t kv_layer_stride,

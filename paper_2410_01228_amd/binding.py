@@ -437,6 +437,8 @@ def cs_run_layers_workspace_bytes(batch: Batch, num_online_seqs: int, Hq: int, H
 
 def run_layers_workspace_for(batch: Batch, num_online_seqs: int, Hq: int, Hkv: int, D: int, device="cuda") -> torch.Tensor:
     n = cs_run_layers_workspace_bytes(batch, num_online_seqs, Hq, Hkv, D)
+    if n:                                               # room for the four layers that share a launch, if that is little
+        n = max(n, min(4 * n + n // 8 + 256, 64 << 20))
     return torch.empty(max(n, 16), dtype=torch.uint8, device=device)
 
 

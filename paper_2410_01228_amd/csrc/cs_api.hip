@@ -423,8 +423,7 @@ static void play_pairs(const cs_batch* b, const DecodePlan& d, int32_t Hkv, int3
 // the slots the tiles have left for good.  Beside: one slot per CU is a decode workgroup's until
 // all bytes have passed at 6.5 TB/s.  Over 196 mixes of four model shapes, the arrangement this
 // model takes is on average 0.0-0.7% (per shape) slower than the fastest of the three by
-// measurement, 8% at worst (always behind: 3-8% on average, always beside: 2-6%); the merges of
-// cut tiles and cut sequences cost the same either way.
+// measurement, 8% at worst (always behind: 3-8% on average, always beside: 2-6%).
 //
 // Beside the tiles, the tiles of the last round are cut (p is changed): a tile that starts when
 // the decode side is about done runs alone on its CU, one wavefront per SIMD, while the slot the
@@ -566,6 +565,8 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
                     // are taken over two unless the model has them 6% behind: measured over the
                     // long-tile mixes they are 2% ahead where it calls them 2-5% behind.
                     double t_r[4] = {0, 0, 0, 0};
+                    // (The price of the partials is that of a merge kernel behind the grid, with which the
+                    // bar was fitted; the grid's own merge costs less.)
                     for (int32_t r = 2; r <= 3 && tail_steps / r >= 128; ++r) {
                         const int32_t rs = (tail_steps + r - 1) / r, ranges = (tail_steps + rs - 1) / rs;
                         list_work(whole, rs, ranges);

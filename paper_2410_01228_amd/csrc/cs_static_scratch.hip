@@ -1,7 +1,8 @@
 // cs_paged_attention_mixed_static: the attention call for callers that cannot allocate device
 // memory (code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc).
-// The workspace of cs_paged_attention_mixed -- the decode work-item list and the fp32 partial
-// results of cut decode sequences and of prefill tiles cut into key ranges -- comes from one
+// The workspace of cs_paged_attention_mixed -- the decode work-item list or the announcements of
+// partials, and the fp32 partial results of cut decode sequences and of prefill tiles cut into key
+// ranges -- comes from one
 // file-scope device array instead of the caller.  Each device the library runs on holds its own
 // copy of the array, at its own address, until the process ends.
 #include <atomic>
@@ -54,9 +55,10 @@ int cs_paged_attention_mixed_static(const cs_kv_pool* pool, int32_t layer, const
         const int rc = cs::static_scratch(&ws);
         if (rc) return rc;
     }
-    // Nothing in the scratch has to start at zero: every word a kernel of this call reads (item
-    // list, partial maxima, sums and outputs) is written earlier in the same call, on the same
-    // stream.  So there is no clearing, and what the previous call left is simply overwritten.
+    // Nothing in the scratch has to start at zero: the item list and the partial maxima, sums and
+    // outputs are read only once they have been written in the same call, and the words that announce
+    // partials hold the launch's own number, which nothing that lies there from before does.  So there is
+    // no clearing, and what the previous call left is simply overwritten.
     return cs_paged_attention_mixed(pool, layer, batch, q, out, num_q_heads, softmax_scale,
                                     ws, need > 0 ? (size_t)CS_STATIC_SCRATCH_BYTES : 0, stream);
 }

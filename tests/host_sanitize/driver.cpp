@@ -122,6 +122,8 @@ int main() {
                 const cs::Plans& many = cs::plans_for(&b, sh[0], sh[1], sh[2], n);
                 CHECK(many.need <= cs::workspace_for_layers(&b, sh[0], sh[1], sh[2], n));
                 CHECK((cs::workspace_for_layers(&b, sh[0], sh[1], sh[2], n) == 0) == (one.need == 0));
+                // (what the header advises to bring)
+                CHECK(cs::workspace_for_layers(&b, sh[0], sh[1], sh[2], n) <= n * one.need + one.need / 8 + 256);
                 CHECK(many.d.split_tokens == one.d.split_tokens && many.d.total_items == one.d.total_items && many.d.num_multi == one.d.num_multi);
                 CHECK(std::equal(one.d.arg_items.e, one.d.arg_items.e + (one.d.in_args ? one.d.total_items : 0), many.d.arg_items.e));
                 CHECK(many.p.range_steps == one.p.range_steps && many.p.max_ranges == one.p.max_ranges);
