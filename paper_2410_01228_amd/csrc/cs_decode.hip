@@ -50,9 +50,11 @@ __global__ __launch_bounds__(kPlanThreads) void decode_plan_kernel(
 
 // grid = (items * Hkv, layers) workgroups, kv head fastest (the heads of one page are neighbours
 // in memory, so neighbouring workgroups share DRAM pages and translations).
-// kMerge: cut sequences are merged in place.  (Launches that do not have the code at their end run
-// pages of 8 tokens 5% faster: 137 sequences of 47-349 keys, 64/8 heads, 27.0 -> 25.6 us.)
-template <int D, class Src, class E, int kAhead, int PS, bool kMerge>
+// kCut: a list in the arguments that holds pieces, which part.words may ask to merge in place.  (Launches
+// without cuts run pages of 8 tokens 4% faster without that code: 137 sequences of 47-349 keys, 64/8 heads,
+// 27.0 -> 26.1 us.  Cut lists that a kernel merges are faster with it: 64 of 1K-8K keys, 28/4 heads, the
+// append included, 112.7 -> 109.4 us.)
+template <int D, class Src, class E, int kAhead, int PS, bool kCut>
 __global__ __launch_bounds__(kDecodeThreads, 2) void decode_split_kernel(
     const uint16_t* __restrict__ layer_base, int64_t page_stride, int32_t num_pages,
     int32_t Hkv, int32_t G,
@@ -68,7 +70,9 @@ __global__ __launch_bounds__(kDecodeThreads, 2) void decode_split_kernel(
     out += blockIdx.y * next_q;
     decode_item<D, Src, E, kAhead, PS>(lds, layer_base + blockIdx.y * next_layer, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
                            cu_q_lens, q + blockIdx.y * next_q, out, scale_log2e, mine, item, g);
-    if constexpr (kMerge) merge_in_place<D, E>(lds, mine, src, item, g, ctx_lens, cu_q_lens, Hkv, G, out);
+    if constexpr (kCut) {
+        if (part.words) merge_in_place<D, E>(lds, mine, src, item, g, ctx_lens, cu_q_lens, Hkv, G, out);
+    }
 }
 
 // Merge of the partials of the cut sequences where the workgroups do not do it themselves: grid as
@@ -101,22 +105,22 @@ static int launch_decode_as(const cs_kv_pool& pool, int32_t layer, const LayerSp
                                  in_place ? next_launch_number() : 0};
     const uint32_t n_items = plan.in_args || cut ? plan.total_items : b.num_seqs;
     dim3 grid(n_items * (uint32_t)Hkv, (uint32_t)span.n);
-#define CS_LAUNCH_DECODE_P(DD, SRC, src, AH, PS, MERGE)                                                        \
-    hipLaunchKernelGGL((decode_split_kernel<DD, SRC, E, AH, PS, MERGE>), grid, dim3(kDecodeThreads), 0, st, layer_base, \
+#define CS_LAUNCH_DECODE_P(DD, SRC, src, AH, PS, CUT)                                                        \
+    hipLaunchKernelGGL((decode_split_kernel<DD, SRC, E, AH, PS, CUT>), grid, dim3(kDecodeThreads), 0, st, layer_base, \
                        pool.page_stride, pool.num_pages, Hkv, G, b.block_tables, b.max_blocks_per_seq, \
                        src, b.ctx_lens, b.cu_q_lens, (const uint16_t*)q, (uint16_t*)out,               \
                        scale_log2e, part, span.pool, span.q);
-#define CS_LAUNCH_DECODE_A(DD, SRC, src, AH, MERGE)                                                            \
-    if (pool.page_size == 16) { CS_LAUNCH_DECODE_P(DD, SRC, src, AH, 16, MERGE) } else { CS_LAUNCH_DECODE_P(DD, SRC, src, AH, 8, MERGE) }
-#define CS_LAUNCH_DECODE(DD, SRC, src, MERGE)                                                                 \
-    if (plan.pages_ahead == 2) { CS_LAUNCH_DECODE_A(DD, SRC, src, 2, MERGE) } else { CS_LAUNCH_DECODE_A(DD, SRC, src, 1, MERGE) }
-#define CS_LAUNCH_MERGE(DD, SRC, src)                                                                  \
+#define CS_LAUNCH_DECODE_A(DD, SRC, src, AH, CUT)                                                            \
+    if (pool.page_size == 16) { CS_LAUNCH_DECODE_P(DD, SRC, src, AH, 16, CUT) } else { CS_LAUNCH_DECODE_P(DD, SRC, src, AH, 8, CUT) }
+#define CS_LAUNCH_DECODE(DD, SRC, src, CUT)                                                                 \
+    if (plan.pages_ahead == 2) { CS_LAUNCH_DECODE_A(DD, SRC, src, 2, CUT) } else { CS_LAUNCH_DECODE_A(DD, SRC, src, 1, CUT) }
+#define CS_LAUNCH_MERGE(DD, SRC, src)                                                                       \
     hipLaunchKernelGGL((decode_merge_kernel<DD, SRC, E>), grid, dim3(kDecodeThreads), 0, st, Hkv, G, src, b.ctx_lens, \
                        b.cu_q_lens, (uint16_t*)out, part, span.q);
     if (plan.in_args) {
         // (merge_only: the fused mixed-batch kernel has already done the items' work)
         if (!merge_only) {
-            if (in_place) {
+            if (cut) {
                 if (D == 128) { CS_LAUNCH_DECODE(128, ItemsInArgs, plan.arg_items, true) } else { CS_LAUNCH_DECODE(64, ItemsInArgs, plan.arg_items, true) }
             } else {
                 if (D == 128) { CS_LAUNCH_DECODE(128, ItemsInArgs, plan.arg_items, false) } else { CS_LAUNCH_DECODE(64, ItemsInArgs, plan.arg_items, false) }
