@@ -85,8 +85,10 @@ int launch_page_copy(const cs_kv_pool& pool, int32_t layer_begin, int32_t layer_
 // lane + 64 (consecutive lanes, consecutive units: 8 lines an instruction, where a lane that moved
 // 8 features touched 64 lines with each), and K and V are loaded before either is stored.  Only the staging
 // side streams past the caches: the lines of the page hold up to 16 neighbouring tokens, which meet in
-// the L2 (written past it, 2-byte elements cost a restore of neighbours 2-4 times as much).  Eight
-// elements a lane -> this, 1024 tokens x 48 layers x 8 kv heads, 1 / 4 / 15 neighbours a page: gather
+// the L2 (written past it, 2-byte elements cost a restore of neighbours 2-4 times as much; of tokens alone in
+// their pages 1.5-2.3 times up to 300 MB of lines, which the last-level cache holds, and 0.8 from 500 MB on:
+// streaming those alone was measured, by a look at 64 tokens of the list, and made shuffled neighbours 2.5 times
+// as slow).  Eight elements a lane -> this, 1024 tokens x 48 layers x 8 kv heads, 1 / 4 / 15 neighbours a page: gather
 // 344 / 219 / 209 -> 342 / 134 / 115 us, restore 797 / 327 / 271 -> 805 / 163 / 139 us.
 // ------------------------------------------------------------------------------------
 constexpr int kTokenCopyThreads = 64;
