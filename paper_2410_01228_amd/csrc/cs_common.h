@@ -59,6 +59,36 @@ __host__ __device__ inline int64_t prefill_slot_start(int32_t cu_q, int32_t s, i
     return ((int64_t)cu_q + 16ll * s) * G / (16 * kTileCols) + s;
 }
 
+#ifdef __HIPCC__
+// A sequence, its first packed token, number of new tokens and cached tokens.
+struct OwnedBy { int32_t seq, token, q_len, ctx; };
+
+// The last of the sequences first .. first + n - 1 whose start (start_of(cu_q_lens[s], s), strictly
+// increasing) does not lie behind `at`; the first of them if all do.  By the 64 lanes of a wavefront, each
+// of which tries one sequence: one trip to memory for up to 64 sequences, which brings the lengths
+// along, two for up to 4096, where a bisection takes a dependent load for every power of two and
+// another for the lengths.  (Two chunks + four decodes of 17-100 keys, 4/2 heads, D 64: append + attention
+// 11.3 -> 10.9 us; 64 decodes + four 256-token chunks, 40/8 heads: 186.7 -> 185.5.)
+template <class StartOf>
+__device__ __forceinline__ OwnedBy owner_of(const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ ctx_lens,
+                                            int32_t first, int32_t n, int32_t at, StartOf start_of)
+{
+    const int32_t lane = threadIdx.x & 63;
+    while (n > 64) {
+        const int32_t stride = (n + 63) >> 6, i = min(lane * stride, n - 1);
+        const bool reached = lane * stride < n && start_of(cu_q_lens[first + i], first + i) <= at;
+        const int32_t k = max((int32_t)__popcll(__ballot(reached)), 1) - 1;
+        first += k * stride;
+        n = min(stride, n - k * stride);
+    }
+    const int32_t i = first + min(lane, n - 1);
+    const int32_t t0 = cu_q_lens[i], t1 = cu_q_lens[i + 1], c = ctx_lens[i];
+    const int32_t k = max((int32_t)__popcll(__ballot(lane < n && start_of(t0, i) <= at)), 1) - 1;
+    const int32_t t = __builtin_amdgcn_readlane(t0, k);
+    return {first + k, t, __builtin_amdgcn_readlane(t1, k) - t, __builtin_amdgcn_readlane(c, k)};
+}
+#endif
+
 // Small batches carry their work-item list inside the kernel arguments: the host already has
 // the lengths, so it lists the items itself, longest first, and no planning kernel and no
 // host-to-device copy is needed.  One word per item: sequence (bits 0-15), piece (16-23),

@@ -225,15 +225,10 @@ __device__ __forceinline__ void append_page_block(
     const int32_t group = block / per, in_group = block - group * per;
     const int32_t h = in_group >> 3;
     const int32_t slot_id = group * 8 + (in_group & 7);
-    int32_t lo = 0, hi = S;                                       // largest s with start(s) <= slot_id
-    while (hi - lo > 1) {
-        const int32_t mid = (lo + hi) >> 1;
-        if ((cu_q_lens[mid] >> kAppendSlotShift) + 2 * mid <= slot_id) lo = mid; else hi = mid;
-    }
-    const int32_t s = lo;
-    const int32_t t_seq = cu_q_lens[s];
-    const int32_t first = ctx_lens[s];                            // the step fills positions [first, last)
-    const int32_t last = first + (cu_q_lens[s + 1] - t_seq);
+    const OwnedBy own = owner_of(cu_q_lens, ctx_lens, 0, S, slot_id, [](int32_t t, int32_t i) { return (t >> kAppendSlotShift) + 2 * i; });
+    const int32_t s = own.seq, t_seq = own.token;
+    const int32_t first = own.ctx;                                // the step fills positions [first, last)
+    const int32_t last = first + own.q_len;
     if (last - first == 1) return;                               // single tokens: append_token_kernel
     // the workgroup's 16 positions: one page, or (pages of 8 tokens) two consecutive table entries
     const int32_t blk = (first >> 4) + (slot_id - ((t_seq >> kAppendSlotShift) + 2 * s));

@@ -49,20 +49,14 @@ __global__ __launch_bounds__(kPrefillThreads) void prefill_merge_kernel(
     constexpr int kRows = kTileCols * 16 / kMergeParts;            // rows of this workgroup
     const int32_t g = blockIdx.x % Hkv, cut_pos = blockIdx.x / Hkv, pos = cut_first_pos + cut_pos;
     const int32_t b = base_slot + (backwards ? num_slots - 1 - pos : pos);
-    int32_t lo = 0, hi = S;
-    while (hi - lo > 1) {
-        const int32_t mid = (lo + hi) >> 1;
-        if (prefill_slot_start(cu_q_lens[mid], mid, G) <= b) lo = mid; else hi = mid;
-    }
-    const int32_t s = lo;
-    const int32_t t_seq = cu_q_lens[s];
-    const int32_t q_len = cu_q_lens[s + 1] - t_seq;
+    const OwnedBy own = owner_of(cu_q_lens, ctx_lens, 0, S, b, [&](int32_t t, int32_t i) { return prefill_slot_start(t, i, G); });
+    const int32_t s = own.seq, t_seq = own.token, q_len = own.q_len;
     if (q_len <= 1) return;
     const int32_t n_ct = ((q_len + 15) >> 4) * G;
     const int32_t ct0 = (int32_t)(b - prefill_slot_start(t_seq, s, G)) * kTileCols;
     if (ct0 >= n_ct) return;
     const int32_t tb_max = (min(ct0 + kTileCols, n_ct) - 1) / G;
-    const int32_t n_keys = ctx_lens[s] + min(q_len, (tb_max + 1) * 16);
+    const int32_t n_keys = own.ctx + min(q_len, (tb_max + 1) * 16);
     const int32_t n_steps = (n_keys + kKeysPerStep - 1) / kKeysPerStep;
     const int32_t n_ranges = (n_steps + range_steps - 1) / range_steps;
     if (n_ranges <= 1) return;                               // written directly by the tile kernel

@@ -165,22 +165,16 @@ __device__ __forceinline__ void prefill_tile(
     auto& lds_k = lds.k;
     auto& lds_v = lds.v;
 
-    // sequence owning slot b: the largest s with start(s) <= b
-    int32_t lo = 0, hi = S;
-    while (hi - lo > 1) {
-        const int32_t mid = (lo + hi) >> 1;
-        if (prefill_slot_start(cu_q_lens[mid], mid, G) <= b) lo = mid; else hi = mid;
-    }
-    const int32_t s = lo;
-    const int32_t t_seq = cu_q_lens[s];
-    const int32_t q_len = cu_q_lens[s + 1] - t_seq;
+    // sequence owning slot b
+    const OwnedBy own = owner_of(cu_q_lens, ctx_lens, 0, S, b, [&](int32_t t, int32_t i) { return prefill_slot_start(t, i, G); });
+    const int32_t s = own.seq, t_seq = own.token, q_len = own.q_len;
     if (q_len <= 1) return;                            // decode and idle sequences: other path
     const int32_t n_ct = ((q_len + 15) >> 4) * G;      // column tiles of the sequence
     const int32_t ct0 = (int32_t)(b - prefill_slot_start(t_seq, s, G)) * kTileCols;
     if (ct0 >= n_ct) return;
     const int32_t tb_min = ct0 / G;                    // first and last token block of the tile
     const int32_t tb_max = (min(ct0 + kTileCols, n_ct) - 1) / G;
-    const int32_t C = ctx_lens[s];
+    const int32_t C = own.ctx;
     const int32_t n_seq_keys = C + q_len;              // keys the sequence holds after the append
     const int32_t n_keys = C + min(q_len, (tb_max + 1) * 16);   // keys visible to the tile's last token
     const int32_t n_steps = (n_keys + kKeysPerStep - 1) / kKeysPerStep;

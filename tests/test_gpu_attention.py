@@ -510,3 +510,19 @@ def test_plans_for_other_compute_unit_counts_are_still_correct(cus):
         assert_attention_close(out, st.oracle_attention(), "planned for %d CUs, chunks" % cus)
     finally:
         cs.cs_debug_set_cu_count(0)
+
+
+@pytest.mark.parametrize("S", [1, 2, 63, 64, 65, 127, 4095, 4096, 4097, 4161])
+def test_chunks_are_found_among_any_number_of_sequences(S):
+    """A chunk's workgroups find their sequence 64 candidates at a time, in one round up to 64
+    sequences, in two up to 4096: chunks at both ends, around the 64th and the 4096th sequence and at
+    the last stride, decodes and idle sequences between them, through append and attention."""
+    sh = synth.Shape(2, 1, 64)
+    g = synth.generator(4700 + S)
+    q = synth.uniform_int(0, 1, S, g).tolist()
+    for s, n in ((0, 17), (1, 2), (62, 3), (63, 40), (64, 33), (65, 5), (S // 2, 16), (4094, 7), (4095, 35), (4096, 9), (S - 2, 31), (S - 1, 50)):
+        if 0 <= s < S:
+            q[s] = n
+    b = synth.make_batch(sh, synth.uniform_int(0, 40, S, g).tolist(), q, g)
+    out, st, _, _ = run_step(b, 47)
+    assert_attention_close(out, st.oracle_attention(), "chunks among %d sequences" % S)
