@@ -526,3 +526,16 @@ def test_chunks_are_found_among_any_number_of_sequences(S):
     b = synth.make_batch(sh, synth.uniform_int(0, 40, S, g).tolist(), q, g)
     out, st, _, _ = run_step(b, 47)
     assert_attention_close(out, st.oracle_attention(), "chunks among %d sequences" % S)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("ctx,ranges", [(1500, 2), (6900, 6), (8300, 8), (9300, 9), (16500, 16)])
+def test_merge_of_two_to_sixteen_key_ranges(D, ctx, ranges):
+    """prefill_merge_kernel keeps eight ranges' loads in flight and reads the maxima beforehand where there
+    are more: either side of eight, the fewest and the most ranges, with rows that no token uses."""
+    sh = synth.Shape(4, 2, D)
+    b = synth.make_batch(sh, [ctx], [19], synth.generator(48))
+    bb = cs.Batch(b.block_tables, b.ctx_lens, b.cu_q_lens)
+    assert cs.cs_paged_attention_workspace_bytes(bb, 4, 2, D) == 2 * ranges * 8 * 16 * (D + 4) * 4
+    out, st, _, _ = run_step(b, 48, q_gain=2.0)
+    assert_attention_close(out, st.oracle_attention(), "%d ranges" % ranges)
