@@ -390,8 +390,8 @@ int32_t cs_debug_prefill_order(const cs_batch* batch, int32_t num_q_heads, int32
 int32_t cs_debug_decode_pages_ahead(const cs_batch* batch, int32_t num_kv_heads, int32_t head_dim);
 
 /* Tuning knob for measurements and tests: pages (of 16 keys) a wavefront of the decode kernel
- * keeps in flight beyond the one it is multiplying: 1 or 2; 0 = automatic (by item length and
- * grid size).  Process-wide. */
+ * keeps in flight beyond the one it is multiplying: 1 or 2, of the kernel for full chips; 0 =
+ * automatic (depth and kernel by item length and grid size).  Process-wide. */
 void cs_set_decode_pages_ahead(int32_t pages);
 
 /* Tuning knob for measurements and tests.  A call that holds both prefill chunks and decode

@@ -87,19 +87,37 @@ int validate_batch(const cs_kv_pool* pool, const cs_batch* b) {
     return CS_OK;
 }
 
-// Two pages ahead per wavefront need the registers of the third workgroup per CU.  Measured
-// over 33 batch shapes: the deeper queue wins 2-6% once the launch is long enough for the
-// steady state to dominate (from about 0.65 GB of K/V on, ~100 us), and loses 2-7% on
-// smaller launches, where start-up and tail decide and every workgroup slot counts.
-static int32_t pages_ahead_of(const DecodePlan& p, int32_t Hkv, int32_t head_dim, int32_t layers) {
-    const int32_t forced = g_forced_ahead.load();
-    if (forced == 1 || forced == 2) return forced;
+// How the decode kernel loads its pages in a launch of `layers` layers: pages_ahead, counted_loads.
+static void plan_decode_loads(DecodePlan& p, int32_t Hkv, int32_t head_dim, int32_t layers) {
     const int64_t cus = device_cus(), wgs = (int64_t)p.total_items * Hkv * layers;
     const int64_t kv_bytes = p.decode_keys * 2 * Hkv * head_dim * 2 * layers;
-    // equal items run in rounds over the workgroup slots: between 513 and 768 of them are one
-    // round of three per CU, but a round and a quarter of two per CU
-    if (p.uniform && wgs > 2 * cus && wgs <= 3 * cus) return 1;
-    return kv_bytes >= 650000000ll * cus / 256 ? 2 : 1;
+    // Two pages ahead per wavefront need the registers of the third workgroup per CU.  Measured
+    // over 33 batch shapes: the deeper queue wins 2-6% once the launch is long enough for the
+    // steady state to dominate (from about 0.65 GB of K/V on, ~100 us), and loses 2-7% on
+    // smaller launches, where start-up and tail decide and every workgroup slot counts.
+    // Equal items run in rounds over the workgroup slots: between 513 and 768 of them are one
+    // round of three per CU, but a round and a quarter of two per CU.
+    const bool one_round = p.uniform && wgs > 2 * cus && wgs <= 3 * cus;
+    p.pages_ahead = !one_round && kv_bytes >= 650000000ll * cus / 256 ? 2 : 1;
+    // An item longer than everything else a CU has to read ends the launch with its workgroup alone on its CU:
+    // then its loads are counted (decode_item), because nothing else there covers a wait.  Any launch of at most a
+    // workgroup per CU is such a one, and one with a sequence far longer than the others; items under 512 keys
+    // start and end so close together that 0.9 of a CU's share is enough.  Append + attention, 190 batches of five model shapes: 4% faster on
+    // average where the rule holds, 4% slower at worst.  32 sequences of 338-394 keys (256 workgroups, 40/8 heads) 16.4 -> 14.3
+    // us, one of 107-297 keys 11.9-13.3 -> 10.5-11.8, 32 of 4001 (pages of 8, 32/8) 92 -> 83, 62 of 74-4573 95 -> 65; longer
+    // items beside others lose: 264 workgroups of 1041 keys at most (0.99 of a share) 34.5 -> 36.4, 336 of 1024 (0.75) 39 -> 42.
+    // While the rest of the chip is done, a third page in flight pays for the loads past an item's end from about 16
+    // pages a wavefront on: (62 of 74-4573, the longest 2.4 shares) 73 -> 65, 195 of 19-1598 (28/4) 38.8 -> 36.8; items of
+    // 256 keys 15.8 -> 17.1.
+    const double shares = (double)p.longest * cus / ((double)p.decode_keys * Hkv * layers);      // the longest item in CU's shares
+    p.counted_loads = p.in_args && (wgs <= cus || shares >= (p.longest < 512 ? 0.9 : 1.1));
+    if (p.counted_loads && p.longest >= 1024 && shares >= 1.25) p.pages_ahead = 2;
+    // (a depth asked for is that of the form for full chips)
+    const int32_t forced = g_forced_ahead.load();
+    if (forced == 1 || forced == 2) {
+        p.pages_ahead = forced;
+        p.counted_loads = false;
+    }
 }
 
 DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim) {
@@ -163,12 +181,13 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim) {
         p.total_items += k;
         if (k > 1) ++p.num_multi;
         if (k > max_k) max_k = k;
+        p.longest = std::max(p.longest, k > 1 ? decode_chunk_keys(b->h_ctx_lens[s] + 1, k) : b->h_ctx_lens[s] + 1);
     }
-    p.pages_ahead = pages_ahead_of(p, Hkv, head_dim, 1);
     // A list short enough for the argument block is written here, longest items first: the
     // workgroups of a launch start in index order, so the long ones get going at once and
     // the short ones fill in behind them (measured: 7% on 256 sequences of 512..4096 keys).
     p.in_args = p.total_items <= kMaxArgItems && b->num_seqs <= 65536 && max_k <= 255;
+    plan_decode_loads(p, Hkv, head_dim, 1);
     if (p.in_args) {
         struct Rec { int32_t keys, seq, k; };
         Rec recs[kMaxArgItems];
@@ -739,7 +758,7 @@ static void plan_layer(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, in
 // results are those of a launch of its own; only what does not touch them is chosen anew for the
 // larger grid.
 static void plan_for_layers(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t fuse, int32_t layers, Plans& plans) {
-    if (plans.d.num_decode > 0) plans.d.pages_ahead = pages_ahead_of(plans.d, Hkv, D, layers);
+    if (plans.d.num_decode > 0) plan_decode_loads(plans.d, Hkv, D, layers);
     if (plans.d.num_prefill > 0 && plans.p.max_ranges == 1) plans.p = plan_prefill(b, Hq, Hkv, D, layers);
     // (tiles cut from a launch position on stay in the order that the position counts in)
     if (plans.p.cut_first_pos == 0) plans.f = plan_fusion_by_model(b, plans.d, plans.p, Hq, Hkv, D, fuse, layers);

@@ -54,6 +54,27 @@ __global__ __launch_bounds__(kPlanThreads) void decode_plan_kernel(
 // without cuts run pages of 8 tokens 4% faster without that code: 137 sequences of 47-349 keys, 64/8 heads,
 // 27.0 -> 26.1 us.  Cut lists that a kernel merges are faster with it: 64 of 1K-8K keys, 28/4 heads, the
 // append included, 112.7 -> 109.4 us.)
+template <int D, class Src, class E, int kAhead, int PS, bool kCut, bool kCountedLoads>
+__device__ __forceinline__ void split_workgroup(
+    const uint16_t* __restrict__ layer_base, int64_t page_stride, int32_t num_pages,
+    int32_t Hkv, int32_t G,
+    const int32_t* __restrict__ block_tables, int32_t max_blocks,
+    const Src& src,
+    const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens,
+    const uint16_t* __restrict__ q, uint16_t* __restrict__ out,
+    float scale_log2e, const DecodePartials& part, int64_t next_layer, int64_t next_q)
+{
+    __shared__ DecodeLds<D> lds;
+    const int32_t item = blockIdx.x / Hkv, g = blockIdx.x - item * Hkv, n_items = gridDim.x / Hkv;
+    const DecodePartials mine = part.of_layer(blockIdx.y, n_items, Hkv * G, Hkv, D);
+    out += blockIdx.y * next_q;
+    decode_item<D, Src, E, kAhead, PS, kCountedLoads>(lds, layer_base + blockIdx.y * next_layer, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
+                           cu_q_lens, q + blockIdx.y * next_q, out, scale_log2e, mine, item, g);
+    if constexpr (kCut) {
+        if (part.words) merge_in_place<D, E>(lds, mine, src, item, g, ctx_lens, cu_q_lens, Hkv, G, out);
+    }
+}
+
 template <int D, class Src, class E, int kAhead, int PS, bool kCut>
 __global__ __launch_bounds__(kDecodeThreads, 2) void decode_split_kernel(
     const uint16_t* __restrict__ layer_base, int64_t page_stride, int32_t num_pages,
@@ -64,15 +85,24 @@ __global__ __launch_bounds__(kDecodeThreads, 2) void decode_split_kernel(
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out,
     float scale_log2e, const DecodePartials part, int64_t next_layer, int64_t next_q)
 {
-    __shared__ DecodeLds<D> lds;
-    const int32_t item = blockIdx.x / Hkv, g = blockIdx.x - item * Hkv, n_items = gridDim.x / Hkv;
-    const DecodePartials mine = part.of_layer(blockIdx.y, n_items, Hkv * G, Hkv, D);
-    out += blockIdx.y * next_q;
-    decode_item<D, Src, E, kAhead, PS>(lds, layer_base + blockIdx.y * next_layer, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
-                           cu_q_lens, q + blockIdx.y * next_q, out, scale_log2e, mine, item, g);
-    if constexpr (kCut) {
-        if (part.words) merge_in_place<D, E>(lds, mine, src, item, g, ctx_lens, cu_q_lens, Hkv, G, out);
-    }
+    split_workgroup<D, Src, E, kAhead, PS, kCut, false>(layer_base, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
+                                                        cu_q_lens, q, out, scale_log2e, part, next_layer, next_q);
+}
+
+// The same for launches that end with workgroups alone on their CUs (plan_decode_loads says which, and
+// what it measured): bound there by one wavefront per SIMD waiting for its pages, so the loads are counted.
+template <int D, class Src, class E, int kAhead, int PS, bool kCut>
+__global__ __launch_bounds__(kDecodeThreads, 2) void decode_lone_kernel(
+    const uint16_t* __restrict__ layer_base, int64_t page_stride, int32_t num_pages,
+    int32_t Hkv, int32_t G,
+    const int32_t* __restrict__ block_tables, int32_t max_blocks,
+    const Src src,
+    const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ cu_q_lens,
+    const uint16_t* __restrict__ q, uint16_t* __restrict__ out,
+    float scale_log2e, const DecodePartials part, int64_t next_layer, int64_t next_q)
+{
+    split_workgroup<D, Src, E, kAhead, PS, kCut, true>(layer_base, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
+                                                       cu_q_lens, q, out, scale_log2e, part, next_layer, next_q);
 }
 
 // Merge of the partials of the cut sequences where the workgroups do not do it themselves: grid as
@@ -105,15 +135,17 @@ static int launch_decode_as(const cs_kv_pool& pool, int32_t layer, const LayerSp
                                  in_place ? next_launch_number() : 0};
     const uint32_t n_items = plan.in_args || cut ? plan.total_items : b.num_seqs;
     dim3 grid(n_items * (uint32_t)Hkv, (uint32_t)span.n);
-#define CS_LAUNCH_DECODE_P(DD, SRC, src, AH, PS, CUT)                                                        \
-    hipLaunchKernelGGL((decode_split_kernel<DD, SRC, E, AH, PS, CUT>), grid, dim3(kDecodeThreads), 0, st, layer_base, \
+#define CS_LAUNCH_DECODE_P(KERNEL, DD, SRC, src, AH, PS, CUT)                                                \
+    hipLaunchKernelGGL((KERNEL<DD, SRC, E, AH, PS, CUT>), grid, dim3(kDecodeThreads), 0, st, layer_base, \
                        pool.page_stride, pool.num_pages, Hkv, G, b.block_tables, b.max_blocks_per_seq, \
                        src, b.ctx_lens, b.cu_q_lens, (const uint16_t*)q, (uint16_t*)out,               \
                        scale_log2e, part, span.pool, span.q);
-#define CS_LAUNCH_DECODE_A(DD, SRC, src, AH, CUT)                                                            \
-    if (pool.page_size == 16) { CS_LAUNCH_DECODE_P(DD, SRC, src, AH, 16, CUT) } else { CS_LAUNCH_DECODE_P(DD, SRC, src, AH, 8, CUT) }
-#define CS_LAUNCH_DECODE(DD, SRC, src, CUT)                                                                 \
-    if (plan.pages_ahead == 2) { CS_LAUNCH_DECODE_A(DD, SRC, src, 2, CUT) } else { CS_LAUNCH_DECODE_A(DD, SRC, src, 1, CUT) }
+#define CS_LAUNCH_DECODE_A(KERNEL, DD, SRC, src, AH, CUT)                                                    \
+    if (pool.page_size == 16) { CS_LAUNCH_DECODE_P(KERNEL, DD, SRC, src, AH, 16, CUT) } else { CS_LAUNCH_DECODE_P(KERNEL, DD, SRC, src, AH, 8, CUT) }
+#define CS_LAUNCH_DECODE(KERNEL, DD, SRC, src, CUT)                                                         \
+    if (plan.pages_ahead == 2) { CS_LAUNCH_DECODE_A(KERNEL, DD, SRC, src, 2, CUT) } else { CS_LAUNCH_DECODE_A(KERNEL, DD, SRC, src, 1, CUT) }
+#define CS_LAUNCH_DECODE_ARGS(DD, CUT)                                                                      \
+    if (plan.counted_loads) { CS_LAUNCH_DECODE(decode_lone_kernel, DD, ItemsInArgs, plan.arg_items, CUT) } else { CS_LAUNCH_DECODE(decode_split_kernel, DD, ItemsInArgs, plan.arg_items, CUT) }
 #define CS_LAUNCH_MERGE(DD, SRC, src)                                                                       \
     hipLaunchKernelGGL((decode_merge_kernel<DD, SRC, E>), grid, dim3(kDecodeThreads), 0, st, Hkv, G, src, b.ctx_lens, \
                        b.cu_q_lens, (uint16_t*)out, part, span.q);
@@ -121,9 +153,9 @@ static int launch_decode_as(const cs_kv_pool& pool, int32_t layer, const LayerSp
         // (merge_only: the fused mixed-batch kernel has already done the items' work)
         if (!merge_only) {
             if (cut) {
-                if (D == 128) { CS_LAUNCH_DECODE(128, ItemsInArgs, plan.arg_items, true) } else { CS_LAUNCH_DECODE(64, ItemsInArgs, plan.arg_items, true) }
+                if (D == 128) { CS_LAUNCH_DECODE_ARGS(128, true) } else { CS_LAUNCH_DECODE_ARGS(64, true) }
             } else {
-                if (D == 128) { CS_LAUNCH_DECODE(128, ItemsInArgs, plan.arg_items, false) } else { CS_LAUNCH_DECODE(64, ItemsInArgs, plan.arg_items, false) }
+                if (D == 128) { CS_LAUNCH_DECODE_ARGS(128, false) } else { CS_LAUNCH_DECODE_ARGS(64, false) }
             }
         }
         if (cut && !in_place) {
@@ -131,16 +163,17 @@ static int launch_decode_as(const cs_kv_pool& pool, int32_t layer, const LayerSp
         }
     } else if (!cut) {
         const ItemsIdentity src = {0};
-        if (D == 128) { CS_LAUNCH_DECODE(128, ItemsIdentity, src, false) } else { CS_LAUNCH_DECODE(64, ItemsIdentity, src, false) }
+        if (D == 128) { CS_LAUNCH_DECODE(decode_split_kernel, 128, ItemsIdentity, src, false) } else { CS_LAUNCH_DECODE(decode_split_kernel, 64, ItemsIdentity, src, false) }
     } else {
         DecodeItem* items = (DecodeItem*)(ws + w.items);
         hipLaunchKernelGGL(decode_plan_kernel, dim3(1), dim3(kPlanThreads), 0, st, b.num_seqs, b.ctx_lens,
                            b.cu_q_lens, plan.split_tokens, plan.total_items, items);
         const ItemsInMemory src = {items};
-        if (D == 128) { CS_LAUNCH_DECODE(128, ItemsInMemory, src, false) } else { CS_LAUNCH_DECODE(64, ItemsInMemory, src, false) }
+        if (D == 128) { CS_LAUNCH_DECODE(decode_split_kernel, 128, ItemsInMemory, src, false) } else { CS_LAUNCH_DECODE(decode_split_kernel, 64, ItemsInMemory, src, false) }
         if (D == 128) { CS_LAUNCH_MERGE(128, ItemsInMemory, src) } else { CS_LAUNCH_MERGE(64, ItemsInMemory, src) }
     }
 #undef CS_LAUNCH_DECODE
+#undef CS_LAUNCH_DECODE_ARGS
 #undef CS_LAUNCH_DECODE_A
 #undef CS_LAUNCH_DECODE_P
 #undef CS_LAUNCH_MERGE

@@ -307,8 +307,8 @@ __device__ __forceinline__ void merge_pieces(const DecodePartials& part, int32_t
 // workgroups per CU) that is the faster form (2-3% on the decode workloads): the other
 // workgroups cover the wait, and no load is wasted.  true: such a step loads page 0 instead, all
 // loads are straight-line code, and the compiler waits only for the page about to be multiplied,
-// so ONE workgroup per CU streams at 26-48 GB/s instead of 17: what a decode workgroup that
-// shares its CU with a prefill tile needs.
+// so ONE workgroup per CU streams at 26-48 GB/s instead of 17: what a decode workgroup needs that
+// shares its CU with a prefill tile, or ends the launch alone there.
 template <int D, class Src, class E, int kAhead, int PS, bool kCountedLoads = false>
 __device__ __forceinline__ void decode_item(
     DecodeLds<D>& lds,

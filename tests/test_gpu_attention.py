@@ -539,3 +539,20 @@ def test_merge_of_two_to_sixteen_key_ranges(D, ctx, ranges):
     assert cs.cs_paged_attention_workspace_bytes(bb, 4, 2, D) == 2 * ranges * 8 * 16 * (D + 4) * 4
     out, st, _, _ = run_step(b, 48, q_gain=2.0)
     assert_attention_close(out, st.oracle_attention(), "%d ranges" % ranges)
+
+
+@pytest.mark.parametrize("page", [16, 8])
+@pytest.mark.parametrize("D,dtype", [(64, torch.bfloat16), (128, torch.bfloat16), (128, torch.float16)])
+@pytest.mark.parametrize("ctxs", [[0], [14, 15, 16, 63, 64, 127], [257, 255, 1, 300, 31], [1022, 5, 900], [1400, 3, 129],
+                                  [2600] + [17, 90, 40] * 20])
+def test_lone_workgroups_count_their_loads(ctxs, D, dtype, page):
+    """decode_lone_kernel (launches that end with workgroups alone on their CUs: not a workgroup per CU, or
+    one sequence far longer than the others), cut and whole, one and two pages ahead, wavefronts with 0, 1, 2
+    and many pages: the pages are multiplied in the same order as in decode_split_kernel, so the bits are the same."""
+    sh = synth.Shape(8, 2, D, page_size=page)
+    b = decode_batch(sh, ctxs, 61)
+    o1, _, _, _ = run_step(b, 61, dtype=dtype, ahead=1)
+    o, st, _, _ = run_step(b, 61, dtype=dtype)
+    assert torch.equal(o.view(torch.int16), o1.view(torch.int16))
+    check = assert_attention_close if dtype == torch.bfloat16 else assert_close_f16
+    check(o, st.oracle_attention(), "alone on their CUs, D %d, pages of %d, %s" % (D, page, ctxs))
