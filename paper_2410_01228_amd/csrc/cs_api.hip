@@ -209,10 +209,9 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim) {
 }
 
 // Host plan of the key-range split (a pure function of the host lengths).  The cuts are those of
-// one layer's launch; the order of uncut tiles suits a launch of `layers` layers.  whole: no tile is cut.
-PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers, bool whole) {
+// one layer's launch; the order of uncut tiles suits a launch of `layers` layers.
+PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t layers) {
     PrefillPlan p = {};
-    p.whole = whole;
     const int32_t G = Hq / Hkv;
     int64_t total_steps = 0, tiles = 0;
     int32_t max_steps = 0, first = -1, last = -1;
@@ -237,7 +236,6 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, 
             ++tiles;
         }
     }
-    p.longest = max_steps;
     p.range_steps = std::max(max_steps, 1);
     p.max_ranges = 1;
     if (tiles == 0) return p;
@@ -249,14 +247,14 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, 
     // The chip: `cus` compute units, two workgroup slots each.  (The counts in the comments below
     // are those of the 256-CU part the rules were measured on.)
     const int64_t cus = device_cus(), slots = 2 * cus;
-    if (!whole && wgs <= cus * 3 / 4 && max_steps < 128) {
+    if (wgs <= cus * 3 / 4 && max_steps < 128) {
         // few and short tiles: about four workgroups per CU, ranges of at least 32 steps
         const int64_t rs = std::max<int64_t>(32, (total_steps * Hkv + 4 * cus - 1) / (4 * cus));
         if (rs < max_steps) {
             p.range_steps = (int32_t)rs;
             p.max_ranges = (max_steps + p.range_steps - 1) / p.range_steps;
         }
-    } else if (!whole && wgs <= 4 * cus) {
+    } else if (wgs <= 4 * cus) {
         // Up to four workgroups per CU the grid runs as one or two rounds over the 512 workgroup
         // slots (or leaves CUs empty), and a round that is not full costs almost as much as a
         // full one.  Cutting every tile into r key ranges multiplies the workgroups and divides
@@ -627,16 +625,6 @@ static FusePlan plan_fusion_by_model(const cs_batch* b, const DecodePlan& d, Pre
 static FusePlan plan_fusion(const cs_batch* b, const DecodePlan& d, PrefillPlan& p, int32_t Hq, int32_t Hkv,
                             int32_t D, int32_t mode) {
     const FusePlan f = plan_fusion_by_model(b, d, p, Hq, Hkv, D, mode, 1);
-    // In the fused grid tiles are cut to end sooner than the longest of them would; where the decode stream
-    // outlasts that one anyway, the pieces only add their start-up, partials and merge to it.  A whole tile takes
-    // about 0.8 us a step, and 10 us is what those cost.  Over 122 mixes with cut tiles (four model shapes, head dim
-    // 128, 2-1900 new tokens a chunk) the 31 that this takes are 3.1% faster whole, 3% slower at worst (48
-    // workgroups of 154 steps beside a stream of 242 us); of those it leaves, most are more than 10% faster cut.  Tiles
-    // long enough for six ranges and more gain nothing (0.985-1.001 on three).  (32/8 heads, four chunks of 153
-    // tokens + 279 us: cut in 4 313 us, whole 290; 64/8, six of 71 + 269 us: 309, 286; 64/8, four of 23 + 26 us: 40, 36.)
-    const double t_stream = (double)d.decode_keys * 2 * Hkv * D * 2 / 6.5e6, t_tile = 0.8 * p.longest;      // microseconds
-    if (mode == 1 && D == 128 && f.arrangement != 0 && p.max_ranges > 1 && p.max_ranges <= 5 && p.cut_first_pos == 0 && t_tile <= 0.7 * t_stream + 10)
-        p = plan_prefill(b, Hq, Hkv, D, 1, true);
     const int32_t forced_whole = g_forced_tail_whole.load(), forced_ranges = g_forced_tail_ranges.load();
     if (forced_whole >= 0 && forced_ranges >= 1 && f.arrangement != 0) {
         // measurement and test knob: cut the launch positions from forced_whole on into forced_ranges
@@ -672,9 +660,9 @@ static bool decode_merges_in_place(const DecodePlan& d, const PrefillPlan& p, co
 
 // Where the fused grid merges cut tiles itself and no kernel follows (in the prefill kernel's own grid one
 // always does).  The last range of a tile adds the others' partials alone on its CU, up to 1 MB for 16
-// ranges, rows without a token included, where the kernel spreads a tile over sixteen workgroups and leaves
+// ranges, rows without a token included, where the kernel spreads a tile over four workgroups and leaves
 // those rows out; but it saves the kernel's launch, and costs nothing while decode work still runs.  Over
-// 182 mixes with chunks of 2-600 tokens on 300-60000 keys (four model shapes, same box; the kernel with four workgroups a tile): a kernel 3.0% off
+// 182 mixes with chunks of 2-600 tokens on 300-60000 keys (four model shapes, same box): a kernel 3.0% off
 // the better of the two, 20% at worst; in place 4.9% and 41%; two ranges, or a decode stream of 0.7 of a
 // range's time and more, in place: 1.3%, 13%.
 static bool tiles_merge_in_place(const DecodePlan& d, const PrefillPlan& p, const FusePlan& f, int32_t Hkv, int32_t D, int32_t layers) {
@@ -771,7 +759,7 @@ static void plan_layer(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, in
 // larger grid.
 static void plan_for_layers(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t fuse, int32_t layers, Plans& plans) {
     if (plans.d.num_decode > 0) plan_decode_loads(plans.d, Hkv, D, layers);
-    if (plans.d.num_prefill > 0 && plans.p.max_ranges == 1) plans.p = plan_prefill(b, Hq, Hkv, D, layers, plans.p.whole);
+    if (plans.d.num_prefill > 0 && plans.p.max_ranges == 1) plans.p = plan_prefill(b, Hq, Hkv, D, layers);
     // (tiles cut from a launch position on stay in the order that the position counts in)
     if (plans.p.cut_first_pos == 0) plans.f = plan_fusion_by_model(b, plans.d, plans.p, Hq, Hkv, D, fuse, layers);
     plans.p.bytes *= layers;

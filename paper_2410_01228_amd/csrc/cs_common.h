@@ -164,10 +164,8 @@ struct PrefillPlan {
     int32_t num_slots;         // slots from base_slot on: the grid's extent; partials are indexed by slot - base_slot
     size_t  bytes;             // workspace for the partials (0 when nothing is cut)
     bool    merges_in_place;   // the fused grid merges cut tiles itself, no kernel follows
-    bool    whole;             // planned without cuts, whatever the tiles are
-    int32_t longest;           // 32-key steps of the longest tile
 };
-PrefillPlan plan_prefill(const cs_batch* batch, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim, int32_t layers, bool whole = false);
+PrefillPlan plan_prefill(const cs_batch* batch, int32_t num_q_heads, int32_t num_kv_heads, int32_t head_dim, int32_t layers);
 int launch_prefill(const cs_kv_pool& pool, int32_t layer, const cs_batch& b, const PrefillPlan& plan,
                    const void* q, void* out, int32_t Hq, float scale, void* workspace, hipStream_t st, bool f16);
 // The merge of the partials of cut tiles alone (what launch_prefill ends with when tiles are cut).

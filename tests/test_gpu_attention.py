@@ -556,20 +556,3 @@ def test_lone_workgroups_count_their_loads(ctxs, D, dtype, page):
     assert torch.equal(o.view(torch.int16), o1.view(torch.int16))
     check = assert_attention_close if dtype == torch.bfloat16 else assert_close_f16
     check(o, st.oracle_attention(), "alone on their CUs, D %d, pages of %d, %s" % (D, page, ctxs))
-
-
-@pytest.mark.parametrize("ctx,q", [(3000, (23, 9, 17, 2)), (100, (16,)), (4100, (40, 33))])
-def test_mixes_whose_stream_outlasts_their_tiles_keep_them_whole(ctx, q):
-    """Short chunks that would be cut on their own are not cut beside a decode stream longer than any of them:
-    whole tiles in the fused grid, against the oracle."""
-    sh = synth.Shape(32, 8, 128)
-    g = synth.generator(71)
-    chunks = synth.make_batch(sh, [ctx] * len(q), list(q), g)
-    bb = cs.Batch(chunks.block_tables, chunks.ctx_lens, chunks.cu_q_lens)
-    alone = cs.cs_paged_attention_workspace_bytes(bb, 32, 8, 128)
-    b = synth.make_batch(sh, [3000] * 96 + [ctx] * len(q), [1] * 96 + list(q), g)
-    out, st, _, bb = run_step(b, 71)
-    slots, first, ranges = cs.cs_debug_mixed_tail_cut(bb, 32, 8, 128)
-    assert cs.cs_debug_mixed_arrangement(bb, 32, 8, 128) != 0 and ranges == 1
-    assert alone > 0 or ctx == 100
-    assert_attention_close(out, st.oracle_attention(), "whole tiles, %d cached, %s" % (ctx, q))
