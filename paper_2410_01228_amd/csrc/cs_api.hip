@@ -660,9 +660,9 @@ static bool decode_merges_in_place(const DecodePlan& d, const PrefillPlan& p, co
 
 // Where the fused grid merges cut tiles itself and no kernel follows (in the prefill kernel's own grid one
 // always does).  The last range of a tile adds the others' partials alone on its CU, up to 1 MB for 16
-// ranges, rows without a token included, where the kernel spreads a tile over four workgroups and leaves
+// ranges, rows without a token included, where the kernel spreads a tile over sixteen workgroups and leaves
 // those rows out; but it saves the kernel's launch, and costs nothing while decode work still runs.  Over
-// 182 mixes with chunks of 2-600 tokens on 300-60000 keys (four model shapes, same box): a kernel 3.0% off
+// 182 mixes with chunks of 2-600 tokens on 300-60000 keys (four model shapes, same box; the kernel had four then): a kernel 3.0% off
 // the better of the two, 20% at worst; in place 4.9% and 41%; two ranges, or a decode stream of 0.7 of a
 // range's time and more, in place: 1.3%, 13%.
 static bool tiles_merge_in_place(const DecodePlan& d, const PrefillPlan& p, const FusePlan& f, int32_t Hkv, int32_t D, int32_t layers) {
