@@ -389,6 +389,13 @@ int32_t cs_debug_prefill_order(const cs_batch* batch, int32_t num_q_heads, int32
  * CS_ERR_INVALID_ARG. */
 int32_t cs_debug_decode_pages_ahead(const cs_batch* batch, int32_t num_kv_heads, int32_t head_dim);
 
+/* The same in a launch of `layers` layers (1 or more), with the form of the kernel beside it:
+ * *counted_loads (optional) receives 1 where the batch takes the form for launches that end with
+ * workgroups alone on their compute units, else 0.  CS_ERR_INVALID_ARG on bad arguments.  No device
+ * work. */
+int32_t cs_debug_decode_loads(const cs_batch* batch, int32_t num_kv_heads, int32_t head_dim, int32_t layers,
+                              int32_t* counted_loads);
+
 /* Tuning knob for measurements and tests: pages (of 16 keys) a wavefront of the decode kernel
  * keeps in flight beyond the one it is multiplying: 1 or 2, of the kernel for full chips; 0 =
  * automatic (depth and kernel by item length and grid size).  Process-wide. */

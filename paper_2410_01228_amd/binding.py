@@ -137,6 +137,7 @@ def lib():
         L.cs_debug_prefill_order.restype = ctypes.c_int32
         L.cs_debug_prefill_order.argtypes = [BP, i32, i32, i32, ctypes.POINTER(ctypes.c_int32), i32]
         L.cs_debug_decode_pages_ahead.restype, L.cs_debug_decode_pages_ahead.argtypes = ctypes.c_int32, [BP, i32, i32]
+        L.cs_debug_decode_loads.restype, L.cs_debug_decode_loads.argtypes = ctypes.c_int32, [BP, i32, i32, i32, ctypes.POINTER(ctypes.c_int32)]
         L.cs_debug_decode_items.restype = ctypes.c_int32
         L.cs_debug_decode_items.argtypes = [BP, i32, i32, ctypes.POINTER(ctypes.c_uint32), i32, ctypes.POINTER(ctypes.c_int32)]
         L.cs_status_string.restype, L.cs_status_string.argtypes = ctypes.c_char_p, [ctypes.c_int]
@@ -151,7 +152,7 @@ EXPORTS = [
     "cs_kv_ckpt_restore_tokens", "cs_kv_ckpt_save",
     "cs_kv_ckpt_load", "cs_kv_ckpt_save_run", "cs_kv_ckpt_load_run", "cs_page_map_create", "cs_page_map_destroy",
     "cs_page_map_host_of", "cs_page_map_gpu_of", "cs_page_map_free_host_pages", "cs_page_map_checkpoint",
-    "cs_page_map_evict", "cs_page_map_bind", "cs_page_map_drop", "cs_run_layers", "cs_run_layers_f16", "cs_run_layers_workspace_bytes", "cs_debug_set_cu_count", "cs_debug_copy", "cs_debug_decode_items", "cs_debug_decode_pages_ahead", "cs_debug_prefill_order",
+    "cs_page_map_evict", "cs_page_map_bind", "cs_page_map_drop", "cs_run_layers", "cs_run_layers_f16", "cs_run_layers_workspace_bytes", "cs_debug_set_cu_count", "cs_debug_copy", "cs_debug_decode_items", "cs_debug_decode_pages_ahead", "cs_debug_decode_loads", "cs_debug_prefill_order",
     "cs_set_decode_split_tokens", "cs_set_decode_pages_ahead", "cs_set_mixed_fusion", "cs_debug_mixed_arrangement", "cs_debug_mixed_tile_priority", "cs_debug_mixed_tail_cut", "cs_debug_set_tail_cut", "cs_debug_play_tiles", "cs_status_string", "cs_last_hip_error",
 ]
 
@@ -463,6 +464,15 @@ def cs_debug_decode_items(batch: "Batch", Hkv: int, D: int, capacity: int = 1024
     if n < 0:
         raise CsError(n, "cs_debug_decode_items")
     return [(w & 0xffff, (w >> 16) & 0xff, w >> 24) for w in buf[:min(n, capacity)]], n, split.value
+
+
+def cs_debug_decode_loads(batch: "Batch", Hkv: int, D: int, layers: int = 1):
+    """(pages ahead, whether the loads are counted) of the decode kernel in a launch of `layers` layers."""
+    counted = ctypes.c_int32(0)
+    n = lib().cs_debug_decode_loads(ctypes.byref(batch.c), Hkv, D, layers, ctypes.byref(counted))
+    if n < 0:
+        raise CsError(n, "cs_debug_decode_loads")
+    return n, bool(counted.value)
 
 
 def cs_set_decode_pages_ahead(pages: int):

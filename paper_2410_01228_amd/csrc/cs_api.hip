@@ -1023,6 +1023,13 @@ int32_t cs_debug_decode_pages_ahead(const cs_batch* batch, int32_t Hkv, int32_t 
     return plan_decode(batch, Hkv, D).pages_ahead;
 }
 
+int32_t cs_debug_decode_loads(const cs_batch* batch, int32_t Hkv, int32_t D, int32_t layers, int32_t* counted_loads) {
+    if (!shape_supported(Hkv, D) || layers < 1 || validate_batch(nullptr, batch) != CS_OK || batch->num_seqs == 0) return CS_ERR_INVALID_ARG;
+    const DecodePlan& p = plans_for(batch, Hkv, Hkv, D, layers).d;       // (the decode side's plan depends on no query head)
+    if (counted_loads) *counted_loads = p.counted_loads;
+    return p.pages_ahead;
+}
+
 int32_t cs_debug_prefill_order(const cs_batch* batch, int32_t Hq, int32_t Hkv, int32_t D, int32_t* slots, int32_t capacity) {
     if (attention_shape_ok(Hq, Hkv, D) != CS_OK || validate_batch(nullptr, batch) != CS_OK || capacity < 0 ||
         (capacity > 0 && !slots))

@@ -85,6 +85,8 @@ int main() {
         CHECK(split >= 256 && split % 16 == 0);
         const int32_t ahead = cs_debug_decode_pages_ahead(&b, sh[1], sh[2]);
         CHECK(ahead == 1 || ahead == 2);
+        int32_t counted = -1;
+        CHECK(cs_debug_decode_loads(&b, sh[1], sh[2], 1, &counted) == ahead && (counted == 0 || counted == 1));
         const int32_t n_ord = cs_debug_prefill_order(&b, sh[0], sh[1], sh[2], order.data(), (int32_t)order.size());
         CHECK(n_ord >= 0 && n_ord <= 512);
         int32_t first_cut = -1, ranges = -1;

@@ -219,8 +219,8 @@ def test_decode_plan_falls_back_to_the_planning_kernel_beyond_the_argument_block
 
 
 def test_decode_prefetch_depth_follows_the_launch_volume():
-    """Two pages in flight per wavefront from about 0.65 GB of K/V per launch on, one below;
-    the knob overrides either way."""
+    """Where a launch does not end with lone workgroups (next test): two pages in flight per wavefront from
+    about 0.65 GB of K/V per launch on, one below; the knob overrides either way."""
     lib = cs.lib()
 
     def ahead(ctx, Hkv, D):
@@ -247,6 +247,61 @@ def test_decode_prefetch_depth_follows_the_launch_volume():
     b, keep = _batch([5, 5], [3, 4], max_blocks=16)
     assert lib.cs_debug_decode_pages_ahead(ctypes.byref(b), 8, 128) == 1      # no decode sequence
     assert lib.cs_debug_decode_pages_ahead(ctypes.byref(b), 8, 100) == cs.CS_ERR_INVALID_ARG
+
+
+def test_decode_loads_are_counted_where_a_launch_ends_with_lone_workgroups():
+    """Both sides of every line of that rule (256 compute units): a workgroup per unit; 0.9 of a unit's share
+    of the keys for the longest item, 1.1 from 512 keys on; a second page ahead from 1.25 shares and 1024 keys
+    on; lists that do not travel in the arguments; several layers in a launch; a forced depth."""
+    lib = cs.lib()
+
+    def loads(ctx, Hkv=8, D=128, layers=1):
+        b, keep = _batch(ctx, [1] * len(ctx), max_blocks=1 << 16)
+        counted = ctypes.c_int32(-1)
+        ahead = lib.cs_debug_decode_loads(ctypes.byref(b), Hkv, D, layers, ctypes.byref(counted))
+        return ahead, counted.value
+
+    def one_and_others(longest, keys):                      # 40 sequences, 320 workgroups; a unit's share is total * 8 / 256
+        return loads([longest - 1] + [keys - 1] * 39)
+
+    lib.cs_debug_set_cu_count(256)
+    try:
+        lib.cs_set_decode_split_tokens(1 << 16)             # (nothing is cut)
+        assert loads([600] * 32) == (1, 1)                  # 256 workgroups
+        assert loads([600] * 33) == (1, 0)                  # 264, 0.97 of a share each
+        assert loads([300] * 35) == (1, 1)                  # 32/35 of a share
+        assert loads([300] * 36) == (1, 0)                  # 32/36
+        assert loads([510] * 33) == (1, 1)                  # 511 keys
+        assert loads([511] * 33) == (1, 0)                  # 512
+        assert one_and_others(600, 432) == (1, 1)           # 19200 / 17448 = 1.1004
+        assert one_and_others(600, 433) == (1, 0)           # 1.0980
+        assert one_and_others(1100, 693) == (2, 1)          # 35200 / 28127 = 1.2515
+        assert one_and_others(1100, 694) == (1, 1)          # 1.2497
+        assert one_and_others(1024, 30) == (2, 1)
+        assert one_and_others(1023, 30) == (1, 1)
+        assert loads([4600] + [30] * 200) == (2, 1)         # 44 MB: the volume alone would have one page ahead
+        assert loads([1500] + [3] * 879) == (2, 1)
+        assert loads([1500] + [3] * 880) == (1, 0)          # 881 items: not in the arguments
+        # items, not sequences: 2000 keys in one, or in pieces of 256
+        assert loads([1999] * 4) == (2, 1)
+        lib.cs_set_decode_split_tokens(256)
+        assert loads([1999] * 4) == (1, 1)
+        lib.cs_set_decode_split_tokens(1 << 16)
+        # several layers: 17 sequences are 136 workgroups, 272 at 16/17 of a share, 408 at 0.63
+        assert [loads([300] * 17, layers=n) for n in (1, 2, 3)] == [(1, 1), (1, 1), (1, 0)]
+        # a depth asked for is that of the form for full chips
+        for ahead in (1, 2):
+            lib.cs_set_decode_pages_ahead(ahead)
+            assert loads([4600] + [30] * 200) == (ahead, 0)
+        lib.cs_set_decode_pages_ahead(0)
+    finally:
+        lib.cs_set_decode_pages_ahead(0)
+        lib.cs_set_decode_split_tokens(0)
+        lib.cs_debug_set_cu_count(0)
+    assert loads([10], layers=0)[0] == cs.CS_ERR_INVALID_ARG
+    assert loads([10], D=100)[0] == cs.CS_ERR_INVALID_ARG
+    b, keep = _batch([5, 5], [3, 4], max_blocks=16)
+    assert lib.cs_debug_decode_loads(ctypes.byref(b), 8, 128, 1, None) == 1       # no decode sequence
 
 
 def test_prefill_key_range_plan_follows_the_rounds():

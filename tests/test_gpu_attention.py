@@ -541,18 +541,33 @@ def test_merge_of_two_to_sixteen_key_ranges(D, ctx, ranges):
     assert_attention_close(out, st.oracle_attention(), "%d ranges" % ranges)
 
 
+# lengths, tokens per item (0: the host's choice), workgroups per kv head, pages ahead.  By at most a workgroup per
+# CU (256): one page ahead whole and cut, two ahead whole and cut (items of 1056-1136 keys).  By the longest
+# item's share alone (two kv heads, so from 129 items on): under 512 keys; two ahead whole; two ahead cut, merged
+# in the grid (up to 512 workgroups) and by a kernel.
 @pytest.mark.parametrize("page", [16, 8])
 @pytest.mark.parametrize("D,dtype", [(64, torch.bfloat16), (128, torch.bfloat16), (128, torch.float16)])
-@pytest.mark.parametrize("ctxs", [[0], [14, 15, 16, 63, 64, 127], [257, 255, 1, 300, 31], [1022, 5, 900], [1400, 3, 129],
-                                  [2600] + [17, 90, 40] * 20])
-def test_lone_workgroups_count_their_loads(ctxs, D, dtype, page):
-    """decode_lone_kernel (launches that end with workgroups alone on their CUs: not a workgroup per CU, or
-    one sequence far longer than the others), cut and whole, one and two pages ahead, wavefronts with 0, 1, 2
-    and many pages: the pages are multiplied in the same order as in decode_split_kernel, so the bits are the same."""
+@pytest.mark.parametrize("ctxs,split,items,ahead", [
+    ([0], 0, 1, 1), ([14, 15, 16, 63, 64, 127], 0, 6, 1), ([257, 255, 1, 300, 31], 0, 5, 1), ([1022, 5, 900], 0, 9, 1),
+    ([1400, 3, 129], 0, 7, 1), ([2600] + [17, 90, 40] * 20, 0, 70, 1), ([1400, 3, 129], 1 << 16, 3, 2), ([2100, 40, 2260], 1024, 5, 2),
+    ([400] + [3] * 150, 0, 152, 1), ([1500] + [3] * 150, 1 << 16, 151, 2), ([2100] * 3 + [5] * 150, 1024, 156, 2), ([2100] * 3 + [5] * 260, 1024, 266, 2)])
+def test_lone_workgroups_count_their_loads(ctxs, split, items, ahead, D, dtype, page):
+    """The decode kernel's form for launches that end with workgroups alone on their CUs, in every launch that
+    takes it; wavefronts with 0, 1, 2 and many pages.  The pages are multiplied in the same order as in the form
+    for full chips, so the bits are the same."""
     sh = synth.Shape(8, 2, D, page_size=page)
     b = decode_batch(sh, ctxs, 61)
-    o1, _, _, _ = run_step(b, 61, dtype=dtype, ahead=1)
-    o, st, _, _ = run_step(b, 61, dtype=dtype)
+    o1, _, _, bb = run_step(b, 61, dtype=dtype, split=split, ahead=1)
+    cs.cs_set_decode_split_tokens(split)
+    try:
+        assert cs.cs_debug_decode_items(bb, 2, D)[1] == items
+        assert cs.cs_debug_decode_loads(bb, 2, D) == (ahead, True)
+        cs.cs_set_decode_pages_ahead(1)
+        assert cs.cs_debug_decode_loads(bb, 2, D) == (1, False)
+    finally:
+        cs.cs_set_decode_pages_ahead(0)
+        cs.cs_set_decode_split_tokens(0)
+    o, st, _, _ = run_step(b, 61, dtype=dtype, split=split)
     assert torch.equal(o.view(torch.int16), o1.view(torch.int16))
     check = assert_attention_close if dtype == torch.bfloat16 else assert_close_f16
     check(o, st.oracle_attention(), "alone on their CUs, D %d, pages of %d, %s" % (D, page, ctxs))
