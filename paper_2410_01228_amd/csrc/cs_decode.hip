@@ -54,7 +54,7 @@ __global__ __launch_bounds__(kPlanThreads) void decode_plan_kernel(
 // without cuts run pages of 8 tokens 4% faster without that code: 137 sequences of 47-349 keys, 64/8 heads,
 // 27.0 -> 26.1 us.  Cut lists that a kernel merges are faster with it: 64 of 1K-8K keys, 28/4 heads, the
 // append included, 112.7 -> 109.4 us.)
-template <int D, class Src, class E, int kAhead, int PS, bool kCut, bool kCountedLoads>
+template <int D, class Src, class E, int kAhead, int PS, bool kCut, Loads kLoads>
 __device__ __forceinline__ void split_workgroup(
     const uint16_t* __restrict__ layer_base, int64_t page_stride, int32_t num_pages,
     int32_t Hkv, int32_t G,
@@ -68,7 +68,7 @@ __device__ __forceinline__ void split_workgroup(
     const int32_t item = blockIdx.x / Hkv, g = blockIdx.x - item * Hkv, n_items = gridDim.x / Hkv;
     const DecodePartials mine = part.of_layer(blockIdx.y, n_items, Hkv * G, Hkv, D);
     out += blockIdx.y * next_q;
-    decode_item<D, Src, E, kAhead, PS, kCountedLoads>(lds, layer_base + blockIdx.y * next_layer, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
+    decode_item<D, Src, E, kAhead, PS, kLoads>(lds, layer_base + blockIdx.y * next_layer, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
                            cu_q_lens, q + blockIdx.y * next_q, out, scale_log2e, mine, item, g);
     if constexpr (kCut) {
         if (part.words) merge_in_place<D, E>(lds, mine, src, item, g, ctx_lens, cu_q_lens, Hkv, G, out);
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(kDecodeThreads, 2) void decode_split_kernel(
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out,
     float scale_log2e, const DecodePartials part, int64_t next_layer, int64_t next_q)
 {
-    split_workgroup<D, Src, E, kAhead, PS, kCut, false>(layer_base, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
+    split_workgroup<D, Src, E, kAhead, PS, kCut, Loads::kSkipped>(layer_base, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
                                                         cu_q_lens, q, out, scale_log2e, part, next_layer, next_q);
 }
 
@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kDecodeThreads, 2) void decode_lone_kernel(
     const uint16_t* __restrict__ q, uint16_t* __restrict__ out,
     float scale_log2e, const DecodePartials part, int64_t next_layer, int64_t next_q)
 {
-    split_workgroup<D, Src, E, kAhead, PS, kCut, true>(layer_base, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
+    split_workgroup<D, Src, E, kAhead, PS, kCut, Loads::kLone>(layer_base, page_stride, num_pages, Hkv, G, block_tables, max_blocks, src, ctx_lens,
                                                        cu_q_lens, q, out, scale_log2e, part, next_layer, next_q);
 }
 

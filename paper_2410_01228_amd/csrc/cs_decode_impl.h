@@ -294,22 +294,31 @@ __device__ __forceinline__ void merge_pieces(const DecodePartials& part, int32_t
     }
 }
 
+// How a wavefront of decode_item loads its pages, and what it does about a step without one (past the end of the
+// range, or a bad id).
+// kSkipped: the loads of such a step are skipped.  The compiler cannot count loads behind a branch, so it waits for
+// everything in flight before each multiply: every page's loads are issued early, but a
+// wavefront never computes while its own loads fly.  On a grid that fills the chip (several
+// workgroups per CU) that is the faster form (2-3% on the decode workloads): the other
+// workgroups cover the wait, and no load is wasted.
+// kCounted: such a step loads page 0 instead, all loads are straight-line code, and the compiler waits only for
+// the page about to be multiplied, so ONE workgroup per CU streams at 26-48 GB/s instead of 17: what a decode
+// workgroup needs that shares its CU with a prefill tile.
+// kLone: the same for a workgroup that ends the launch alone on its CU; with one page ahead no loads follow
+// those of the wavefront's last page.  The loop moves the next page into the registers of the current one, so
+// kCounted waits for a page that it does not use at the end of every item: one trip to memory more than the four or
+// five of a short one (320 drawn batches, attention alone: 2% faster in the geometric mean; 288 workgroups of 84
+// keys, 64/8 heads, 7.8 -> 7.5 us; 160 of 256, pages of 8, 15.5 -> 14.4).  Beside tiles the form without that wait wins
+// and loses (200 mixes: 0.5% on average, 5% lost at worst, 0.5-1.6% lost on most with pages of 8).
+enum class Loads { kSkipped, kCounted, kLone };
+
 // The work of one decode workgroup: item `item` (a sequence's key range), kv head g; 4
 // wavefronts.  Src says where the item list is: in memory, in the kernel arguments, or
 // nowhere (item x is sequence x, and the workgroup leaves at once if that sequence is not a
 // decode).  kAhead: pages a wavefront keeps in flight beyond the one it multiplies (1 or 2; a
 // page is 32 registers, so 2 costs the third workgroup per CU: it pays for long items on a
 // full grid, not for short ones on a small grid).
-// kCountedLoads: how a step without a page (past the end of the range, or a bad id) is handled.
-// false: its loads are skipped.  The compiler cannot count loads behind a branch, so it waits for
-// everything in flight before each multiply: every page's loads are issued early, but a
-// wavefront never computes while its own loads fly.  On a grid that fills the chip (several
-// workgroups per CU) that is the faster form (2-3% on the decode workloads): the other
-// workgroups cover the wait, and no load is wasted.  true: such a step loads page 0 instead, all
-// loads are straight-line code, and the compiler waits only for the page about to be multiplied,
-// so ONE workgroup per CU streams at 26-48 GB/s instead of 17: what a decode workgroup needs that
-// shares its CU with a prefill tile, or ends the launch alone there.
-template <int D, class Src, class E, int kAhead, int PS, bool kCountedLoads = false>
+template <int D, class Src, class E, int kAhead, int PS, Loads kLoads = Loads::kSkipped>
 __device__ __forceinline__ void decode_item(
     DecodeLds<D>& lds,
     const uint16_t* __restrict__ layer_base, int64_t page_stride, int32_t num_pages,
@@ -358,7 +367,7 @@ __device__ __forceinline__ void decode_item(
 
     static_assert(kAhead == 1 || kAhead == 2, "one or two pages ahead");
     auto fetch = [&](PageRegs<D>& r, const StepIds<PS>& id) {
-        if constexpr (kCountedLoads) {
+        if constexpr (kLoads != Loads::kSkipped) {
             load_page<D>(r, layer_base, page_stride, loadable<PS>(id, num_pages), g, Hkv, lane);
         } else {
             if (step_ok<PS>(id, num_pages)) load_page<D>(r, layer_base, page_stride, id, g, Hkv, lane);
@@ -373,8 +382,9 @@ __device__ __forceinline__ void decode_item(
         auto ok = [&](const StepIds<PS>& id) { return step_ok<PS>(id, num_pages); };
         StepIds<PS> id_cur = id_at(pg);
         StepIds<PS> id_nxt = id_at(pg + kDecodeWaves);
-        fetch(cur, id_cur);
-        while (pg < page_end) {
+        constexpr int kPeeled = kLoads == Loads::kLone ? kDecodeWaves : 0;      // (the wavefront's last page)
+        if (kPeeled == 0 || pg < page_end) fetch(cur, id_cur);
+        while (pg + kPeeled < page_end) {
             const int32_t pg_n = pg + kDecodeWaves;
             const StepIds<PS> id_n2 = id_at(pg_n + kDecodeWaves);
             fetch(nxt, id_nxt);
@@ -385,6 +395,7 @@ __device__ __forceinline__ void decode_item(
             id_nxt = id_n2;
             pg = pg_n;
         }
+        if (kPeeled != 0 && pg < page_end && ok(id_cur)) process_page<D, E>(st, cur, qb, scale_log2e, pg << 4, n_keys, lane);
     } else {
         // wave w streams pages page_begin + w, + w + 4, ...; the loads of the next two pages are
         // in flight while the current page is multiplied

@@ -89,7 +89,7 @@ __global__ __launch_bounds__(kPrefillThreads, 2) void mixed_kernel(
             // one page ahead, with loads the compiler can count (a workgroup that shares its CU
             // with a tile must stream by itself); a deeper queue only delays the tile's own
             // copies, which share the CU's memory pipeline
-            decode_item<D, ItemsInArgs, E, 1, PS, true>(lds.decode, layer_base + l * next_layer, page_stride, num_pages, Hkv, G, block_tables,
+            decode_item<D, ItemsInArgs, E, 1, PS, Loads::kCounted>(lds.decode, layer_base + l * next_layer, page_stride, num_pages, Hkv, G, block_tables,
                                            max_blocks, items, ctx_lens, cu_q_lens, q + l * next_q, out + l * next_q, scale_log2e,
                                            mine, item, g);
             // (in place only where every workgroup has one pair)

@@ -94,3 +94,32 @@ def test_no_scc_value_lives_across_the_dma_asm(tmp_path, src):
     assert '"scc"' in open(ASM_HOME).read()
     # EXEC is put back as it was found, never forced to all lanes
     assert "s_mov_b64 exec, -1" not in text and "s_andn2_b64 exec" in text
+
+
+LONE = """
+#include "cs_decode_impl.h"
+using namespace cs;
+__global__ __launch_bounds__(kDecodeThreads, 2) void lone(const uint16_t* base, int64_t stride, int32_t pages, const int32_t* tables,
+    int32_t blocks, const ItemsInArgs src, const int32_t* ctx, const int32_t* cu, const uint16_t* q, uint16_t* out, const DecodePartials part)
+{
+    __shared__ DecodeLds<%d> lds;
+    decode_item<%d, ItemsInArgs, Bf16, 1, %d, Loads::kLone>(lds, base, stride, pages, 8, 4, tables, blocks, src, ctx, cu, q, out, 1.f, part, blockIdx.x, 0);
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"), reason="no hipcc")
+@pytest.mark.parametrize("D,page", [(64, 16), (128, 16), (128, 8)])
+def test_a_lone_workgroup_loads_no_page_behind_its_last(tmp_path, D, page):
+    """A decode workgroup that is alone on its CU, one page ahead: a wavefront multiplies its last page behind the
+    loop over its pages, where nothing loads another one that the end of the item would wait for."""
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    src, out = tmp_path / "lone.hip", tmp_path / "lone.s"
+    src.write_text(LONE % (D, D, page))
+    cmd = [hipcc, "--offload-arch=gfx950", "-O3", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
+           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-S", "--cuda-device-only", "-o", str(out), str(src)]
+    subprocess.run(cmd, check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
+    text = out.read_text()
+    # loads: the first page's in front of the loop, the next one's in it; products: a page's in the loop, the last one's behind it
+    assert len(re.findall(r"global_load_dwordx[24] .*\bnt\b", text)) == 2 * (D // 32 + D // 16)
+    assert len(re.findall(r"v_mfma_f32_16x16x32", text)) == 2 * (D // 32)
