@@ -87,8 +87,15 @@ int validate_batch(const cs_kv_pool* pool, const cs_batch* b) {
     return CS_OK;
 }
 
+// Keys of a work item, by its word of the list in the arguments.
+static int32_t item_keys(const cs_batch* b, uint32_t w) {
+    const int32_t n = b->h_ctx_lens[w & 0xffffu] + 1, piece = (int32_t)((w >> 16) & 0xffu), k = (int32_t)(w >> 24);
+    const int64_t chunk = k > 1 ? decode_chunk_keys(n, k) : n;
+    return (int32_t)(std::min<int64_t>(n, (piece + 1) * chunk) - std::min<int64_t>(n, piece * chunk));
+}
+
 // How the decode kernel loads its pages in a launch of `layers` layers: pages_ahead, counted_loads.
-static void plan_decode_loads(DecodePlan& p, int32_t Hkv, int32_t head_dim, int32_t layers) {
+static void plan_decode_loads(const cs_batch* b, DecodePlan& p, int32_t Hkv, int32_t head_dim, int32_t layers) {
     const int64_t cus = device_cus(), wgs = (int64_t)p.total_items * Hkv * layers;
     const int64_t kv_bytes = p.decode_keys * 2 * Hkv * head_dim * 2 * layers;
     // Two pages ahead per wavefront need the registers of the third workgroup per CU.  Measured
@@ -102,16 +109,28 @@ static void plan_decode_loads(DecodePlan& p, int32_t Hkv, int32_t head_dim, int3
     // An item longer than everything else a CU has to read ends the launch with its workgroup alone on its CU:
     // then its loads are counted (decode_item), because nothing else there covers a wait.  Any launch of at most a
     // workgroup per CU is such a one, and one with a sequence far longer than the others; items under 512 keys
-    // start and end so close together that 0.9 of a CU's share is enough.  Append + attention, 190 batches of five model shapes: 4% faster on
-    // average where the rule holds, 4% slower at worst.  32 sequences of 338-394 keys (256 workgroups, 40/8 heads) 16.4 -> 14.3
-    // us, one of 107-297 keys 11.9-13.3 -> 10.5-11.8, 32 of 4001 (pages of 8, 32/8) 92 -> 83, 62 of 74-4573 95 -> 65; longer
+    // start and end so close together that 0.9 of a CU's share is enough.  32 sequences of 338-394 keys (256
+    // workgroups, 40/8 heads; append + attention) 16.4 -> 14.3 us, one of 107-297 keys 11.9-13.3 -> 10.5-11.8, 32 of
+    // 4001 (pages of 8, 32/8) 92 -> 83, 62 of 74-4573 95 -> 65; longer
     // items beside others lose: 264 workgroups of 1041 keys at most (0.99 of a share) 34.5 -> 36.4, 336 of 1024 (0.75) 39 -> 42.
     // While the rest of the chip is done, a third page in flight pays for the loads past an item's end from about 16
     // pages a wavefront on: (62 of 74-4573, the longest 2.4 shares) 73 -> 65, 195 of 19-1598 (28/4) 38.8 -> 36.8; items of
     // 256 keys 15.8 -> 17.1.
+    // The longest item is alone only once the workgroup beside it is done, the first of the second round (the dispatcher
+    // gives the first workgroup of every CU a CU of its own, in list order).  Where that one has more than 0.58 of its
+    // keys, the two share the CU almost to the end, and at head dim 128 skipped loads are the better form again: of 60
+    // such batches counted ones lost 1-5% on half (288 workgroups, 2797 keys with 1900 beside them, 1.18 shares, 40/8
+    // heads: 60.8 us skipped, 63.8 counted; 264, 1264 with 900, 64/8: 32.5, 33.5) and gained up to 4% on others, most
+    // with pages of 8, which the plan does not know.  From there down they gain (296, 528 with 300, pages of 8, 64/8:
+    // 21.0, 19.0; 336, 715 with 415: 20.2, 19.2; at half and less 10% and more).  A third page in flight
+    // loses from half on (320, 1534 with 980, 32/8: 34.4 skipped, 38.7 two ahead, 34.8 one).  At head dim 64, with half as
+    // many loads a page, both pay all the same (310, 725 with 480, 4/2 heads: 16.9 skipped, 14.8; 488, 3027
+    // with 1600: 49.8, two ahead 34.0, one 36.6).
     const double shares = (double)p.longest * cus / ((double)p.decode_keys * Hkv * layers);      // the longest item in CU's shares
-    p.counted_loads = p.in_args && (wgs <= cus || shares >= (p.longest < 512 ? 0.9 : 1.1));
-    if (p.counted_loads && p.longest >= 1024 && shares >= 1.25) p.pages_ahead = 2;
+    const bool has_second = p.in_args && wgs > cus && head_dim == 128;
+    const double beside = has_second ? (double)item_keys(b, p.arg_items.e[cus / Hkv % p.total_items]) / p.longest : 0.0;
+    p.counted_loads = p.in_args && (wgs <= cus || (p.longest < 512 ? shares >= 0.9 : shares >= 1.1 && beside <= 0.58));
+    if (p.counted_loads && p.longest >= 1024 && shares >= 1.25 && beside <= 0.5) p.pages_ahead = 2;
     // (a depth asked for is that of the form for full chips)
     const int32_t forced = g_forced_ahead.load();
     if (forced == 1 || forced == 2) {
@@ -187,7 +206,6 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim) {
     // workgroups of a launch start in index order, so the long ones get going at once and
     // the short ones fill in behind them (measured: 7% on 256 sequences of 512..4096 keys).
     p.in_args = p.total_items <= kMaxArgItems && b->num_seqs <= 65536 && max_k <= 255;
-    plan_decode_loads(p, Hkv, head_dim, 1);
     if (p.in_args) {
         struct Rec { int32_t keys, seq, k; };
         Rec recs[kMaxArgItems];
@@ -205,6 +223,7 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim) {
                 p.arg_items.e[item++] = (uint32_t)recs[r].seq | ((uint32_t)i << 16) | ((uint32_t)recs[r].k << 24);
         }
     }
+    plan_decode_loads(b, p, Hkv, head_dim, 1);
     return p;
 }
 
@@ -421,10 +440,7 @@ static void play_pairs(const cs_batch* b, const DecodePlan& d, int32_t Hkv, int3
     std::vector<double> walked((size_t)groups, 0.0), ends(2 * (size_t)groups, 0.0);      // (ends: a heap, the earliest on top)
     double sum = 0;
     for (int32_t i = 0; i < n; ++i) {
-        const uint32_t w = d.arg_items.e[i % d.total_items];
-        const int32_t keys = b->h_ctx_lens[w & 0xffffu] + 1, piece = (int32_t)((w >> 16) & 0xffu), k = (int32_t)(w >> 24);
-        const int32_t chunk = k > 1 ? decode_chunk_keys(keys, k) : keys;
-        const double len = (double)(std::min<int64_t>(keys, (int64_t)(piece + 1) * chunk) - std::min<int64_t>(keys, (int64_t)piece * chunk));
+        const double len = item_keys(b, d.arg_items.e[i % d.total_items]);
         const int32_t at = i % groups;
         walked[(size_t)((i / groups) & 1 ? groups - 1 - at : at)] += len;
         std::pop_heap(ends.begin(), ends.end(), std::greater<double>());
@@ -758,7 +774,7 @@ static void plan_layer(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, in
 // results are those of a launch of its own; only what does not touch them is chosen anew for the
 // larger grid.
 static void plan_for_layers(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, int32_t fuse, int32_t layers, Plans& plans) {
-    if (plans.d.num_decode > 0) plan_decode_loads(plans.d, Hkv, D, layers);
+    if (plans.d.num_decode > 0) plan_decode_loads(b, plans.d, Hkv, D, layers);
     if (plans.d.num_prefill > 0 && plans.p.max_ranges == 1) plans.p = plan_prefill(b, Hq, Hkv, D, layers);
     // (tiles cut from a launch position on stay in the order that the position counts in)
     if (plans.p.cut_first_pos == 0) plans.f = plan_fusion_by_model(b, plans.d, plans.p, Hq, Hkv, D, fuse, layers);

@@ -251,8 +251,9 @@ def test_decode_prefetch_depth_follows_the_launch_volume():
 
 def test_decode_loads_are_counted_where_a_launch_ends_with_lone_workgroups():
     """Both sides of every line of that rule (256 compute units): a workgroup per unit; 0.9 of a unit's share
-    of the keys for the longest item, 1.1 from 512 keys on; a second page ahead from 1.25 shares and 1024 keys
-    on; lists that do not travel in the arguments; several layers in a launch; a forced depth."""
+    of the keys for the longest item, 1.1 from 512 keys on; at most 0.58 of its keys in the workgroup beside it; a
+    second page ahead from 1.25 shares and 1024 keys on, with at most half of them beside it; lists that do not travel in the arguments; several layers
+    in a launch; a forced depth."""
     lib = cs.lib()
 
     def loads(ctx, Hkv=8, D=128, layers=1):
@@ -261,8 +262,8 @@ def test_decode_loads_are_counted_where_a_launch_ends_with_lone_workgroups():
         ahead = lib.cs_debug_decode_loads(ctypes.byref(b), Hkv, D, layers, ctypes.byref(counted))
         return ahead, counted.value
 
-    def one_and_others(longest, keys):                      # 40 sequences, 320 workgroups; a unit's share is total * 8 / 256
-        return loads([longest - 1] + [keys - 1] * 39)
+    def one_and_others(longest, keys, second=100, **kw):    # 40 sequences, 320 workgroups; a unit's share is total * 8 / 256
+        return loads([longest - 1] + [keys - 1] * 31 + [second - 1] + [99] * 7, **kw)
 
     lib.cs_debug_set_cu_count(256)
     try:
@@ -273,10 +274,17 @@ def test_decode_loads_are_counted_where_a_launch_ends_with_lone_workgroups():
         assert loads([300] * 36) == (1, 0)                  # 32/36
         assert loads([510] * 33) == (1, 1)                  # 511 keys
         assert loads([511] * 33) == (1, 0)                  # 512
-        assert one_and_others(600, 432) == (1, 1)           # 19200 / 17448 = 1.1004
-        assert one_and_others(600, 433) == (1, 0)           # 1.0980
-        assert one_and_others(1100, 693) == (2, 1)          # 35200 / 28127 = 1.2515
-        assert one_and_others(1100, 694) == (1, 1)          # 1.2497
+        assert one_and_others(600, 517) == (1, 1)           # 19200 / 17427 = 1.1017
+        assert one_and_others(600, 518) == (1, 0)           # 1.0998
+        assert one_and_others(1100, 847) == (2, 1)          # 35200 / 28157 = 1.2501
+        assert one_and_others(1100, 848) == (1, 1)          # 1.2488
+        assert one_and_others(1000, 700, 580) == (1, 1)     # (1.36 shares) beside the longest 0.58 of its keys
+        assert one_and_others(1000, 700, 581) == (1, 0)
+        assert one_and_others(1000, 700, 581, D=64) == (1, 1)
+        assert one_and_others(500, 400, 390) == (1, 1)      # (under 512 keys)
+        assert one_and_others(1200, 700, 600) == (2, 1)     # (1.52 shares) half of its keys
+        assert one_and_others(1200, 700, 601) == (1, 1)
+        assert one_and_others(1200, 700, 601, D=64) == (2, 1)
         assert one_and_others(1024, 30) == (2, 1)
         assert one_and_others(1023, 30) == (1, 1)
         assert loads([4600] + [30] * 200) == (2, 1)         # 44 MB: the volume alone would have one page ahead
