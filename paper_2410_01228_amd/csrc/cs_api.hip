@@ -193,19 +193,19 @@ DecodePlan plan_decode(const cs_batch* b, int32_t Hkv, int32_t head_dim) {
             if (workgroups_at(split) >= need) break;
     }
     p.split_tokens = split;
-    int32_t max_k = 1;
+    p.max_pieces = 1;
     for (int32_t s = 0; s < b->num_seqs; ++s) {
         if (b->h_cu_q_lens[s + 1] - b->h_cu_q_lens[s] != 1) continue;
         const int32_t k = decode_num_splits(b->h_ctx_lens[s] + 1, split);
         p.total_items += k;
         if (k > 1) ++p.num_multi;
-        if (k > max_k) max_k = k;
+        p.max_pieces = std::max(p.max_pieces, k);
         p.longest = std::max(p.longest, k > 1 ? decode_chunk_keys(b->h_ctx_lens[s] + 1, k) : b->h_ctx_lens[s] + 1);
     }
     // A list short enough for the argument block is written here, longest items first: the
     // workgroups of a launch start in index order, so the long ones get going at once and
     // the short ones fill in behind them (measured: 7% on 256 sequences of 512..4096 keys).
-    p.in_args = p.total_items <= kMaxArgItems && b->num_seqs <= 65536 && max_k <= 255;
+    p.in_args = p.total_items <= kMaxArgItems && b->num_seqs <= 65536 && p.max_pieces <= 255;
     if (p.in_args) {
         struct Rec { int32_t keys, seq, k; };
         Rec recs[kMaxArgItems];
@@ -666,11 +666,18 @@ static FusePlan plan_fusion(const cs_batch* b, const DecodePlan& d, PrefillPlan&
 // workgroups beside the tiles, one per CU, could merge behind the last of their pairs, but whoever ends
 // last then merges sequence after sequence: slower than a kernel on 130 of 150 mixes, by 1-2% on average
 // whatever the number of rounds, 7% at worst (40/8 heads, 928 pairs: 89 -> 95 us).
+// Launches of at most a workgroup per CU, whose loads are counted, end so close together that more than one
+// workgroup may find its sequence complete, and beyond eight pieces each of them reads the maxima twice, past the
+// caches: at head dim 128 a kernel merges those (one sequence of 5900 keys, 23 pieces of 256, 32/8 heads: attention 14.7 us
+// in place, 11.8 by a kernel; 350 drawn batches: a kernel 2-8% slower on average with 2-4 pieces, 3% faster with 5-8 but
+// 3% slower at worst, 2-17% faster from 9 on, 1.5% slower at worst).  At head dim 64 a kernel is 2-19% slower
+// up to 10 pieces and 0-8% faster only from 18 on.
 static bool decode_merges_in_place(const DecodePlan& d, const PrefillPlan& p, const FusePlan& f, int32_t Hkv, int32_t D, int32_t layers) {
     if (!d.in_args || d.num_multi == 0) return false;
     const int64_t cus = device_cus(), wgs = (int64_t)d.total_items * Hkv * layers;
     if (f.arrangement == 2) return false;
     if (f.arrangement == 1) return wgs + (int64_t)p.num_slots * p.max_ranges * Hkv * layers <= 2 * cus;
+    if (D == 128 && wgs <= cus && d.max_pieces > 8) return false;
     return wgs <= cus * (D == 128 ? (d.pages_ahead == 2 ? 2 : 3) : 4);
 }
 

@@ -107,6 +107,7 @@ struct DecodePlan {
     int64_t decode_keys;       // total keys read by decode sequences
     bool    uniform;           // their lengths lie within 25% of each other
     int32_t longest;           // keys of the longest work item
+    int32_t max_pieces;        // items of the sequence that is cut into most
     int32_t pages_ahead;       // pages a wavefront of the decode kernel prefetches (1 or 2)
     bool    counted_loads;     // the decode kernel's form for workgroups that are alone on their CU
     bool    in_args;           // the item list below is valid and replaces the planning kernel

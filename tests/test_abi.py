@@ -439,6 +439,30 @@ def test_a_few_tiles_beside_decodes_that_deal_out_evenly(Hq, Hkv, decodes, chunk
     assert cs.lib().cs_debug_mixed_arrangement(ctypes.byref(b), Hq, Hkv, 128) == want
 
 
+def test_short_launches_merge_sequences_of_many_pieces_by_a_kernel():
+    """The workspace shows who merges cut decode sequences (where a kernel does, no partial is announced): in a launch of at
+    most a workgroup per compute unit (256) the workgroups up to eight pieces a sequence, a kernel beyond at head
+    dim 128; in a launch of more than that the workgroups again."""
+    lib = cs.lib()
+
+    def announced(ctx, Hkv, D):                              # bytes; (nothing is rounded up: 8 query heads a kv head)
+        b, keep = _batch(ctx, [1] * len(ctx), max_blocks=1 << 12)
+        n = lib.cs_debug_decode_items(ctypes.byref(b), Hkv, D, (ctypes.c_uint32 * 1024)(), 1024, None)
+        return n, lib.cs_paged_attention_workspace_bytes(ctypes.byref(b), 8 * Hkv, Hkv, D) - n * 8 * Hkv * (D + 2) * 4
+
+    lib.cs_debug_set_cu_count(256)
+    try:
+        lib.cs_set_decode_split_tokens(256)
+        assert announced([8 * 256 - 1], 8, 128) == (8, 8 * 8 * 8)
+        assert announced([9 * 256 - 1], 8, 128) == (9, 0)
+        assert announced([9 * 256 - 1], 8, 64) == (9, 9 * 8 * 8)
+        assert announced([9 * 256 - 1] + [100] * 23, 8, 128) == (32, 0)            # 256 workgroups
+        assert announced([9 * 256 - 1] + [100] * 24, 8, 128) == (33, 33 * 8 * 8)   # 264
+    finally:
+        lib.cs_set_decode_split_tokens(0)
+        lib.cs_debug_set_cu_count(0)
+
+
 def test_announcements_of_partials_refuse_no_batch_the_static_scratch():
     """15 cut sequences whose partials all but fill the static scratch (67.07 MB of 67.11 MB): the words
     that announce partials to workgroups that merge in place would not fit beside them."""

@@ -71,10 +71,10 @@ def test_captured_layers_replay_bit_identical(maker, shrink):
         np.testing.assert_array_equal(bits(pool_g.tensor), want_pool)
 
 
-# cut sequences alone; cut sequences and tiles of two ranges in one grid, all workgroups resident; tiles that a
+# cut sequences alone, by a kernel (ten pieces of one) and in the grid (eight); cut sequences and tiles of two ranges in one grid, all workgroups resident; tiles that a
 # decode stream outlasts.  (What merges in the grid announces partials by words that the next replay must
 # find cleared: a replay launches with the same number.)
-@pytest.mark.parametrize("ctx,ql,ranges", [([900, 2500, 1700, 40], [1] * 4, 1),
+@pytest.mark.parametrize("ctx,ql,ranges", [([900, 2500, 1700, 40], [1] * 4, 1), ([900, 2000, 1700, 40], [1] * 4, 1),
                                            ([900, 2500, 1700, 40, 2000], [1] * 4 + [40], 2),
                                            ([3000] * 48 + [3000], [1] * 48 + [100], 4)])
 @pytest.mark.parametrize("one_call", [False, True])

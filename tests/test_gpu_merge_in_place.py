@@ -51,16 +51,17 @@ def test_merge_in_place_and_by_kernel_agree(Hq, Hkv, D, ctx, split, chunk):
 
 
 # pieces: fewer than, exactly and more than the eight that a merge holds in flight
-@pytest.mark.parametrize("ctx", [47, 127, 160])
+# (head dim 64: in the grid also beyond eight)
+@pytest.mark.parametrize("ctx,D", [(47, 128), (127, 128), (160, 128), (160, 64)])
 @pytest.mark.parametrize("cus", [256, 2])
-def test_an_infinity_in_v_stays_one_through_the_merge(ctx, cus):
+def test_an_infinity_in_v_stays_one_through_the_merge(ctx, D, cus):
     """The last piece's weight is not zero anywhere, so its infinite feature is infinite in the output and
     the other features are what they are without it."""
-    sh = synth.Shape(8, 2, 128)
+    sh = synth.Shape(8, 2, D)
     b = synth.make_batch(sh, [ctx], [1], synth.generator(98))
     st = Step(b, 98)
     want = st.oracle_attention()
-    st.v_new[0, 1, 77] = float("inf")
+    st.v_new[0, 1, 47] = float("inf")
     pool = cs.Pool(from_bits(st.prior_pool(), "cuda"), 1, b.num_pages, sh.Hkv, sh.D)
     bb = cs.Batch(b.block_tables, b.ctx_lens, b.cu_q_lens)
     cs.cs_kv_append(pool, 0, bb, st.k_new.cuda(), st.v_new.cuda())
@@ -73,8 +74,8 @@ def test_an_infinity_in_v_stays_one_through_the_merge(ctx, cus):
     finally:
         cs.cs_set_decode_split_tokens(0)
         cs.cs_debug_set_cu_count(0)
-    assert (out[0, 4:, 77] == float("inf")).all()
-    out[0, 4:, 77] = torch.from_numpy(want[0, 4:, 77]).to(out)
+    assert (out[0, 4:, 47] == float("inf")).all()
+    out[0, 4:, 47] = torch.from_numpy(want[0, 4:, 47]).to(out)
     assert_attention_close(out, want, "finite features")
 
 
