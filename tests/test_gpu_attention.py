@@ -529,10 +529,10 @@ def test_chunks_are_found_among_any_number_of_sequences(S):
 
 
 @pytest.mark.parametrize("D", [64, 128])
-@pytest.mark.parametrize("ctx,ranges", [(1500, 2), (6900, 6), (8300, 8), (9300, 9), (16500, 16)])
+@pytest.mark.parametrize("ctx,ranges", [(1500, 2), (2500, 3), (3500, 4), (5500, 5), (6900, 6), (8300, 8), (9300, 9), (16500, 16)])
 def test_merge_of_two_to_sixteen_key_ranges(D, ctx, ranges):
-    """prefill_merge_kernel keeps eight ranges' loads in flight and reads the maxima beforehand where there
-    are more: either side of eight, the fewest and the most ranges, with rows that no token uses."""
+    """prefill_merge_kernel keeps two, four or eight ranges' loads in flight and reads the maxima beforehand where
+    there are more than eight: either side of each, the fewest and the most ranges, with rows that no token uses."""
     sh = synth.Shape(4, 2, D)
     b = synth.make_batch(sh, [ctx], [19], synth.generator(48))
     bb = cs.Batch(b.block_tables, b.ctx_lens, b.cu_q_lens)
