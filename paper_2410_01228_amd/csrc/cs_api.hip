@@ -109,7 +109,9 @@ static void plan_decode_loads(const cs_batch* b, DecodePlan& p, int32_t Hkv, int
     // An item longer than everything else a CU has to read ends the launch with its workgroup alone on its CU:
     // then its loads are counted (decode_item), because nothing else there covers a wait.  Any launch of at most a
     // workgroup per CU is such a one, and one with a sequence far longer than the others; items under 512 keys
-    // start and end so close together that 0.9 of a CU's share is enough.  32 sequences of 338-394 keys (256
+    // start and end so close together that 0.9 of a CU's share is enough.  (Append + attention, 160 drawn batches that
+    // the rule takes, five model shapes: 12% faster in the geometric mean, none slower beyond what two runs of a launch
+    // of 10 us differ by.)  32 sequences of 338-394 keys (256
     // workgroups, 40/8 heads; append + attention) 16.4 -> 14.3 us, one of 107-297 keys 11.9-13.3 -> 10.5-11.8, 32 of
     // 4001 (pages of 8, 32/8) 92 -> 83, 62 of 74-4573 95 -> 65; longer
     // items beside others lose: 264 workgroups of 1041 keys at most (0.99 of a share) 34.5 -> 36.4, 336 of 1024 (0.75) 39 -> 42.
@@ -283,7 +285,8 @@ PrefillPlan plan_prefill(const cs_batch* b, int32_t Hq, int32_t Hkv, int32_t D, 
         // workgroups are resident the longest tile decides, beyond that the average tile and a
         // round count halfway between W/512 and its ceiling (tiles end at different times, so
         // rounds blur); every workgroup pays about 8 steps of start-up and store; the partials
-        // cost a launch plus their bytes written and read back at 5 TB/s.
+        // cost a launch plus their bytes written and read back at 5 TB/s.  (The fit is to a merge kernel of four workgroups
+        // a tile, each lane's loads one after the other; the present one takes 2-24 us less, the more the finer the cut.)
         const double avg_steps = (double)total_steps / (double)tiles;
         auto cost = [&](int r) -> double {
             const double W = (double)wgs * r;
@@ -684,10 +687,13 @@ static bool decode_merges_in_place(const DecodePlan& d, const PrefillPlan& p, co
 // Where the fused grid merges cut tiles itself and no kernel follows (in the prefill kernel's own grid one
 // always does).  The last range of a tile adds the others' partials alone on its CU, up to 1 MB for 16
 // ranges, rows without a token included, where the kernel spreads a tile over sixteen workgroups and leaves
-// those rows out; but it saves the kernel's launch, and costs nothing while decode work still runs.  Over
-// 182 mixes with chunks of 2-600 tokens on 300-60000 keys (four model shapes, same box; the kernel had four then): a kernel 3.0% off
+// those rows out; but it saves the kernel's launch, and costs nothing while decode work still runs.  Fitted to
+// 182 mixes with chunks of 2-600 tokens on 300-60000 keys (four model shapes) when the kernel had four workgroups a tile: a kernel 3.0% off
 // the better of the two, 20% at worst; in place 4.9% and 41%; two ranges, or a decode stream of 0.7 of a
-// range's time and more, in place: 1.3%, 13%.
+// range's time and more, in place: 1.3%, 13%.  That kernel took 2-24 us longer than the present one, with which over 200 such
+// mixes this rule is 2.1% off the better of the two, 37% at worst (33 decodes + 27 tokens on 16K keys in 15 ranges, 28/4 heads: 77 us
+// in place, 56 by the kernel); a kernel always 1.3% and 14%, in place always 12% and 94%, in place with two ranges only
+// 0.4% and 11%.
 static bool tiles_merge_in_place(const DecodePlan& d, const PrefillPlan& p, const FusePlan& f, int32_t Hkv, int32_t D, int32_t layers) {
     if (f.arrangement == 0 || p.max_ranges <= 1) return false;
     const double t_decode = (double)layers * d.decode_keys * 2 * Hkv * D * 2 / 6.5e6, t_range = 0.88 * p.range_steps;    // microseconds

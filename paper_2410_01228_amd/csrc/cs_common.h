@@ -67,8 +67,11 @@ struct OwnedBy { int32_t seq, token, q_len, ctx; };
 // increasing) does not lie behind `at`; the first of them if all do.  By the 64 lanes of a wavefront, each
 // of which tries one sequence: one trip to memory for up to 64 sequences, which brings the lengths
 // along, two for up to 4096, where a bisection takes a dependent load for every power of two and
-// another for the lengths.  (Two chunks + four decodes of 17-100 keys, 4/2 heads, D 64: append + attention
-// 11.3 -> 10.9 us; 64 decodes + four 256-token chunks, 40/8 heads: 186.7 -> 185.5.)
+// another for the lengths.  (Append + attention replayed from a graph, which leaves the host out: two chunks + four
+// decodes of 17-100 keys, 4/2 heads, D 64, 9.37 -> 9.09 us; 64 decodes + four 256-token chunks, 40/8, 186.5 -> 185.3;
+// but in the tiles beside a decode stream, whose loads fill the vector memory pipeline, the two trips are longer
+// than a bisection's scalar ones: 128 decodes of 2K-32K keys + 1024 tokens, 64/8, 1399 -> 1407.  Bisection in the tiles
+// alone: 180 drawn mixes 0.3% slower on average, chunks alone 0.2% faster.)
 template <class StartOf>
 __device__ __forceinline__ OwnedBy owner_of(const int32_t* __restrict__ cu_q_lens, const int32_t* __restrict__ ctx_lens,
                                             int32_t first, int32_t n, int32_t at, StartOf start_of)

@@ -264,8 +264,9 @@ __device__ __forceinline__ void append_page_block(
     const uint16_t* ksrc = k_new + (tok_base + tok) * row + (int64_t)h * D + dblk * 8;
     const uint16_t* vsrc = v_new + (tok_base + th * 8) * row + (int64_t)h * D + feat;
     // The rows come in beside the table's entries: one trip to memory less in a workgroup that is little but
-    // trips (the empty asm below keeps the loads in front of the pages' checks).  Append + attention of three
-    // chunks (32/8 heads) 94.5 -> 93.9 us, 32 layers of 24 decodes + a 200-token chunk 1004 -> 1000.
+    // trips (the empty asm below keeps the loads in front of the pages' checks).  Whole steps hardly show it (replayed
+    // from a graph, append + attention of three chunks, 32/8 heads, 98.9 us with and without; eight decodes, by the same
+    // in append_token_block, 16.4 -> 16.1).
     const bool k_row = pos >= first && pos < last, v_rows = vpos >= first && vpos + 8 <= last;
     u32x4 kv = {0u, 0u, 0u, 0u};
     uint16_t e[8] = {0, 0, 0, 0, 0, 0, 0, 0};

@@ -77,9 +77,10 @@ __device__ __forceinline__ void merge_row(const float* __restrict__ base, int64_
 // cut much leave the chip idle, so what counts is the chain of loads: a lane has one piece of one row and up to
 // eight ranges of it in flight.  (Four such pieces one after the other, each range's loads too, append +
 // attention of 26 tokens on 5-12K keys, 28/4 heads: 44.2 -> 34.4 us; 128 on 30K, 32/8: 107 -> 83; 95 on 13K, 40/8:
-// 74 -> 53.)  (Merged by the last range's workgroup instead, alone on its CU,
-// chunks of 2-600 tokens on 500-60000 keys took 7% longer in the geometric mean of 140, 39% at worst: 2-3
-// tokens on 0.6-12K keys, 64/8 heads, 48 -> 65 us.)
+// 74 -> 53.  At head dim 64 half the lanes have no row; eight workgroups a tile without idle lanes are 3% faster
+// from 64 tiles on and 1% slower below, 0.01% over 70 drawn batches.)  (Merged by the last range's workgroup instead,
+// alone on its CU, chunks of 2-600 tokens on 500-60000 keys took 7% longer in the geometric mean of 140, 39% at worst, than
+// with the four workgroups that did the four pieces in turn: 2-3 tokens on 0.6-12K keys, 64/8 heads, 48 -> 65 us.)
 constexpr int kMergeParts = 16;
 template <int D, class E>
 __global__ __launch_bounds__(kPrefillThreads) void prefill_merge_kernel(
